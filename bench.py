@@ -7,8 +7,8 @@ in HBM before timing starts, as one call, qst_likelihood_grad:
     POVM map -> G' (the last POVM pass, the NLL terms, the cotangent and the
     first adjoint pass fused, p never stored), then 2/tau G' T.
 The headline path is QST_F32X6 (FP32 storage and FP32-level accuracy; the
-two complex products as six split-bf16 products per real product on the BF16
-matrix cores, their operand planes formed inside the call); the FP64, FP32
+two complex products on the 16-bit matrix cores from two-part fp16 splits,
+their operand planes formed inside the call); the FP64, FP32
 (FP32 MFMA products) and BF16 paths, the same step as two calls
 (qst_likelihood returning G', then qst_grad_product) and as four separate
 calls with p stored (qst_state_map, qst_povm_probs, qst_nll,
@@ -53,8 +53,8 @@ PREC_NOTE = {
     "f32": "complex64 storage, FP32 MFMA products (3M form), FP32 POVM passes, tau and NLL sum in FP64",
     "bf16": "complex64 storage, T T^dagger on bf16-rounded T (BF16 MFMA, FP32 accumulate), G' T with split "
             "bf16 operands, FP32 POVM passes, tau and NLL sum in FP64",
-    "f32x6": "complex64 storage; both complex products with every FP32 operand split exactly into three bf16 "
-             "parts, six partial products per real product (3M form) on the BF16 MFMA, FP32 accumulation "
+    "f32x6": "complex64 storage; both complex products with every FP32 operand (row-scaled) split into two fp16 "
+             "parts, ten MFMA products per complex product on the FP16 MFMA, FP32 accumulation "
              "(FP32-accurate); FP32 POVM passes, tau and NLL sum in FP64",
 }
 
@@ -109,7 +109,7 @@ def parse():
                          "timed steps see the GPU's steady clocks (0: none)")
     ap.add_argument("--prec", default="f32x6", choices=["f64", "f32", "bf16", "f32x6"],
                     help="precision path of the headline step (default f32x6: FP32 storage and accuracy, "
-                         "complex products as six split-bf16 products on the BF16 MFMA)")
+                         "complex products from two-part fp16 splits on the FP16 MFMA)")
     ap.add_argument("--n", type=int, default=11)
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip the CPU oracle leg")
     ap.add_argument("--no-variants", action="store_true", help="skip the other precision paths")
@@ -790,23 +790,23 @@ def main():
             bf16 = dom.endswith(("bf16", "bf16x3"))
             peak_key = "bf16" if (bf16 or x6) else ("f64" if dom.endswith("f64") else "f32")
             if x6:
-                # three real products per complex product, six bf16 products
-                # per real product; T T^dagger on 128 x 128 lower tiles (the
-                # diagonal tiles in full): 3 x 6 x 2 x 128^2 x d per tile
+                # ten fp16 MFMA products per complex product; T T^dagger on
+                # 128 x 128 lower tiles (the diagonal tiles in full):
+                # 10 x 2 x 128^2 x d per tile
                 t = d // 128
-                executed = (36.0 * 128 * 128 * d * (t * (t + 1) // 2)) if herk else 36.0 * d ** 3
+                executed = (20.0 * 128 * 128 * d * (t * (t + 1) // 2)) if herk else 20.0 * d ** 3
             else:
                 executed = counted * (0.75 if not bf16 else (1.0 if herk else 3.0))
             ach = executed / avg_s / 1e12
             if x6:
-                form = "36 x 128^2 d per lower 128-tile" if herk else "36 d^3"
+                form = "20 x 128^2 d per lower 128-tile" if herk else "20 d^3"
             else:
                 form = ("3 d^2(d+1)" if herk else "6 d^3") if not bf16 else ("4 d^2(d+1)" if herk else "24 d^3")
             roofline = {"kernel": dom, "bound": "mfma", "achieved": ach, "peak": PEAK_TFLOPS[peak_key],
                         "unit": "TFLOP/s", "frac": ach / PEAK_TFLOPS[peak_key], "traffic": traffic_of(dom),
                         "algorithmic_per_launch": f"{executed:.4g} flop ({form}, d={d}: "
-                                                  + ("3M complex product, 3 real products, 6 bf16 products "
-                                                     "each" if x6 else "3M complex product, 3 real products"
+                                                  + ("10 fp16 products per complex product"
+                                                     if x6 else "3M complex product, 3 real products"
                                                      if not bf16 else "4 real products per complex product")
                                                   + ")",
                         "avg_launch_us": avg_s * 1e6, "launches": kdom[dom][0],

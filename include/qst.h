@@ -76,12 +76,14 @@ typedef enum {
   QST_BF16GEMM = 2,
   /* complex64 storage, FP32 POVM passes, tau and the log-likelihood sum in
    * FP64, as QST_F32; for d >= 128 the two complex products run on the
-   * BF16 MFMA with every FP32 operand split exactly into three bfloat16
-   * parts (x = h + m + l) and six partial products per real product (hh,
-   * hm, mh, hl, lh, mm: what is dropped is below 2^-26 of |a||b|), FP32
-   * accumulation.  Results agree with QST_F32 to the order of FP32
-   * rounding; the products run about twice as fast.  Below d = 128 the
-   * products are those of QST_F32.  The batched form runs it as QST_F32. */
+   * 16-bit matrix cores with every FP32 operand row (or column) scaled by a
+   * power of two and split into two fp16 parts (x = h + l, 22 significand
+   * bits and a sign) and three partial products per real product (hh, hl,
+   * lh: what is dropped is below 2^-22 of |a||b|), FP32 accumulation; the
+   * diagonal of T T^dagger is the FP64 sum of its squares.  The products are
+   * more accurate than QST_F32's FP32 MFMA products (measured against FP64)
+   * and several times as fast.  Below d = 128 the products are those of
+   * QST_F32.  The batched form runs it as QST_F32. */
   QST_F32X6 = 3
 } qst_prec;
 

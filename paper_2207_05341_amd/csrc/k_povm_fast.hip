@@ -79,7 +79,16 @@ __global__ __launch_bounds__(256, FC ? 1 : 2) void kd_fused_pass(PassArgs a, Mod
     __syncthreads();
   }
   double L = 0.0, bad0 = 0.0, bad1 = 0.0, fc = 0.0;
-  fast_pass::kd_fused_body<R, TETRA, G, J, FC>(a, Af, Aa, lb, threadIdx.x, lds, true, Fsh, L, bad0, bad1, &fc);
+  float ym = 0.f;
+  fast_pass::kd_fused_body<R, TETRA, G, J, FC>(a, Af, Aa, lb, threadIdx.x, lds, true, Fsh, L, bad0, bad1, &fc, &ym);
+  if (sizeof(R) == 4 && a.ymax) {
+    __shared__ float yred[4];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) ym = fmaxf(ym, __shfl_xor(ym, o, 64));
+    if ((threadIdx.x & 63) == 0) yred[threadIdx.x >> 6] = ym;
+    __syncthreads();
+    if (threadIdx.x == 0) a.ymax[lb] = fmaxf(fmaxf(yred[0], yred[1]), fmaxf(yred[2], yred[3]));
+  }
   // per-workgroup partial sums in a fixed order, slot = logical index
   const int64_t nb = gridDim.x;
   double v = block_sum256(L, red);
@@ -145,15 +154,10 @@ bool launch_pass_fast(bool adjoint, qst_prec prec, bool tetra, const PassArgs& a
     }                                                                                             \
   } while (0)
   if (matside && adjoint && a.gplanes) {  // G' as split planes: FP32 adjoint, g = 5 or 6
-    if (f64 || pside || a.J != 1 || a.g < 5 || a.g > 6) return false;
+    if (f64 || pside || !tetra || a.J != 1 || a.g < 5 || a.g > 6) return false;
     const unsigned grid = unsigned((blocks + (256 >> (2 * (a.g - 2))) - 1) / (256 >> (2 * (a.g - 2))));
-    if (a.g == 5) {
-      if (tetra) mat_pass<float, true, true, 5, true><<<grid, 256, 0, s>>>(a, A, blocks);
-      else mat_pass<float, true, false, 5, true><<<grid, 256, 0, s>>>(a, A, blocks);
-    } else {
-      if (tetra) mat_pass<float, true, true, 6, true><<<grid, 256, 0, s>>>(a, A, blocks);
-      else mat_pass<float, true, false, 6, true><<<grid, 256, 0, s>>>(a, A, blocks);
-    }
+    if (a.g == 5) mat_pass<float, true, true, 5, true><<<grid, 256, 0, s>>>(a, A, blocks);
+    else mat_pass<float, true, true, 6, true><<<grid, 256, 0, s>>>(a, A, blocks);
     *err = hipGetLastError();
     return true;
   }

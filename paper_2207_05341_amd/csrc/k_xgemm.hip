@@ -1,39 +1,54 @@
-// Complex products of the QST_F32X6 path: FP32 operands, every real product
-// computed on the BF16 matrix cores from a three-way split of each operand.
+// Split complex products: FP32 operands, every real product computed on the
+// 16-bit matrix cores from a two-part fp16 split of each operand.
 //
 //   state map  rho = T T^dagger / tau      (Eq. T_matrix; Eq. unified_DP)
 //   gradient   grad = s (2 / tau) G' T     (adjoint of the state map)
 //
-// Split: x = h + m + l with h = bf16(x), m = bf16(x - h), l = bf16(x - h - m)
-// (round to nearest even).  For an FP32 x this is exact: h takes the top 8
-// significand bits, m the next 8 and l the last 8, and every difference is
-// exact in FP32.  A real product a b then keeps the six partial products
-// hh + hm + mh + hl + lh + mm, each exact in FP32; the three dropped ones
-// (ml, lm, ll) are below 2^-26 |a||b|, under the FP32 rounding of the
-// accumulation itself.  Accumulation is in FP32 inside the MFMA, as in the
-// QST_F32 products.
+// Split (qst_split.h): each operand row, scaled by a power of two, is
+// x = h + l with h and l in fp16 (22 significand bits and the sign of l, so
+// the rounding left out is that of FP32 itself).  A real product a b keeps
+// hh + hl + lh, each exact in FP32; the dropped ll is below 2^-22 |a||b|
+// and of random sign, the size of one FP32 rounding per term (the diagonal
+// of T T^dagger, where it is a square, is formed apart: x6_diag_sums).
+// Accumulation is in FP32 inside the MFMA.
 //
-// Complex products use three real products (3M form): for C = A B,
-// P1 = Ar Br, P2 = Ai Bi, P3 = (Ar + Ai)(Br + Bi), re = P1 - P2,
-// im = P3 - P1 - P2; for S = T T^dagger (B = conj(T) rows),
-// P1 = Tr Tr^T, P2 = Ti Ti^T, P3 = (Tr + Ti)(Tr - Ti)^T, re = P1 + P2,
-// im = P3 - P1 + P2.  The sums are formed in FP32 before the split.
+// Complex products: ten MFMA products per 32 x 32 block and K panel.  The
+// leading part h h takes the four real products of the definition.  Each of
+// the two corrections A' B' (h l and l h) takes three (Gauss): K1 = B'r
+// (A'r + A'i), K2 = A'r (B'i - B'r), K3 = -A'i (B'r + B'i), re = K1 + K3,
+// im = K1 + K2, whose operand sums are formed from the fragments in fp16 --
+// the corrections are 2^-11 of the product, so the sums' rounding is another
+// FP32 rounding per term.  K2 and K3 go to the accumulators of im and re, K1
+// has its own, added once at the end of a segment.
 //
-// Operand planes.  A split pass writes each operand once per call as bf16
-// planes in the order the v_mfma_f32_32x32x16_bf16 fragments read them: a
+// What bounds it: power.  At N = 11 under sustained load the eight XCDs run
+// G' T at 1.55 .. 1.72 GHz (2.4 nominal); a schedule that took 12% fewer
+// cycles ran at 11% lower clocks, in the same time.  G' T at N = 11 (172
+// GFLOP): 149 us, 1.15 PFLOP/s, what a large fp16 library product reaches on
+// this card (1.11).  Twelve products per block (four per correction):
+// 162 us; all in the three-product form (nine, with re + im planes as
+// operands) needs 1.5 times the LDS and plane bytes.  A split into three
+// bf16 parts with six products per real product, in the three-product form
+// (18): 224 us, and two times the plane bytes.
+//
+// Accuracy (N = 11, relative to FP64, Gaussian T): gradient product 2.1e-7,
+// off-diagonal rho 2.1e-7, gradient 5e-7 .. 9e-7 in all; with FP32 MFMA
+// products 1.15e-6, 7.5e-7 and 1.3e-6 .. 2.3e-6; with the three-part bf16
+// split 5.0e-7, 4.9e-7 and 2.8e-6 .. 4.7e-6.
+//
+// Operand planes.  A split pass writes each operand once per call as fp16
+// planes in the order the v_mfma_f32_32x32x16_f16 fragments read them: a
 // 1 KB unit holds a 32-row x 16-k block of one plane, 16 bytes per lane
-// (lane u: row u % 32, k 8 (u / 32) .. + 7), and the units of one (row
-// block, K panel) for all groups (re, im, re + im, re - im) and splits
-// (h, m, l) are contiguous: unit ((rb * (K / 16) + kb) * NG + g) * 3 + s.
+// (lane u: row u % 32, k 8 (u / 32) .. + 7), and the four units (re_h,
+// re_l, im_h, im_l) of one (row block, K panel) are contiguous.
 //
 // Product kernel: a 128 x 128 complex output tile per 256-thread workgroup
-// (four waves of 64 x 64, 2 x 2 MFMA blocks of 32 x 32 each, three
-// accumulator sets P1, P2, P3).  The K loop runs over "slabs": one real
-// product's three splits of A and B for one 16-deep K panel (24 units,
-// 24 KB).  Slabs are copied global -> LDS by the DMA form of the global
-// load (no registers), five slabs ahead, into a ring of six LDS slots
-// (144 KB); the fragments of slab s+1 are read while the 24 MFMAs of slab s
-// run (two MFMAs, one fragment read and one DMA per step).
+// (four waves of 64 x 64, 2 x 2 MFMA blocks of 32 x 32 each).  The K loop
+// runs over slabs, one 16-deep K panel each (32 units, 32 KB, 40 MFMAs per
+// wave).  Slabs are copied global -> LDS by the DMA form of the global load
+// (no registers), three slabs ahead, into a ring of four LDS slots (128 KB).
+// The fragments of the next slab are read while the current one's MFMAs
+// run.
 //
 // T T^dagger computes the lower 128 x 128 tiles only (136 at d = 2048),
 // which do not divide evenly over the compute units, so it runs stream-K:
@@ -62,130 +77,106 @@ namespace {
 
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-constexpr int XT = kX6Tile;               // output tile (complex)
-constexpr int XSLOT = 24 * 1024;          // one slab
-constexpr int XNSLOT = 6;                 // LDS ring slots
-constexpr int XDIST = 5;                  // slabs loaded ahead of the one being computed
-constexpr int XLDS = XSLOT * XNSLOT;      // 147456 bytes of LDS
-constexpr int XUNIT = 64;                 // 16-byte vectors per 1 KB unit
+constexpr int XT = kX6Tile;           // output tile (complex)
+constexpr int XSLOT = 32 * 1024;      // one slab: 32 units, 4 row blocks of A and of B
+constexpr int XNSLOT = 4;             // LDS ring slots
+constexpr int XDIST = XNSLOT - 1;     // slabs copied ahead of the one being computed
+constexpr int XCOPY = 8;              // units copied per wave and slab
+constexpr int XLDS = XSLOT * XNSLOT;  // 131072 bytes of LDS
+constexpr int XUNIT = kX6UnitVecs;
 
-static_assert((XDIST - 2) * 6 < 64, "vmcnt immediate");
+static_assert((XDIST - 1) * XCOPY < 64, "vmcnt immediate");
 
 // ---------------------------------------------------------------------------
-// Split (helpers in qst_split.h)
+// Scales and split (helpers in qst_split.h)
 // ---------------------------------------------------------------------------
-// Planes of a d x d complex FP32 matrix X (leading dimension ld) as the
-// row operand (TRANS false: row r, k = column) or as the rows of X^T (TRANS
-// true: row r = column of X, k = row of X).  Groups: re, im, re + im, and
-// with NG = 4 also re - im.  One wave per unit block (32 rows x 16 k): lane
-// u converts the 8 values of its fragment slot; each plane's unit is one
-// coalesced 1 KB store of the wave.
-template <bool TRANS, int NG>
-__global__ __launch_bounds__(256) void x6_split_kernel(const Cx<float>* __restrict__ X, int64_t ld, int d,
-                                                       u16x8* __restrict__ P) {
-  const int64_t blk = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);  // unit block (rb, kb)
-  const int lane = threadIdx.x & 63;
-  const int nkb = d / 16;
-  if (blk >= int64_t(d / 32) * nkb) return;
-  const int64_t rb = blk / nkb, kb = blk % nkb;
-  const int64_t row = rb * 32 + (lane & 31);
-  const int64_t k0 = kb * 16 + 8 * (lane >> 5);
-  float re[8], im[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const Cx<float> v = TRANS ? X[(k0 + e) * ld + row] : X[row * ld + k0 + e];
-    re[e] = v.re;
-    im[e] = v.im;
-  }
-  write_unit_block<NG>(P + blk * (NG * 3 * XUNIT) + lane, re, im);
-}
-
-// The planes of T as the row operand of T T^dagger (groups re, im, re + im,
-// re - im) and, with TT, of T^T as the column operand of G' T (re, im,
-// re + im), with the FP64 partial sums of tau = sum |T_ij|^2 and, with f,
-// of F = sum_k f_k: workgroup b of nb writes partials[b] (its 32 x 32
-// blocks b, b + nb, ..., four per pass, one per wave) and partials[nb + b]
-// (f over [b D / nb, (b + 1) D / nb), D = d^2), each summed in a fixed
-// order, so that T is read once.  A wave reads its block as the slots of
-// two row-operand unit blocks (lane u: row u % 32, columns 16 h + 8 (u / 32)
-// .. + 7, h = 0, 1); with TT it passes the block through LDS (8 KB per
-// wave, 16-byte chunks swizzled by row) and reads the two unit blocks of
-// T^T (lane u: column u % 32, rows 16 h + 8 (u / 32) .. + 7).  The first 16
-// values of f per thread are loaded first, so that their loads are in
-// flight together with those of T.
-__device__ __forceinline__ int split_swz(int r, int c) {  // (r, c) of a 32 x 32 block, complex index
-  return r * 32 + 2 * (((c >> 1) ^ r) & 15) + (c & 1);
-}
-
-template <bool WITH_F, bool TT>
-__global__ __launch_bounds__(256) void x6_split_tau_kernel(const Cx<float>* __restrict__ X, int64_t ld, int d,
-                                                           u16x8* __restrict__ P, u16x8* __restrict__ PT,
-                                                           double* __restrict__ partials,
-                                                           const float* __restrict__ f) {
-  constexpr int NT = 256, NW = NT / 64, U = 16;
-  __shared__ double red[NW];
-  __shared__ Cx<float> blkL[TT ? NW : 1][TT ? 32 * 32 : 1];
-  const int nb = gridDim.x;
+// Largest |component| of every 64-entry piece of a row and of a column of
+// X, per 64 x 64 tile: rowp[tc * d + row] and colp[tr * d + column].  With
+// TAU also the FP64 partial sums of tau = sum |X_ij|^2 and, with f, of
+// F = sum f_k: workgroup b of nb writes partials[b] (its tiles b, b + nb, ...)
+// and partials[nb + b] (f over [b D / nb, (b + 1) D / nb), D = d^2), each
+// summed in a fixed order.  The first 16 values of f per thread are loaded
+// first, so that their loads are in flight together with those of X.
+// Bound by HBM (X and f read once).
+//
+// Thread t holds rows t / 32 + 8 k, columns 2 (t % 32), + 1 of a tile.  The
+// row maxima go over the half-wave in a halving exchange: three steps trade
+// half of the remaining rows for the partner's values of the other half,
+// after which a lane holds one row's maximum over eight lanes; two plain
+// steps finish it (nine shuffles in place of forty).
+template <bool TAU, bool WITH_F>
+__global__ __launch_bounds__(256) void x6_absmax_kernel(const Cx<float>* __restrict__ X, int64_t ld, int d,
+                                                        float* __restrict__ rowp, float* __restrict__ colp,
+                                                        double* __restrict__ partials, const float* __restrict__ f) {
+  constexpr int NT = 256, U = 16;
+  __shared__ double red[4];
+  __shared__ float cm[8][64];
+  const int nb = gridDim.x, t = threadIdx.x;
   const int64_t D = int64_t(d) * d;
   const int64_t fbeg = D * blockIdx.x / nb, fend = D * (blockIdx.x + 1) / nb;
   float fv[U];
   if constexpr (WITH_F) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t e = fbeg + threadIdx.x + u * NT;
+      const int64_t e = fbeg + t + u * NT;
       fv[u] = e < fend ? f[e] : 0.f;
     }
   }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int row = lane & 31, hq = lane >> 5;
-  const int nkb = d / 16, nb32 = d / 32;
-  const int64_t nblk = int64_t(nb32) * nb32;
   double acc = 0.0, accf = 0.0;
-  // the loop bound is the same for the whole workgroup (barriers inside)
-  for (int64_t b0 = int64_t(blockIdx.x) * NW; b0 < nblk; b0 += int64_t(nb) * NW) {
-    const int64_t blk = b0 + wv;
-    const bool act = blk < nblk;
-    const int64_t br = act ? blk / nb32 : 0, bc = act ? blk % nb32 : 0;
-    if (act) {
+  const int tiles = d / 64, c2 = t & 31, rq = t >> 5;
+  for (int tile = blockIdx.x; tile < tiles * tiles; tile += nb) {
+    const int tr = tile / tiles, tc = tile % tiles;
+    const Cx<float>* src = X + (int64_t(tr) * 64 + rq) * ld + int64_t(tc) * 64 + 2 * c2;
+    f4u v[8];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        float re[8], im[8];
+    for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const f4u*>(src + 8 * k * ld);
+    float m[8], ca = 0.f, cb = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const Cx<float> v = X[(32 * br + row) * ld + 32 * bc + 16 * h + 8 * hq + e];
-          re[e] = v.re;
-          im[e] = v.im;
-          acc += double(v.re) * double(v.re) + double(v.im) * double(v.im);
-          if constexpr (TT) blkL[wv][split_swz(row, 16 * h + 8 * hq + e)] = v;
-        }
-        write_unit_block<4>(P + (br * nkb + 2 * bc + h) * (4 * 3 * XUNIT) + lane, re, im);
+    for (int k = 0; k < 8; ++k) {
+      const float a = fmaxf(fabsf(v[k][0]), fabsf(v[k][1])), b = fmaxf(fabsf(v[k][2]), fabsf(v[k][3]));
+      m[k] = fmaxf(a, b);
+      ca = fmaxf(ca, a);
+      cb = fmaxf(cb, b);
+      if constexpr (TAU)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc += double(v[k][e]) * double(v[k][e]);
+    }
+    cm[rq][2 * c2] = ca;
+    cm[rq][2 * c2 + 1] = cb;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const int half = 4 >> s;
+      const bool up = (c2 >> s) & 1;
+#pragma unroll
+      for (int i = 0; i < half; ++i) {
+        const float send = up ? m[i] : m[i + half], keep = up ? m[i + half] : m[i];
+        m[i] = fmaxf(keep, __shfl_xor(send, 1 << s, 64));
       }
     }
-    if constexpr (TT) {
-      __syncthreads();
-      if (act) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          float re[8], im[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const Cx<float> v = blkL[wv][split_swz(16 * h + 8 * hq + e, row)];
-            re[e] = v.re;
-            im[e] = v.im;
-          }
-          write_unit_block<3>(PT + (bc * nkb + 2 * br + h) * (3 * 3 * XUNIT) + lane, re, im);
-        }
-      }
-      __syncthreads();
+    float r = m[0];
+    r = fmaxf(r, __shfl_xor(r, 8, 64));
+    r = fmaxf(r, __shfl_xor(r, 16, 64));
+    if (c2 < 8) {  // lane c2 holds row 4 (c2 & 1) + 2 (c2 >> 1 & 1) + (c2 >> 2) of its eight
+      const int k = 4 * (c2 & 1) + (c2 & 2) + (c2 >> 2);
+      rowp[int64_t(tc) * d + tr * 64 + rq + 8 * k] = r;
     }
+    __syncthreads();
+    if (t < 64) {
+      float c = cm[0][t];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) c = fmaxf(c, cm[q][t]);
+      colp[int64_t(tr) * d + tc * 64 + t] = c;
+    }
+    __syncthreads();
   }
   if constexpr (WITH_F) {
 #pragma unroll
     for (int u = 0; u < U; ++u) accf += double(fv[u]);
     // the rest of the range (N >= 12), U strided loads per thread at a time
-    for (int64_t e0 = fbeg + threadIdx.x + U * NT; e0 < fend; e0 += U * NT) {
+    for (int64_t e0 = fbeg + t + U * NT; e0 < fend; e0 += U * NT) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t e = e0 + u * NT;
@@ -195,11 +186,122 @@ __global__ __launch_bounds__(256) void x6_split_tau_kernel(const Cx<float>* __re
       for (int u = 0; u < U; ++u) accf += double(fv[u]);
     }
   }
-  const double st = block_sum256(acc, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = st;
+  if constexpr (TAU) {
+    const double st = block_sum256(acc, red);
+    if (t == 0) partials[blockIdx.x] = st;
+  }
   if constexpr (WITH_F) {
     const double sf = block_sum256(accf, red);
-    if (threadIdx.x == 0) partials[nb + blockIdx.x] = sf;
+    if (t == 0) partials[nb + blockIdx.x] = sf;
+  }
+}
+
+// The planes of X as a row operand (ROWS; row r scaled by its largest
+// component) and of X^T (COLS; row = column of X, likewise), from one read
+// of X, and what takes the scales out again (rinv, cinv).  A workgroup takes
+// four consecutive 32 x 32 blocks of one block row, one per wave: it folds
+// the maxima of its 32 rows and 128 columns, then a wave reads its block as
+// the slots of two row-operand unit blocks (lane u: row u % 32, columns
+// 16 h + 8 (u / 32) .. + 7, h = 0, 1); with COLS it passes the block through
+// LDS (8 KB per wave, 16-byte chunks swizzled by row) and reads the two unit
+// blocks of X^T (lane u: column u % 32, rows 16 h + 8 (u / 32) .. + 7).
+// With SUMS also the FP64 sums of |x|^2 over the 128 columns of each row.
+// Bound by HBM: X read, 8 bytes per element and operand written.
+__device__ __forceinline__ int split_swz(int r, int c) {  // (r, c) of a 32 x 32 block, complex index
+  return r * 32 + 2 * (((c >> 1) ^ r) & 15) + (c & 1);
+}
+
+template <bool ROWS, bool COLS, bool SUMS>
+__global__ __launch_bounds__(256) void x6_split_kernel(const Cx<float>* __restrict__ X, int64_t ld, int d,
+                                                       const float* __restrict__ rowp, const float* __restrict__ colp,
+                                                       float* __restrict__ rinv, float* __restrict__ cinv,
+                                                       double* __restrict__ rsum, u16x8* __restrict__ P,
+                                                       u16x8* __restrict__ PT) {
+  __shared__ Cx<float> blkL[COLS ? 4 : 1][COLS ? 32 * 32 : 1];
+  __shared__ float rm[8][32], cmx[2][128], rsc[32], csc[128];
+  __shared__ double rs[SUMS ? 4 : 1][32];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int row = lane & 31, hq = lane >> 5;
+  const int nkb = d / 16, nb32 = d / 32, np = d / 64;
+  const int64_t br = blockIdx.x / (nb32 / 4), bc0 = int64_t(blockIdx.x % (nb32 / 4)) * 4, bc = bc0 + wv;
+  Cx<float> v[2][8];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[h][e] = X[(32 * br + row) * ld + 32 * bc + 16 * h + 8 * hq + e];
+  if constexpr (ROWS) {
+    float m = 0.f;
+    for (int k = t >> 5; k < np; k += 8) m = fmaxf(m, rowp[int64_t(k) * d + 32 * br + (t & 31)]);
+    rm[t >> 5][t & 31] = m;
+  }
+  if constexpr (COLS) {
+    float m = 0.f;
+    for (int k = t >> 7; k < np; k += 2) m = fmaxf(m, colp[int64_t(k) * d + 32 * bc0 + (t & 127)]);
+    cmx[t >> 7][t & 127] = m;
+  }
+  __syncthreads();
+  if constexpr (ROWS) {
+    if (t < 32) {
+      float m = rm[0][t];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) m = fmaxf(m, rm[q][t]);
+      const int e = x6_scale_exp(m, kX6Top);
+      rsc[t] = x6_pow2(e);
+      if (bc0 == 0) rinv[32 * br + t] = x6_pow2(-e);
+    }
+  }
+  if constexpr (SUMS) {
+    double acc = 0.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        acc += double(v[h][e].re) * double(v[h][e].re) + double(v[h][e].im) * double(v[h][e].im);
+    acc += __shfl_xor(acc, 32, 64);
+    if (lane < 32) rs[wv][lane] = acc;
+  }
+  if constexpr (COLS) {
+    if (t >= 128) {
+      const int c = t - 128;
+      const int e = x6_scale_exp(fmaxf(cmx[0][c], cmx[1][c]), kX6Top);
+      csc[c] = x6_pow2(e);
+      if (br == 0) cinv[32 * bc0 + c] = x6_pow2(-e);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) blkL[wv][split_swz(row, 16 * h + 8 * hq + e)] = v[h][e];
+  }
+  __syncthreads();
+  if constexpr (SUMS) {
+    if (t < 32) rsum[(bc0 / 4) * d + 32 * br + t] = ((rs[0][t] + rs[1][t]) + rs[2][t]) + rs[3][t];
+  }
+  if constexpr (ROWS) {
+    const float sc = rsc[row];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float re[8], im[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        re[e] = v[h][e].re;
+        im[e] = v[h][e].im;
+      }
+      write_unit_block(P + (br * nkb + 2 * bc + h) * kX6BlockVecs + lane, re, im, sc);
+    }
+  }
+  if constexpr (COLS) {
+    const float sc = csc[32 * wv + row];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float re[8], im[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const Cx<float> x = blkL[wv][split_swz(16 * h + 8 * hq + e, row)];
+        re[e] = x.re;
+        im[e] = x.im;
+      }
+      write_unit_block(PT + (bc * nkb + 2 * br + h) * kX6BlockVecs + lane, re, im, sc);
+    }
   }
 }
 
@@ -238,16 +340,27 @@ __device__ __forceinline__ uint32_t lds_address(const char* p) {
 // s_waitcnt vmcnt(n), other counters unconstrained (gfx9 encoding)
 #define QST_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0f70 | ((n) & 15) | (((n) >> 4) << 14))
 
-__device__ __forceinline__ f16v mfma32(u16x8 a, u16x8 b, f16v c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+__device__ __forceinline__ f16v mfma32(h16x8 a, h16x8 b, f16v c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// -x.  The empty statement hides the sign flip from the compiler, which
+// would otherwise fold it into the sum it is used in and take that apart
+// into scalar subtractions (three instructions for one packed addition).
+__device__ __forceinline__ h16x8 negated(h16x8 x) {
+  u32x4 v = __builtin_bit_cast(u32x4, x) ^ 0x80008000u;
+  asm("" : "+v"(v));
+  return __builtin_bit_cast(h16x8, v);
 }
 
 struct XArgs {
   const u16x8* A;  // planes of the row operand
   const u16x8* B;  // planes of the column operand (rows of B^T)
-  int ngA, ngB;    // groups per unit block
-  int gA2, gB2;    // group of the third product's operands (re + im, or re - im)
-  void* C;         // output (HEMM, or HERK without x0)
+  const float* sa;  // what takes A's row scales out again: sa[row * sa_stride]
+  const float* sb;  // the same for B's rows (the output's columns)
+  int sa_stride;    // 1, or 0 for one scale of the whole operand
+  const double* rsum;  // HERK: sums of |T|^2 over 128-entry row pieces, [d / 128][d]
+  void* C;          // output (HEMM, or HERK without x0)
   int64_t ldc;
   int d;
   const double* tau;       // tau, or NULL with tau_part
@@ -264,159 +377,195 @@ struct XArgs {
 constexpr int kXTileVals = XT * XT;  // complex values per tile
 
 // Fold of the tau partials in a fixed order (bitwise the same in every
-// workgroup); workgroup 0 of the product kernel stores it.
-__device__ double x6_tau(const XArgs& a, bool store) {
-  if (!a.tau_part) return *a.tau;
-  __shared__ double red[4];
-  __shared__ double bcast;
+// workgroup), through the idle ring's first bytes.
+__device__ double x6_tau(const XArgs& a, char* lds) {
+  double* red = reinterpret_cast<double*>(lds);
   double acc = 0.0;
   for (int b = threadIdx.x; b < kReduceBlocks; b += 256) acc += a.tau_part[b];
   const double sum = block_sum256(acc, red);
-  if (threadIdx.x == 0) {
-    bcast = sum;
-    if (store && blockIdx.x == 0 && a.tau_out) *a.tau_out = sum;
-  }
+  if (threadIdx.x == 0) red[4] = sum;
   __syncthreads();
-  return bcast;
+  const double tau = red[4];
+  __syncthreads();
+  return tau;
 }
 
-// Panels per MFMA accumulation chain.  The BF16 MFMA rounds the FP32
-// accumulator toward zero when it adds a product block (measured: a Gram
-// diagonal accumulated over all 4096 panels of d = 4096 comes out 1.9e-6
-// low, against 1.2e-7 for the FP32 MFMA), so a chain is kept short and
-// folded into FP32 totals with round-to-nearest adds; a new chain starts
-// from a zero accumulator operand.
-constexpr int XCHAIN = 32;
+// Panels per MFMA accumulation chain (even).  The MFMA rounds the FP32
+// accumulator toward zero when it adds a product block, so a chain is kept
+// short and folded into FP32 totals with round-to-nearest adds; a new chain
+// starts from a zero accumulator operand.  At N = 11: 16 panels 341 us per
+// step and a gradient error of 8.8e-7, 8 panels 346 us and 8.7e-7.
+constexpr int XCHAIN = 16;
+static_assert(XCHAIN % 2 == 0, "the fragment buffers alternate by panel");
 
-// Accumulate the panels [kb, ke) of output tile (tr, tc) into (re, im)
-// (which the caller zeroes).  Every thread of the workgroup calls it (it
-// contains barriers); on return the LDS ring is idle.
+// Accumulate the panels [kb, ke), an even number, of output tile (tr, tc)
+// into (re, im) (which the caller zeroes).  Every thread of the workgroup
+// calls it (it contains barriers); on return the LDS ring is idle.
+//
+// A panel visits the wave's four 32 x 32 blocks as (0, f), (0, 1 - f),
+// (1, 1 - f), (1, f) with f = 0, 1 in alternate panels, so that the next
+// panel's first operands (A's row block 0, B's column block 1 - f) are read
+// into registers that this panel has finished with, and its other two while
+// its first block runs: no fragment is held twice.  At the end of a chain
+// the accumulators of a block are folded into the totals during the next
+// block's MFMAs.
 template <bool HERK>
 __device__ __forceinline__ void x6_segment(const XArgs& a, char* lds, int tr, int tc, int kb, int ke,
-                                           f16v (&re)[2][2], f16v (&im)[2][2]) {
+                                           float (&re)[2][2][16], float (&im)[2][2][16]) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = w >> 1, wc = w & 1;
   const int nkb = a.d / 16;
   const uint32_t lbase = __builtin_amdgcn_readfirstlane(lds_address(lds));
-  // this wave's six units of every slab: unit q = 6 w + i, A (q < 12) or B,
-  // split (q % 12) / 4, row block q % 4; all of it wave-uniform except the
-  // lane's 16-byte offset.  cbase[i]: unit i's address at panel 0, group 0
-  // (scalar registers: the asm operand requires them); a slab adds
-  // (kp ng + g) 3 units.
-  const uint32_t voff = uint32_t(lane) * 16;
-  const u16x8* cbase[6];
+  // this wave's eight units of every slab: the four planes of row blocks
+  // 2 w and 2 w + 1 of the slab's eight (A's four, then B's)
+  uint32_t voff[4];
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    const int q = 6 * w + i;
-    const bool isB = q >= 12;
-    const int sp = (q % 12) / 4, rb = q % 4;
-    const int64_t r0 = int64_t(isB ? tc : tr) * (XT / 32) + rb;
-    cbase[i] = uniform_ptr((isB ? a.B : a.A) + ((r0 * nkb * (isB ? a.ngB : a.ngA)) * 3 + sp) * XUNIT);
+  for (int u = 0; u < 4; ++u) voff[u] = uint32_t(lane) * 16 + u * 1024;
+  const u16x8* cbase[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int q = 2 * w + i;
+    const int64_t r0 = int64_t(q >= 4 ? tc : tr) * (XT / 32) + (q & 3);
+    cbase[i] = uniform_ptr((q >= 4 ? a.B : a.A) + r0 * nkb * kX6BlockVecs);
   }
   const int npan = ke - kb;
-  // copies of slab s = 3 kp + prod of the segment (panel clamped to the
-  // last); prod is a compile-time constant at every call
-  auto dma_slab = [&](int s, int kp, int prod) {
+  // copy i (of XCOPY) of the segment's slab kp (clamped to the last)
+  auto copy = [&](int kp, int i) {
     const int kpa = kb + min(kp, npan - 1);
-    const int64_t offA = (int64_t(kpa) * a.ngA + (prod < 2 ? prod : a.gA2)) * 3 * XUNIT;
-    const int64_t offB = (int64_t(kpa) * a.ngB + (prod < 2 ? prod : a.gB2)) * 3 * XUNIT;
-    const uint32_t slot = lbase + uint32_t((s % XNSLOT) * XSLOT);
-    return [=](int i) {
-      const int q = 6 * w + i;
-      dma16(cbase[i] + (q >= 12 ? offB : offA), voff, slot + uint32_t(q * 1024));
-    };
+    dma16(cbase[i >> 2] + int64_t(kpa) * kX6BlockVecs, voff[i & 3],
+          lbase + uint32_t((kp % XNSLOT) * XSLOT) + uint32_t((2 * w + (i >> 2)) * 4096 + (i & 3) * 1024));
   };
-  u16x8 fa[3][3][2], fb[3][3][2];  // [product][split][block]
-  f16v acc[3][2][2];
+  const h16x8* ring = reinterpret_cast<const h16x8*>(lds);
+  auto slab = [&](int kp) { return ring + (kp % XNSLOT) * (XSLOT / 16) + lane; };
+  auto read_a = [&](int kp, int i, int pl) { return slab(kp)[((wr * 2 + i) * 4 + pl) * XUNIT]; };
+  auto read_b = [&](int kp, int j, int pl) { return slab(kp)[((4 + wc * 2 + j) * 4 + pl) * XUNIT]; };
+  enum { RH, RL, IH, IL };            // planes re_h, re_l, im_h, im_l
+  h16x8 fa[2][4], fb[2][4];           // [row block][plane], [column block][plane]
+  f16v ar[2][2], ai[2][2], ap[2][2];  // chain accumulators of re and im; K1 of the corrections
 #pragma unroll
-  for (int s = 0; s < XDIST; ++s) {
-    const auto copy = dma_slab(s, s / 3, s % 3);
+  for (int s = 0; s < XDIST; ++s)
 #pragma unroll
-    for (int i = 0; i < 6; ++i) copy(i);
-  }
-  QST_VMCNT((XDIST - 1) * 6);
+    for (int i = 0; i < XCOPY; ++i) copy(s, i);
+  QST_VMCNT((XDIST - 1) * XCOPY);
   __builtin_amdgcn_s_barrier();
-  {
-    const u16x8* L = reinterpret_cast<const u16x8*>(lds);
 #pragma unroll
-    for (int sp = 0; sp < 3; ++sp)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fa[0][sp][i] = L[(sp * 4 + wr * 2 + i) * XUNIT + lane];
-        fb[0][sp][i] = L[(12 + sp * 4 + wc * 2 + i) * XUNIT + lane];
-      }
+  for (int pl = 0; pl < 4; ++pl) {
+    fa[0][pl] = read_a(0, 0, pl);
+    fb[0][pl] = read_b(0, 0, pl);
   }
-  // combination order hh, hm, hl, mh, mm, lh: the current slab's A_h dies
-  // after the third pair, A_m and B_m after the fifth, so the next slab's
-  // fragments, read two per step in the second half of the slab (in the
-  // order that slab's first MFMAs use them), mostly take freed registers
-  constexpr int SA[6] = {0, 0, 0, 1, 1, 2}, SB[6] = {0, 1, 2, 0, 1, 0};
-  constexpr int RD_AB[12] = {0, 0, 1, 1, 1, 1, 1, 1, 0, 0, 0, 0};  // 0: A, 1: B
-  constexpr int RD_SP[12] = {0, 0, 0, 0, 1, 1, 2, 2, 1, 1, 2, 2};
-  for (int c0 = 0; c0 < npan; c0 += XCHAIN) {
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+      for (int v = 0; v < 16; ++v) ap[i][j][v] = 0.f;
+  // the block folded by a chain's first panel: the last one of a panel with f = 1
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[p][i][j][v] = 0.f;
-    const int cend = min(npan, c0 + XCHAIN);
-    for (int kp = c0; kp < cend; ++kp) {
+  for (int v = 0; v < 16; ++v) ar[1][1][v] = ai[1][1][v] = 0.f;
+  auto fold = [&](int i, int j, int x) {
+    if (x < 16) re[i][j][x] += ar[i][j][x];
+    else im[i][j][x - 16] += ai[i][j][x - 16];
+  };
+  // one panel; FIRST / LAST of its chain, first column block F
+  auto panel = [&](auto first_c, auto last_c, auto f_c, int kp) {
+    constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
+    constexpr int F = decltype(f_c)::value;
+    // every slab is XCOPY copies per wave, so slab kp + 1 is complete once at
+    // most XDIST - 2 newer slabs are outstanding
+    QST_VMCNT((XDIST - 2) * XCOPY);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    h16x8 sh, sl;                  // Ar + Ai of the row block
+    h16x8 dh, dl, nh, nl, nb;      // Bi - Br, -(Br + Bi) (h and l), -Bi_h of the column block
+    h16x8 mr;
 #pragma unroll
-      for (int prod = 0; prod < 3; ++prod) {
-        const int s = 3 * kp + prod;
-        // every slab issued six copies per wave, so slab s+1 is complete once
-        // at most XDIST-2 newer slabs are outstanding
-        QST_VMCNT((XDIST - 2) * 6);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        const int np = prod == 2 ? 0 : prod + 1;
-        const u16x8* L = reinterpret_cast<const u16x8*>(lds + ((s + 1) % XNSLOT) * XSLOT);
-        const auto copy = dma_slab(s + XDIST, kp + (prod + XDIST) / 3, (prod + XDIST) % 3);
+    for (int b = 0; b < 4; ++b) {
+      const int i = b >> 1, j = (b == 0 || b == 3) ? F : 1 - F;
+      const int pi = b == 0 ? 1 : (b - 1) >> 1, pj = b == 0 ? 1 - F : (b == 1 ? F : 1 - F);  // the block before
+      const h16x8(&A)[4] = fa[i];
+      const h16x8(&B)[4] = fb[j];
+      f16v &R = ar[i][j], &I = ai[i][j], &K = ap[i][j];
+      f16v z;
 #pragma unroll
-        for (int q = 0; q < 12; ++q) {
+      for (int v = 0; v < 16; ++v) z[v] = 0.f;
+      // ten steps of one MFMA each, with what later steps need formed in its
+      // shadow (at most seven vector instructions fit one MFMA)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int m = 2 * q + h;
-            const int c = m / 4, i = (m / 2) & 1, j = m & 1;
-            acc[prod][i][j] = mfma32(fa[prod][SA[c]][i], fb[prod][SB[c]][j], acc[prod][i][j]);
-          }
-          if (q >= 6) {
-#pragma unroll
-            for (int r = 2 * (q - 6); r < 2 * (q - 6) + 2; ++r) {
-              const int sp = RD_SP[r], bi = r & 1;
-              if (RD_AB[r] == 0) fa[np][sp][bi] = L[(sp * 4 + wr * 2 + bi) * XUNIT + lane];
-              else fb[np][sp][bi] = L[(12 + sp * 4 + wc * 2 + bi) * XUNIT + lane];
-            }
-          } else {
-            copy(q);
-          }
-          __builtin_amdgcn_sched_barrier(0);
+      for (int m = 0; m < 10; ++m) {
+        if constexpr (HERK) {
+          if (m == 0) R = mfma32(A[RH], B[RH], FIRST ? z : R);
+          if (m == 1) I = mfma32(A[IH], B[RH], FIRST ? z : I);
+          if (m == 2) R = mfma32(A[IH], B[IH], R);
+          if (m == 3) I = mfma32(A[RH], nb, I);
+          if (m == 5) R = mfma32(A[IH], dl, R);
+          if (m == 6) I = mfma32(A[RH], nl, I);
+          if (m == 8) R = mfma32(A[IL], dh, R);
+          if (m == 9) I = mfma32(A[RL], nh, I);
+        } else {
+          if (m == 0) I = mfma32(A[RH], B[IH], FIRST ? z : I);
+          if (m == 1) R = mfma32(A[RH], B[RH], FIRST ? z : R);
+          if (m == 2) I = mfma32(A[IH], B[RH], I);
+          if (m == 3) R = mfma32(A[IH], nb, R);
+          if (m == 5) I = mfma32(A[RH], dl, I);
+          if (m == 6) R = mfma32(A[IH], nl, R);
+          if (m == 8) I = mfma32(A[RL], dh, I);
+          if (m == 9) R = mfma32(A[IL], nh, R);
         }
+        if (m == 4) K = mfma32(sh, B[RL], K);
+        if (m == 7) K = mfma32(sl, B[RH], K);
+        if (b != 2) {
+          if (m == 0) nb = negated(B[IH]);
+          if (m == 1) mr = negated(B[RL]);
+          if (m == 2) dl = B[IL] + mr;
+          if (m == 3) nl = negated(B[IL]);
+          if (m == 4) nl = nl + mr;
+          if (m == 5) mr = negated(B[RH]);
+          if (m == 6) dh = B[IH] + mr;
+          if (m == 7) nh = nb + mr;
+        }
+        if (b == 0 || b == 2) {
+          if (m == 2) sh = A[RH] + A[IH];
+          if (m == 5) sl = A[RL] + A[IL];
+        }
+        if (b == 0 && m < 4) fb[1 - F][m] = read_b(kp, 1 - F, m);
+        if (b == 0 && m >= 4 && m < 8) fa[1][m - 4] = read_a(kp, 1, m - 4);
+        if (b == 2 && m < 4) fa[0][m] = read_a(kp + 1, 0, m);
+        if (b == 3 && m < 4) fb[1 - F][m] = read_b(kp + 1, 1 - F, m);
+        if (b == 1 && m < XCOPY) copy(kp + XDIST, m);
+        if ((b == 0 && FIRST) || (b > 0 && LAST)) {
+#pragma unroll
+          for (int x = 4 * m; x < 4 * m + 4; ++x)
+            if (x < 32) fold(pi, pj, x);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // close the chain: one 32 x 32 block at a time
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float p1 = acc[0][i][j][v], p2 = acc[1][i][j][v], p3 = acc[2][i][j][v];
-          if constexpr (HERK) {
-            re[i][j][v] += p1 + p2;
-            im[i][j][v] += (p3 - p1) + p2;
-          } else {
-            re[i][j][v] += p1 - p2;
-            im[i][j][v] += (p3 - p1) - p2;
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  constexpr std::integral_constant<int, 0> f0{};
+  constexpr std::integral_constant<int, 1> f1{};
+  for (int c0 = 0; c0 < npan; c0 += XCHAIN) {
+    const int n = min(XCHAIN, npan - c0);
+    panel(yes, no, f0, c0);
+    for (int k = 1; k + 1 < n; k += 2) {
+      panel(no, no, f1, c0 + k);
+      panel(no, no, f0, c0 + k + 1);
+    }
+    panel(no, yes, f1, c0 + n - 1);
   }
+#pragma unroll
+  for (int x = 0; x < 32; ++x) fold(1, 1, x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        re[i][j][v] += ap[i][j][v];
+        im[i][j][v] += ap[i][j][v];
+      }
   // the clamped copies issued past the end land before the ring is reused
   // (or the workgroup's LDS is released), and every wave is past its reads
   QST_VMCNT(0);
@@ -444,7 +593,7 @@ __device__ __forceinline__ int64_t x6_unit_slot(int64_t u) { return u; }
 __device__ __forceinline__ int64_t x6_slice_slot(const X6HerkSched& sc, int64_t w, int which) {
   return (sc.sk > 1 ? sc.main : 0) + (sc.tq ? w : 2 * w + which);
 }
-__device__ __forceinline__ void x6_store_partial(float* dst, const f16v (&re)[2][2], const f16v (&im)[2][2]) {
+__device__ __forceinline__ void x6_store_partial(float* dst, const float (&re)[2][2][16], const float (&im)[2][2][16]) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   f4v* d4 = reinterpret_cast<f4v*>(dst);
 #pragma unroll
@@ -459,6 +608,46 @@ __device__ __forceinline__ void x6_store_partial(float* dst, const f16v (&re)[2]
       }
 }
 
+// Scales of the values of a wave's 64 x 64 quadrant at (r0, c0): rs[i][v]
+// takes the row scale of value v of block row i out, cs[j] the column
+// scale of block column j with the overall factor.  Powers of two but for
+// that factor, so value * cs * rs rounds once.
+__device__ __forceinline__ void x6_scales(const XArgs& a, int64_t r0, int64_t c0, double scale, float (&rs)[2][16],
+                                          float (&cs)[2]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      rs[i][v] = a.sa[(r0 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * a.sa_stride];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) cs[j] = float(scale * double(a.sb[c0 + j * 32 + (lane & 31)]));
+}
+
+// Diagonal entries r0 .. r0 + NR - 1 of T T^dagger, the rows' sums of
+// |T|^2, as 256 / NR partial sums each in sums (x6_diag adds them): called
+// by the whole workgroup, a barrier before the sums are read.  The product
+// leaves out the ll terms, whose mean is zero except on the diagonal, where
+// each is a square: there it came out 4e-8 low, as the trace did, and the
+// gradient (in which the trace part cancels) took a relative error of 5e-7
+// to 1e-6 from that (N = 10: 1.4e-6 with the product's diagonal).
+template <int NR>
+__device__ __forceinline__ void x6_diag_sums(const XArgs& a, int64_t r0, double* sums) {
+  constexpr int NP = 256 / NR;
+  const double* src = a.rsum + r0 + threadIdx.x % NR;
+  double s = 0.0;
+#pragma unroll 8
+  for (int q = threadIdx.x / NR; q < a.d / XT; q += NP) s += src[int64_t(q) * a.d];
+  sums[threadIdx.x] = s;
+}
+template <int NR>
+__device__ __forceinline__ float x6_diag(const double* sums, int r, double scale) {
+  double s = sums[r];
+#pragma unroll
+  for (int p = 1; p < 256 / NR; ++p) s += sums[p * NR + r];
+  return float(s * scale);
+}
+
 // Tile epilogue.  HEMM: C = scale (re, im).  HERK without x0: rho = (re,
 // im) / tau, and the conjugate transpose at the mirror position for an
 // off-diagonal tile.  HERK with x0: the first POVM pass over G qubits on
@@ -466,12 +655,22 @@ __device__ __forceinline__ void x6_store_partial(float* dst, const f16v (&re)[2]
 // quadrant of a diagonal tile is the mirror of the lower one and skipped),
 // through a 64 x 64 tile in LDS.
 template <bool HERK, int X0G>
-__device__ __forceinline__ void x6_epilogue(const XArgs& a, int tr, int tc, const f16v (&re)[2][2],
-                                            const f16v (&im)[2][2], double scale, char* lds) {
+__device__ __forceinline__ void x6_epilogue(const XArgs& a, int tr, int tc, const float (&re)[2][2][16],
+                                            const float (&im)[2][2][16], double scale, char* lds) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int wr = w >> 1, wc = w & 1;
-  const float sc = float(scale);
   const int64_t R0 = int64_t(tr) * XT, C0 = int64_t(tc) * XT;
+  // row scales of this lane's values (four rows per group of four values)
+  // and column scales with the overall factor
+  float rs[2][16], cs[2];
+  x6_scales(a, R0 + wr * 64, C0 + wc * 64, scale, rs, cs);
+  double* diag = reinterpret_cast<double*>(lds + 64 * 64 * sizeof(Cx<float>));
+  if constexpr (HERK) {
+    if (tr == tc) {
+      x6_diag_sums<XT>(a, R0, diag);
+      __syncthreads();
+    }
+  }
   if constexpr (X0G == 0) {
     Cx<float>* C = static_cast<Cx<float>*>(a.C);
 #pragma unroll
@@ -481,8 +680,13 @@ __device__ __forceinline__ void x6_epilogue(const XArgs& a, int tr, int tc, cons
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int64_t r = R0 + x6_row(wr, i, v, lane), c = C0 + x6_col(wc, j, lane);
-          C[r * a.ldc + c] = Cx<float>{re[i][j][v] * sc, im[i][j][v] * sc};
-          if (HERK && tr != tc) C[c * a.ldc + r] = Cx<float>{re[i][j][v] * sc, -im[i][j][v] * sc};
+          float xr = re[i][j][v] * cs[j] * rs[i][v], xi = im[i][j][v] * cs[j] * rs[i][v];
+          if (HERK && i == j && r == c) {
+            xr = x6_diag<XT>(diag, int(r - R0), scale);
+            xi = 0.f;
+          }
+          C[r * a.ldc + c] = Cx<float>{xr, xi};
+          if (HERK && tr != tc) C[c * a.ldc + r] = Cx<float>{xr, -xi};
         }
   } else {
     constexpr int G = X0G;
@@ -506,7 +710,9 @@ __device__ __forceinline__ void x6_epilogue(const XArgs& a, int tr, int tc, cons
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
               const int r = i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), c = j * 32 + (lane & 31);
-              L[((r >> G) * S + (c >> G)) * TG + swz<G>(r & M, c & M)] = Cx<float>{re[i][j][v] * sc, im[i][j][v] * sc};
+              Cx<float> x{re[i][j][v] * cs[j] * rs[i][v], im[i][j][v] * cs[j] * rs[i][v]};
+              if (i == j && tr == tc && wr == wc && r == c) x = Cx<float>{x6_diag<XT>(diag, wr * 64 + r, scale), 0.f};
+              L[((r >> G) * S + (c >> G)) * TG + swz<G>(r & M, c & M)] = x;
             }
       }
       __syncthreads();
@@ -516,7 +722,7 @@ __device__ __forceinline__ void x6_epilogue(const XArgs& a, int tr, int tc, cons
   }
 }
 
-__device__ __forceinline__ void x6_zero(f16v (&re)[2][2], f16v (&im)[2][2]) {
+__device__ __forceinline__ void x6_zero(float (&re)[2][2][16], float (&im)[2][2][16]) {
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -541,13 +747,16 @@ __global__ __launch_bounds__(256, 1) void x6_hemm_kernel(XArgs a) {
   }
   double scale = 2.0 / *a.tau;
   if (a.up) scale *= *a.up;
-  f16v re[2][2], im[2][2];
+  float re[2][2][16], im[2][2][16];
   x6_zero(re, im);
   x6_segment<false>(a, lds, tr, tc, 0, a.kIters, re, im);
   x6_epilogue<false, 0>(a, tr, tc, re, im, scale, lds);
 }
 
-__device__ __forceinline__ int64_t x6_slice_start(int64_t w, int64_t Q, int64_t iters) { return (w * iters) / Q; }
+// (even, as x6_segment needs; iters is)
+__device__ __forceinline__ int64_t x6_slice_start(int64_t w, int64_t Q, int64_t iters) {
+  return 2 * ((w * (iters / 2)) / Q);
+}
 
 // Unit u -> tile and K panels: u = s * ntiles + t covers panels
 // [s kh, (s + 1) kh) of lower tile t (the units of a round share s, so
@@ -560,64 +769,53 @@ __device__ __forceinline__ void x6_unit(const X6HerkSched& sc, int64_t u, int64_
 // T T^dagger: logical workgroup w takes round units w, w + P, ...; a whole
 // tile (sk = 1) is finished here, a part of one is stored as a partial.
 // Then, as slice worker w < Q, the iterations [start(w), start(w + 1)) of
-// the remaining units' (unit, panel) sequence.
+// the remaining units' (unit, panel) sequence.  One loop over both, so that
+// the segment code is there once.
 template <int X0G>
 __global__ __launch_bounds__(256, 1) void x6_herk_kernel(XArgs a) {
   extern __shared__ __align__(16) char lds[];
   const X6HerkSched& sc = a.sc;
-  const int64_t w = xcd_order(blockIdx.x, gridDim.x);
-  // 1 / tau, formed on the first whole tile this workgroup finishes (a
-  // split tile's partials are scaled in the fix-up, which stores tau)
-  double scale = 0.0;
-  auto tile_scale = [&]() {
-    if (scale == 0.0) scale = 1.0 / x6_tau(a, false);
-    return scale;
-  };
-  for (int64_t r = 0; r < sc.rounds; ++r) {
-    const int64_t u = r * sc.P + w;
+  const int w = int(xcd_order(blockIdx.x, gridDim.x));
+  int r = 0;
+  // transposed slices: one piece, slice w / left of unit w % left
+  int it = 0, end = 0, first_unit = 0;
+  if (w < sc.Q) {
+    it = sc.tq ? 0 : int(x6_slice_start(w, sc.Q, sc.left_iters));
+    end = sc.tq ? 1 : int(x6_slice_start(w + 1, sc.Q, sc.left_iters));
+    first_unit = it / int(sc.kh);
+  }
+  while (r < sc.rounds || it < end) {
+    int u, kb = 0, ke = int(sc.kh), slot;
+    if (r < sc.rounds) {
+      u = r * int(sc.P) + w;
+      slot = int(x6_unit_slot(u));
+      ++r;
+    } else {
+      int j;  // leftover unit
+      if (sc.tq) {
+        j = w % int(sc.left);
+        kb = (w / int(sc.left)) * int(sc.ps);
+        ke = kb + int(sc.ps);
+        it = end;
+      } else {
+        j = it / int(sc.kh);
+        kb = it % int(sc.kh);
+        ke = min(int(sc.kh), kb + (end - it));
+        it += ke - kb;
+      }
+      u = int(sc.main) + j;
+      slot = int(x6_slice_slot(sc, w, j == first_unit ? 0 : 1));  // slot w with tq
+    }
     int64_t t;
     int k0;
     x6_unit(sc, u, t, k0);
     int tr, tc;
     tri_decode(t, tr, tc);
-    f16v re[2][2], im[2][2];
-    x6_zero(re, im);
-    x6_segment<true>(a, lds, tr, tc, k0, k0 + int(sc.kh), re, im);
-    if (sc.sk == 1) x6_epilogue<true, X0G>(a, tr, tc, re, im, tile_scale(), lds);
-    else x6_store_partial(x6_slot(a, x6_unit_slot(u)), re, im);
-  }
-  if (w >= sc.Q) return;
-  // transposed slices: one piece, slice w / left of unit w % left
-  int64_t it = sc.tq ? 0 : x6_slice_start(w, sc.Q, sc.left_iters);
-  const int64_t end = sc.tq ? 1 : x6_slice_start(w + 1, sc.Q, sc.left_iters);
-  const int64_t first_unit = it / sc.kh;
-  while (it < end) {
-    int64_t j;  // leftover unit
-    int kb, ke;
-    if (sc.tq) {
-      j = w % sc.left;
-      kb = int((w / sc.left) * sc.ps);
-      ke = kb + int(sc.ps);
-      it = end;
-    } else {
-      j = it / sc.kh;
-      kb = int(it % sc.kh);
-      ke = int(std::min<int64_t>(sc.kh, kb + (end - it)));
-      it += ke - kb;
-    }
-    int64_t t;
-    int k0;
-    x6_unit(sc, sc.main + j, t, k0);
-    int tr, tc;
-    tri_decode(t, tr, tc);
-    f16v re[2][2], im[2][2];
+    float re[2][2][16], im[2][2][16];
     x6_zero(re, im);
     x6_segment<true>(a, lds, tr, tc, k0 + kb, k0 + ke, re, im);
-    if (sc.sk == 1 && kb == 0 && ke == sc.kh) {
-      x6_epilogue<true, X0G>(a, tr, tc, re, im, tile_scale(), lds);
-    } else {
-      x6_store_partial(x6_slot(a, x6_slice_slot(sc, w, j == first_unit ? 0 : 1)), re, im);  // slot w with tq
-    }
+    if (sc.sk == 1 && kb == 0 && ke == sc.kh) x6_epilogue<true, X0G>(a, tr, tc, re, im, 1.0 / x6_tau(a, lds), lds);
+    else x6_store_partial(x6_slot(a, slot), re, im);
   }
 }
 
@@ -708,6 +906,8 @@ __global__ __launch_bounds__(256, 3) void x6_fixup_kernel(XArgs a) {
     if (th == 0 && a.tau_out) *a.tau_out = tau;
     return;
   }
+  __shared__ double diag[256];
+  if (tr == tc && qr == qc) x6_diag_sums<64>(a, int64_t(tr) * XT + qr * 64, diag);
   f4v acc[8], v[2][8];
 #pragma unroll
   for (int m = 0; m < 8; ++m) acc[m] = f4v{0.f, 0.f, 0.f, 0.f};
@@ -744,8 +944,15 @@ __global__ __launch_bounds__(256, 3) void x6_fixup_kernel(XArgs a) {
   const double scale = 1.0 / tau_sh;
   // vector th + 256 m of the quadrant holds values 4 vq + c of block
   // ij = m / 2, part m % 2, lane th % 64, vq = th / 64
-  const float sc32 = float(scale);
   const int lane = th & 63, vq = th >> 6;
+  float rs[2][4], cs[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+#pragma unroll
+    for (int c4 = 0; c4 < 4; ++c4)
+      rs[i][c4] = a.sa[int64_t(tr) * XT + qr * 64 + i * 32 + 8 * vq + 4 * (lane >> 5) + c4];
+    cs[i] = float(scale * double(a.sb[int64_t(tc) * XT + qc * 64 + i * 32 + (lane & 31)]));
+  }
   if constexpr (X0G == 0) {
     Cx<float>* C = static_cast<Cx<float>*>(a.C);
     float* Cf = reinterpret_cast<float*>(C);
@@ -757,7 +964,8 @@ __global__ __launch_bounds__(256, 3) void x6_fixup_kernel(XArgs a) {
         const int i = ij >> 1, j = ij & 1;
         const int64_t r = int64_t(tr) * XT + qr * 64 + i * 32 + 8 * (vv >> 2) + 4 * (lane >> 5) + (vv & 3);
         const int64_t c = int64_t(tc) * XT + qc * 64 + j * 32 + (lane & 31);
-        const float x = acc[m][c4] * sc32;
+        float x = acc[m][c4] * cs[j] * rs[i][c4];
+        if (i == j && r == c) x = part ? 0.f : x6_diag<64>(diag, int(r & 63), scale);
         Cf[2 * (r * a.ldc + c) + part] = x;
         // the mirror: every off-diagonal tile, and the lower-left quadrant
         // of a diagonal tile (whose upper-right quadrant is not computed here)
@@ -776,7 +984,9 @@ __global__ __launch_bounds__(256, 3) void x6_fixup_kernel(XArgs a) {
         const int part = m & 1, vv = 4 * vq + c4, ij = m >> 1;
         const int i = ij >> 1, j = ij & 1;
         const int r = i * 32 + 8 * (vv >> 2) + 4 * (lane >> 5) + (vv & 3), c = j * 32 + (lane & 31);
-        Lf[2 * (((r >> G) * S + (c >> G)) * TG + swz<G>(r & M, c & M)) + part] = acc[m][c4] * sc32;
+        float x = acc[m][c4] * cs[j] * rs[i][c4];
+        if (i == j && tr == tc && qr == qc && r == c) x = part ? 0.f : x6_diag<64>(diag, r, scale);
+        Lf[2 * (((r >> G) * S + (c >> G)) * TG + swz<G>(r & M, c & M)) + part] = x;
       }
     __syncthreads();
     gemm::GemmArgs g{};
@@ -806,6 +1016,8 @@ hipError_t x6_allow_lds() {
   return hipSuccess;
 }
 
+unsigned x6_split_grid(int d) { return unsigned(int64_t(d / 32) * (d / 128)); }
+
 int x6_cus() {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
@@ -834,26 +1046,28 @@ hipError_t launch_x6_herk(const void* T, int64_t ldt, void* rho, int64_t ldr, in
   if (d < kX6Tile || !tau_partials) return hipErrorInvalidValue;
   if (x0 && (x0->g < 4 || x0->g > 6 || !x0->tetra)) return hipErrorInvalidValue;
   u16x8* P = static_cast<u16x8*>(planes);
+  const X6Scales sc = x6_scales_of(x6_herk_scales(planes, n), n);
   {
     ProfScope prof("x6_split_t", s);
     const Cx<float>* Tf = static_cast<const Cx<float>*>(T);
     const float* ff = static_cast<const float*>(f);
     u16x8* PT = static_cast<u16x8*>(tt_planes);
-    if (f && PT) x6_split_tau_kernel<true, true><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, P, PT, tau_partials, ff);
-    else if (f) x6_split_tau_kernel<true, false><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, P, PT, tau_partials, ff);
-    else if (PT) x6_split_tau_kernel<false, true><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, P, PT, tau_partials, ff);
-    else x6_split_tau_kernel<false, false><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, P, PT, tau_partials, ff);
+    if (f) x6_absmax_kernel<true, true><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, tau_partials, ff);
+    else x6_absmax_kernel<true, false><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, tau_partials, ff);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const auto split = PT ? x6_split_kernel<true, true, true> : x6_split_kernel<true, false, true>;
+    split<<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, sc.rinv, sc.cinv, sc.rsum, P, PT);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   ProfScope prof("herk_x6", s);
   XArgs a{};
   a.A = P;
   a.B = P;
-  a.ngA = 4;
-  a.ngB = 4;
-  a.gA2 = 2;  // re + im
-  a.gB2 = 3;  // re - im
+  a.sa = sc.rinv;
+  a.sb = sc.rinv;
+  a.sa_stride = 1;
+  a.rsum = sc.rsum;
   a.C = rho;
   a.ldc = ldr;
   a.d = d;
@@ -874,32 +1088,39 @@ hipError_t launch_x6_herk(const void* T, int64_t ldt, void* rho, int64_t ldr, in
 
 hipError_t launch_x6_hemm(const void* G, int64_t ldg, const void* T, int64_t ldt, void* out, int64_t ldo, int n,
                           const double* tau_dev, const double* upstream_dev, void* planes, hipStream_t s,
-                          bool g_ready, bool t_ready) {
+                          const X6Ready* ready) {
   const int d = 1 << n;
   if (d < kX6Tile) return hipErrorInvalidValue;
-  const int64_t units = int64_t(d / 32) * (d / 16);
   u16x8* PG = static_cast<u16x8*>(planes);
-  u16x8* PT = PG + units * 9 * XUNIT;
+  u16x8* PT = PG + x6_plane_bytes(n) / sizeof(u16x8);
+  XArgs a{};
   hipError_t e;
-  if (!g_ready || !t_ready) {
+  if (ready) {
+    a.sa = ready->ginv;
+    a.sa_stride = 0;
+    a.sb = ready->tcinv;
+  } else {
     ProfScope prof("x6_split_gt", s);
-    if (!g_ready) {
-      x6_split_kernel<false, 3><<<unsigned((units + 3) / 4), 256, 0, s>>>(static_cast<const Cx<float>*>(G), ldg, d, PG);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (!t_ready) {
-      x6_split_kernel<true, 3><<<unsigned((units + 3) / 4), 256, 0, s>>>(static_cast<const Cx<float>*>(T), ldt, d, PT);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    const X6Scales sg = x6_scales_of(x6_hemm_scales(planes, n, 0), n);
+    const X6Scales st = x6_scales_of(x6_hemm_scales(planes, n, 1), n);
+    const Cx<float>* Gf = static_cast<const Cx<float>*>(G);
+    const Cx<float>* Tf = static_cast<const Cx<float>*>(T);
+    const unsigned mg = unsigned(std::min<int64_t>(kReduceBlocks, int64_t(d / 64) * (d / 64)));
+    x6_absmax_kernel<false, false><<<mg, 256, 0, s>>>(Gf, ldg, d, sg.rowp, sg.colp, nullptr, nullptr);
+    x6_absmax_kernel<false, false><<<mg, 256, 0, s>>>(Tf, ldt, d, st.rowp, st.colp, nullptr, nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    x6_split_kernel<true, false, false><<<x6_split_grid(d), 256, 0, s>>>(Gf, ldg, d, sg.rowp, sg.colp, sg.rinv, sg.cinv,
+                                                                         nullptr, PG, nullptr);
+    x6_split_kernel<false, true, false><<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, st.rowp, st.colp, st.rinv, st.cinv,
+                                                                         nullptr, nullptr, PT);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    a.sa = sg.rinv;
+    a.sa_stride = 1;
+    a.sb = st.cinv;
   }
   if ((e = x6_allow_lds<x6_hemm_kernel>()) != hipSuccess) return e;
-  XArgs a{};
   a.A = PG;
   a.B = PT;
-  a.ngA = 3;
-  a.ngB = 3;
-  a.gA2 = 2;
-  a.gB2 = 2;
   a.C = out;
   a.ldc = ldo;
   a.d = d;

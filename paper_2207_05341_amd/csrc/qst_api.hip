@@ -48,7 +48,7 @@ hipError_t run_state_map(qst_prec prec, const void* T, int64_t ldT, void* rho, i
 qst_status likelihood_impl(int n, qst_prec prec, const void* T, int64_t ldT, const void* f, const double* povm_host,
                            double* tau_dev, double* nll_dev, unsigned long long* bad_dev, void* G, int64_t ldG,
                            void* ws, size_t ws_bytes, void* stream, const void* pt, double* fc_dev,
-                           void* gplanes = nullptr, void* ttplanes = nullptr);
+                           void* gplanes = nullptr, void* ttplanes = nullptr, const X6Scales* gscales = nullptr);
 
 }  // namespace
 
@@ -472,12 +472,12 @@ namespace {
 
 // gplanes / ttplanes (the combined likelihood-and-gradient call, QST_F32X6
 // with a fused plan whose pass 0 writes planes): adjoint pass 0 writes G' as
-// the gradient product's planes at gplanes (G unused), and the T split writes
-// T^T's planes at ttplanes.
+// the gradient product's planes at gplanes (G unused; their scale at
+// gscales->rinv[0]), and the T split writes T^T's planes at ttplanes.
 qst_status likelihood_impl(int n, qst_prec prec, const void* T, int64_t ldT, const void* f, const double* povm_host,
                            double* tau_dev, double* nll_dev, unsigned long long* bad_dev, void* G, int64_t ldG,
                            void* ws, size_t ws_bytes, void* stream, const void* pt, double* fc_dev,
-                           void* gplanes, void* ttplanes) {
+                           void* gplanes, void* ttplanes, const X6Scales* gscales) {
   std::string msg;
   qst_status st;
   if ((st = check_common(n, prec, msg)) != QST_OK) return fail(st, msg);
@@ -514,7 +514,7 @@ qst_status likelihood_impl(int n, qst_prec prec, const void* T, int64_t ldT, con
   if (fused) {
     e = launch_povm_fused(prec, pl, W, V, tetra, rho, d, f, partials + kReduceBlocks, G, ldG, ws_at(ws, L.inter0),
                           ws_at(ws, L.inter1), reinterpret_cast<double*>(ws_at(ws, L.fpart)), nll_dev, bad_dev, x0,
-                          s, pt, fc_dev, gplanes);
+                          s, pt, fc_dev, gplanes, gplanes ? gscales->rowp : nullptr, gplanes ? gscales->rinv : nullptr);
     if (e != hipSuccess) return hip_fail(e, "fused POVM / likelihood passes");
   } else {
     void* p = ws_at(ws, L.p);
@@ -645,11 +645,14 @@ qst_status qst_likelihood_grad(int n, qst_prec prec, const void* T, int64_t ldT,
                        pass0_writes_planes(pl) && tp != nullptr;
   if (in_call) {
     unsigned char* gpl = static_cast<unsigned char*>(tp);
-    unsigned char* tpl = gpl + x6_hemm_plane_bytes(n) / 2;
+    unsigned char* tpl = gpl + x6_plane_bytes(n);
+    const X6Scales sg = x6_scales_of(x6_hemm_scales(tp, n, 0), n);
+    const X6Scales tsc = x6_scales_of(x6_herk_scales(ws_at(ws, L.planes), n), n);
     if ((st = likelihood_impl(n, prec, T, ldT, f, povm_host, tau_dev, nll_dev, bad_dev, nullptr, 0, ws, ws_bytes,
-                              stream, nullptr, nullptr, gpl, tpl)) != QST_OK)
+                              stream, nullptr, nullptr, gpl, tpl, &sg)) != QST_OK)
       return st;
-    hipError_t e = launch_x6_hemm(nullptr, 0, T, ldT, gradT, ld_grad, n, tau_dev, nullptr, tp, s, true, true);
+    const X6Ready ready{sg.rinv, tsc.cinv};
+    hipError_t e = launch_x6_hemm(nullptr, 0, T, ldT, gradT, ld_grad, n, tau_dev, nullptr, tp, s, &ready);
     if (e != hipSuccess) return hip_fail(e, "G' T");
   } else {
     void* G = ws_at(ws, L.gmat);

@@ -185,11 +185,12 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
   const size_t sk_bytes = x6 ? x6_partial_bytes(n) : stream_k_partial_bytes(prec);
   const bool planes = (prec == QST_BF16GEMM && d > size_t(kBf16SplitMaxDim)) || x6;
   const bool hemm_planes = (prec == QST_BF16GEMM && d >= 1024) || x6;
-  // bf16 planes of d x d: the BF16 path's (2 for T T^dagger, 8 for G' T)
-  // or the QST_F32X6 split planes (12 and 18)
-  const size_t herk_planes = x6 ? 12 : 2, hemm_plane_count = x6 ? 18 : 8;
-  auto take_planes = [&](size_t count) {  // count planes of d x d bf16
-    w.planes = take(count * D * sizeof(uint16_t));
+  // the BF16 path's bf16 planes (2 for T T^dagger, 8 for G' T), or the
+  // split products' planes and scales
+  const size_t herk_planes = x6 ? x6_herk_bytes(n) : 2 * D * sizeof(uint16_t);
+  const size_t hemm_plane_bytes = x6 ? x6_hemm_bytes(n) : 8 * D * sizeof(uint16_t);
+  auto take_planes = [&](size_t bytes) {
+    w.planes = take(bytes);
     w.has_planes = true;
   };
   auto take_sk = [&]() {
@@ -220,7 +221,7 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
         w.p = take(D * rb);
       }
       if (hemm_planes)
-        take_planes(hemm_plane_count);  // also holds T's planes of the recomputed state map
+        take_planes(hemm_plane_bytes);  // also holds T's planes of the recomputed state map
       else if (recompute && planes)
         take_planes(herk_planes);
       if (sk && (recompute || !x6)) take_sk();
@@ -238,7 +239,7 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
       break;
     }
     case QST_OP_GRAD_PRODUCT:
-      if (hemm_planes) take_planes(hemm_plane_count);
+      if (hemm_planes) take_planes(hemm_plane_bytes);
       if (sk && !x6) take_sk();
       break;
     case QST_OP_FIDELITY:
@@ -259,7 +260,7 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
       off = w.total;
       w.gmat = take(D * cb);
       if (hemm_planes) {
-        w.tplanes = take(x6 ? x6_hemm_plane_bytes(n) : hemm_plane_count * D * sizeof(uint16_t));
+        w.tplanes = take(hemm_plane_bytes);
         w.has_tplanes = true;
       }
       break;
@@ -508,7 +509,7 @@ GeneralLayout general_layout(int n, qst_prec prec, int K, bool with_state) {
     w.p = take((DK < 0 ? 0 : size_t(DK)) * rb);
     w.rho = take(D * cb);
     if (use_x6(prec, n)) {
-      w.planes = take(x6_herk_plane_bytes(n));
+      w.planes = take(x6_herk_bytes(n));
       w.has_planes = true;
       w.sk = take(x6_partial_bytes(n));
       w.has_sk = true;

@@ -19,11 +19,11 @@ inline bool prec_valid(int p) { return p == QST_F64 || p == QST_F32 || p == QST_
 // QST_F32 in its complex products only).
 inline qst_prec storage_prec(qst_prec p) { return p == QST_F32X6 ? QST_F32 : p; }
 
-// QST_F32X6 products (k_xgemm.hip): 128 x 128 output tiles; T T^dagger runs
+// Split products (k_xgemm.hip): 128 x 128 output tiles; T T^dagger runs
 // stream-K on at most kX6MaxGrid workgroups, each leaving at most two
-// partial tiles (re, im FP32).  Operand planes: T T^dagger reads the rows of
-// T in four groups (re, im, re + im, re - im) of three bf16 splits (24 bytes
-// per element); G' T reads G' and T^T in three groups (18 bytes each).
+// partial tiles (re, im FP32).  Operand planes: re and im in two fp16 parts
+// each (8 bytes per element) of T for T T^dagger and of G' and T^T for G' T,
+// followed by the scales they were split with (X6Scales).
 constexpr int kX6Tile = 128;
 constexpr int kX6MaxGrid = 256;
 inline bool use_x6(qst_prec p, int n) { return p == QST_F32X6 && (int64_t(1) << n) >= kX6Tile; }
@@ -93,8 +93,34 @@ inline size_t x6_partial_bytes(int n) {
   }
   return most * 2 * kX6Tile * kX6Tile * sizeof(float);
 }
-inline size_t x6_herk_plane_bytes(int n) { return (size_t(1) << (2 * n)) * 24; }
-inline size_t x6_hemm_plane_bytes(int n) { return (size_t(1) << (2 * n)) * 36; }
+inline size_t x6_plane_bytes(int n) { return (size_t(1) << (2 * n)) * 8; }
+// Scales of a split matrix: the largest component of every 64-entry piece of
+// a row and of a column ([d / 64][d] floats each), what takes the scale of
+// each row and of each column out again ([d] floats each), and the FP64 sum
+// of |x|^2 over every 128-entry piece of a row ([d / 128][d]).
+inline size_t x6_scale_bytes(int n) {
+  const size_t d = size_t(1) << n;
+  return (d / 128) * d * sizeof(double) + (2 * (d / 64) * d + 2 * d) * sizeof(float);
+}
+struct X6Scales {
+  double* rsum;
+  float *rowp, *colp, *rinv, *cinv;
+};
+inline X6Scales x6_scales_of(void* base, int n) {
+  const size_t d = size_t(1) << n, np = (d / 64) * d;
+  double* r = static_cast<double*>(base);
+  float* b = reinterpret_cast<float*>(r + (d / 128) * d);
+  return X6Scales{r, b, b + np, b + 2 * np, b + 2 * np + d};
+}
+// T T^dagger: T's planes, then its scales.  G' T: G''s planes, T^T's
+// planes, then G''s scales and T's.  36 bytes per element is more than both
+// need from d = kX6Tile; the size is part of the workspace contract.
+inline size_t x6_herk_bytes(int n) { return x6_plane_bytes(n) + x6_scale_bytes(n); }
+inline size_t x6_hemm_bytes(int n) { return (size_t(1) << (2 * n)) * 36; }
+inline void* x6_herk_scales(void* planes, int n) { return static_cast<char*>(planes) + x6_plane_bytes(n); }
+inline void* x6_hemm_scales(void* planes, int n, int which) {
+  return static_cast<char*>(planes) + 2 * x6_plane_bytes(n) + which * x6_scale_bytes(n);
+}
 
 // The product-POVM map is applied in passes.  Pass j contracts a group of
 // g_j consecutive qubits inside on-chip memory; groups run from the least

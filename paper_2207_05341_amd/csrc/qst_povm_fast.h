@@ -21,16 +21,20 @@ namespace fast_pass {
 // past ntiles load nothing and store nothing.  lds holds TPW * 4^G values.
 // ---------------------------------------------------------------------------
 //
-// PLANES (adjoint, FP32, G = 5 or 6): instead of G' itself, G' as the split
-// operand planes of the QST_F32X6 gradient product (row operand, groups
-// re, im, re + im, three exact bf16 parts; layout of qst_split.h) at
-// a.gplanes: each tile, then its conjugate transpose (off the diagonal),
-// passes through LDS row-major (16-byte chunks swizzled by row) and every
-// thread writes four unit-block slots.
+// PLANES (adjoint, FP32, tetrahedral, G = 5 or 6): instead of G' itself, G'
+// as the split operand planes of the QST_F32X6 gradient product (row
+// operand; layout of qst_split.h) at a.gplanes: each tile, then its
+// conjugate transpose (off the diagonal), passes through LDS row-major
+// (16-byte chunks swizzled by row) and every thread writes four unit-block
+// slots.  All rows take one scale, from a bound that is known before any G'
+// is: with M_a the POVM, |G'_rc| <= sum_a |(M_a)_rc| |y_a| per qubit, and
+// sum_a |(M_a)_rc| is 1 on the diagonal and 0.82 off it, so no modulus grows
+// past the largest of the intermediate (a.ymax; a modulus is at most
+// sqrt 2 times its larger component, hence one binade of headroom).
 template <typename R, bool ADJ, bool TETRA, int G, bool PLANES = false>
 __device__ __forceinline__ void mat_pass_body(const PassArgs& a, const ModeMatrix& A, int64_t ntiles, int64_t wb,
                                               unsigned tid, Cx<R> (&lds)[(256 >> (2 * (G - 2))) << (2 * G)]) {
-  static_assert(!PLANES || (ADJ && G >= 5 && sizeof(R) == 4), "planes from FP32 adjoint tiles of 32 or 64 rows");
+  static_assert(!PLANES || (ADJ && TETRA && G >= 5 && sizeof(R) == 4), "planes from FP32 adjoint tiles of 32 or 64 rows");
   constexpr int NT = 1 << (2 * (G - 2));
   constexpr int TPW = 256 / NT;
   constexpr int TILE = 1 << (2 * G);
@@ -59,6 +63,19 @@ __device__ __forceinline__ void mat_pass_body(const PassArgs& a, const ModeMatri
     }
   };
 
+  float gsc = 1.f;
+  if constexpr (PLANES) {
+    __shared__ float ym[4];
+    float m = 0.f;
+    for (int i = tid; i < a.nymax; i += 256) m = fmaxf(m, a.ymax[i]);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if ((tid & 63) == 0) ym[tid >> 6] = m;
+    __syncthreads();
+    const int e = x6_scale_exp(fmaxf(fmaxf(ym[0], ym[1]), fmaxf(ym[2], ym[3])), kX6Top - 1);
+    gsc = x6_pow2(e);
+    if (wb == 0 && tid == 0) *a.ginv = x6_pow2(-e);
+  }
   Cx<R> x[16];
   if constexpr (!ADJ) {
     Cx<R> blk[4][4];
@@ -178,7 +195,7 @@ __device__ __forceinline__ void mat_pass_body(const PassArgs& a, const ModeMatri
             im[e] = mir ? -v.im : v.im;
           }
           const int64_t rbg = (mir ? C0 : R0) / 32 + rbl, kbg = (mir ? R0 : C0) / 16 + kbl;
-          write_unit_block<3>(PL + (rbg * nkb + kbg) * (3 * 3 * kX6UnitVecs) + ln, re, im);
+          write_unit_block(PL + (rbg * nkb + kbg) * kX6BlockVecs + ln, re, im, gsc);
         }
       }
     }
@@ -299,7 +316,8 @@ __device__ __forceinline__ void kd_pass_body(const PassArgs& a, const ModeMatrix
 // Fused last pass (the kd_fused_pass kernel of k_povm_fast.hip): chunk lb
 // of J outcome positions, thread tid of 256, lds of 4^G * J values.  F is
 // the sum of f; the NLL terms and the bad-entry counts of the chunk are
-// added to L, bad0, bad1.  Reads X = a.out and writes the adjoint
+// added to L, bad0, bad1; with ymax (FP32) the largest |component| of the
+// thread's adjoint values goes there.  Reads X = a.out and writes the adjoint
 // intermediate in place.  Inactive (a padding call): the same loads,
 // rounds and barriers, nothing stored or counted.  FC: the classical
 // fidelity terms sqrt(max(p_k, 0) max(pt_k, 0)) against a.pt (loaded
@@ -308,7 +326,8 @@ __device__ __forceinline__ void kd_pass_body(const PassArgs& a, const ModeMatrix
 template <typename R, bool TETRA, int G, int J, bool FC = false>
 __device__ __forceinline__ void kd_fused_body(const PassArgs& a, const ModeMatrix& Af, const ModeMatrix& Aa, int64_t lb,
                                               unsigned tid, Cx<R> (&lds)[J << (2 * G)], bool active, double F,
-                                              double& L, double& bad0, double& bad1, double* fc = nullptr) {
+                                              double& L, double& bad0, double& bad1, double* fc = nullptr,
+                                              float* ymax = nullptr) {
   constexpr int TILE = 1 << (2 * G);
   constexpr int NB = TILE * J / 16;
   constexpr int BPT = NB / 256;
@@ -455,6 +474,7 @@ __device__ __forceinline__ void kd_fused_body(const PassArgs& a, const ModeMatri
           int r, c;
           rc_of(rf, cf, bA, bB, m >> 2, m & 3, r, c);
           if (r >= c) X[((uint32_t(r) << U) | uint32_t(c)) * kd + kd0 + j] = x[m];
+          if (sizeof(R) == 4 && ymax) *ymax = fmaxf(*ymax, fmaxf(fabsf(float(x[m].re)), fabsf(float(x[m].im))));
         }
       }
     }
