@@ -9,7 +9,7 @@ in HBM before timing starts, as one call, qst_likelihood_grad:
 The headline path is QST_F32X6 (FP32 storage and FP32-level accuracy; the
 two complex products on the 16-bit matrix cores from two-part fp16 splits,
 their operand planes formed inside the call); the FP64, FP32
-(FP32 MFMA products) and BF16 paths, the same step as two calls
+(the same products, G' written) and BF16 paths, the same step as two calls
 (qst_likelihood returning G', then qst_grad_product) and as four separate
 calls with p stored (qst_state_map, qst_povm_probs, qst_nll,
 qst_nll_backward) are reported alongside, each with its error against the
@@ -50,7 +50,8 @@ METRIC = "likelihood fwd+bwd evals/sec at N=11 on 1 GPU; % HBM/MFMA peak; max|Δ
 
 PREC_NOTE = {
     "f64": "complex128 storage, FP64 MFMA products, FP64 POVM passes and NLL",
-    "f32": "complex64 storage, FP32 MFMA products (3M form), FP32 POVM passes, tau and NLL sum in FP64",
+    "f32": "complex64 storage, split fp16 products as f32x6 from N = 10 (FP32 MFMA products, 3M form, below), FP32 "
+           "POVM passes, tau and NLL sum in FP64",
     "bf16": "complex64 storage, T T^dagger on bf16-rounded T (BF16 MFMA, FP32 accumulate), G' T with split "
             "bf16 operands, FP32 POVM passes, tau and NLL sum in FP64",
     "f32x6": "complex64 storage; both complex products with every FP32 operand (row-scaled) split into two fp16 "
@@ -68,14 +69,9 @@ PEAK_HBM_GBS = 8000.0
 # holds only for the kernel sources it was measured on (SHA-256 over the
 # record's source files, in order, the build script with its flags among
 # them); otherwise the reported traffic is null.
-TRAFFIC_F32_SOURCES = ["paper_2207_05341_amd/csrc/k_gemm.hip", "paper_2207_05341_amd/csrc/qst_gemm_tiles.h",
-                       "paper_2207_05341_amd/csrc/qst_device.h", "paper_2207_05341_amd/build.py"]
 TRAFFIC_X6_SOURCES = ["paper_2207_05341_amd/csrc/k_xgemm.hip", "paper_2207_05341_amd/csrc/qst_device.h",
                       "paper_2207_05341_amd/csrc/qst_plan.h", "paper_2207_05341_amd/build.py"]
 TRAFFIC = {
-    # N = 11, d = 2048: 173432.6 KiB fetched x 1.9998 + 32768.0 KiB written x 1.0000
-    "hemm_f32": {"bytes": 388.72e6, "sources": TRAFFIC_F32_SOURCES,
-                 "sources_sha256": "92d43825669e57af5b4f19e9eb0247c3d2ccf7bd79bec7799dba5a7c54c5f5ab"},
     # N = 11, d = 2048: 221292.0 KiB fetched x 1.9998 + 32768.0 KiB written x 1.0000
     "hemm_x6": {"bytes": 486.72e6, "sources": TRAFFIC_X6_SOURCES,
                 "sources_sha256": "d07ab688a35ba92bf5fc8a9fcf87fd584398d052e065de90a6fb1023555d4950"},

@@ -64,7 +64,9 @@ typedef enum {
   /* complex128 T and rho, float64 p and f; FP64 MFMA products. */
   QST_F64 = 0,
   /* complex64 T and rho, float32 p and f; FP32 MFMA products with FP32
-   * accumulation; tau and the log-likelihood sum in FP64. */
+   * accumulation up to N = 9, the split products of QST_F32X6 from N = 10
+   * (smaller errors against FP64 there); tau and the log-likelihood sum in
+   * FP64. */
   QST_F32 = 1,
   /* complex64 storage as QST_F32.  For d >= 256, T T^dagger takes T rounded
    * to bfloat16 (round-to-nearest-even) on the BF16 MFMA with FP32
@@ -81,9 +83,9 @@ typedef enum {
    * bits and a sign) and three partial products per real product (hh, hl,
    * lh: what is dropped is below 2^-22 of |a||b|), FP32 accumulation; the
    * diagonal of T T^dagger is the FP64 sum of its squares.  The products are
-   * more accurate than QST_F32's FP32 MFMA products (measured against FP64)
-   * and several times as fast.  Below d = 128 the products are those of
-   * QST_F32.  The batched form runs it as QST_F32. */
+   * more accurate than FP32 MFMA products (measured against FP64) and several
+   * times as fast.  Below d = 128 the products are those of QST_F32.  The
+   * batched form runs it as QST_F32. */
   QST_F32X6 = 3
 } qst_prec;
 

@@ -321,13 +321,10 @@ hipError_t launch_fixup(const GemmArgs& g, int64_t Pn, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <class P, int X0G = 0>
-hipError_t run_gemm(GemmArgs g, hipStream_t s) {
-  g.kIters = g.d / P::KP;
-  g.iters = int64_t(g.ntiles) * g.kIters;
+template <class P, int X0G>
+hipError_t run_gemm_sk(GemmArgs g, hipStream_t s) {
   const int cus = device_cus();
-  g.dp_tiles = 0;
-  bool sk = P::kStreamK && g.partial != nullptr && g.ntiles % cus != 0;
+  bool sk = g.partial != nullptr && g.ntiles % cus != 0;
   if (sk && X0G != 0) {
     // The POVM epilogue raises the register use of the stream-K kernel.
     // When no workgroup of the plain kernel's grid can finish a whole tile
@@ -361,6 +358,19 @@ hipError_t run_gemm(GemmArgs g, hipStream_t s) {
   return launch_fixup<P, X0G>(g, Pn, s);
 }
 
+template <class P, int X0G = 0>
+hipError_t run_gemm(GemmArgs g, hipStream_t s) {
+  g.kIters = g.d / P::KP;
+  g.iters = int64_t(g.ntiles) * g.kIters;
+  g.dp_tiles = 0;
+  if constexpr (!P::kStreamK) {
+    gemm_dp_kernel<P, X0G><<<unsigned(g.ntiles), 256, 0, s>>>(g);
+    return hipGetLastError();
+  } else {
+    return run_gemm_sk<P, X0G>(g, s);
+  }
+}
+
 template <int G>
 hipError_t run_herk_x0(qst_prec prec, int d, const GemmArgs& g, hipStream_t s, bool planes) {
   if (prec == QST_F64) return run_gemm<CxPolicy<double, true>, G>(g, s);
@@ -376,10 +386,8 @@ hipError_t launch_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int
                        const double* tau_partials, double* tau_dev, void* sk_partial, hipStream_t s,
                        const Pass0Out* x0, const void* planes) {
   const int d = 1 << n;
-  if (prec == QST_F32X6) {
-    if (use_x6(prec, n)) return hipErrorInvalidValue;  // launch_x6_herk forms tau itself
-    prec = QST_F32;
-  }
+  if (use_x6(prec, n)) return hipErrorInvalidValue;  // launch_x6_herk forms tau itself
+  prec = storage_prec(prec);
   if (x0 && (d < BM || x0->g < 4 || x0->g > 6 || !x0->tetra)) return hipErrorInvalidValue;
   ProfScope prof(d < BM ? "herk_small" : (prec == QST_F64 ? "herk_f64" : prec == QST_F32 ? "herk_f32" : "herk_bf16"), s);
   if (d < BM) {
@@ -603,10 +611,8 @@ hipError_t launch_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T,
                        int64_t ldo, int n, const double* tau_dev, const double* upstream_dev,
                        void* sk_partial, hipStream_t s, void* planes) {
   const int d = 1 << n;
-  if (prec == QST_F32X6) {
-    if (use_x6(prec, n)) return launch_x6_hemm(G, ldg, T, ldt, out, ldo, n, tau_dev, upstream_dev, planes, s);
-    prec = QST_F32;
-  }
+  if (use_x6(prec, n)) return launch_x6_hemm(G, ldg, T, ldt, out, ldo, n, tau_dev, upstream_dev, planes, s);
+  prec = storage_prec(prec);
   ProfScope prof(d < BM ? "hemm_small" : (prec == QST_F64 ? "hemm_f64" : prec == QST_F32 ? "hemm_f32" : "hemm_bf16x3"), s);
   if (d < BM) {
     if (prec == QST_F64)

@@ -108,9 +108,9 @@ static_assert((XDIST - 1) * XCOPY < 64, "vmcnt immediate");
 // after which a lane holds one row's maximum over eight lanes; two plain
 // steps finish it (nine shuffles in place of forty).
 template <bool TAU, bool WITH_F>
-__global__ __launch_bounds__(256) void x6_absmax_kernel(const Cx<float>* __restrict__ X, int64_t ld, int d,
-                                                        float* __restrict__ rowp, float* __restrict__ colp,
-                                                        double* __restrict__ partials, const float* __restrict__ f) {
+__device__ __forceinline__ void x6_absmax(const Cx<float>* __restrict__ X, int64_t ld, int d, float* __restrict__ rowp,
+                                          float* __restrict__ colp, double* __restrict__ partials,
+                                          const float* __restrict__ f) {
   constexpr int NT = 256, U = 16;
   __shared__ double red[4];
   __shared__ float cm[8][64];
@@ -196,6 +196,26 @@ __global__ __launch_bounds__(256) void x6_absmax_kernel(const Cx<float>* __restr
   }
 }
 
+// T, for T T^dagger.
+template <bool WITH_F>
+__global__ __launch_bounds__(256) void x6_absmax_t_kernel(const Cx<float>* __restrict__ T, int64_t ld, int d,
+                                                          float* __restrict__ rowp, float* __restrict__ colp,
+                                                          double* __restrict__ partials, const float* __restrict__ f) {
+  x6_absmax<true, WITH_F>(T, ld, d, rowp, colp, partials, f);
+}
+
+// G' (blockIdx.y 0) and T (1), for G' T: one launch for both.
+struct X6Pair {
+  const Cx<float>* X[2];
+  int64_t ld[2];
+  X6Scales sc[2];
+  u16x8* P[2];
+};
+__global__ __launch_bounds__(256) void x6_absmax_gt_kernel(X6Pair p, int d) {
+  const int y = blockIdx.y;
+  x6_absmax<false, false>(p.X[y], p.ld[y], d, p.sc[y].rowp, p.sc[y].colp, nullptr, nullptr);
+}
+
 // The planes of X as a row operand (ROWS; row r scaled by its largest
 // component) and of X^T (COLS; row = column of X, likewise), from one read
 // of X, and what takes the scales out again (rinv, cinv).  A workgroup takes
@@ -212,11 +232,9 @@ __device__ __forceinline__ int split_swz(int r, int c) {  // (r, c) of a 32 x 32
 }
 
 template <bool ROWS, bool COLS, bool SUMS>
-__global__ __launch_bounds__(256) void x6_split_kernel(const Cx<float>* __restrict__ X, int64_t ld, int d,
-                                                       const float* __restrict__ rowp, const float* __restrict__ colp,
-                                                       float* __restrict__ rinv, float* __restrict__ cinv,
-                                                       double* __restrict__ rsum, u16x8* __restrict__ P,
-                                                       u16x8* __restrict__ PT) {
+__device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_t ld, int d, const X6Scales& sc6,
+                                         u16x8* __restrict__ P, u16x8* __restrict__ PT) {
+  const float *rowp = sc6.rowp, *colp = sc6.colp;
   __shared__ Cx<float> blkL[COLS ? 4 : 1][COLS ? 32 * 32 : 1];
   __shared__ float rm[8][32], cmx[2][128], rsc[32], csc[128];
   __shared__ double rs[SUMS ? 4 : 1][32];
@@ -247,7 +265,7 @@ __global__ __launch_bounds__(256) void x6_split_kernel(const Cx<float>* __restri
       for (int q = 1; q < 8; ++q) m = fmaxf(m, rm[q][t]);
       const int e = x6_scale_exp(m, kX6Top);
       rsc[t] = x6_pow2(e);
-      if (bc0 == 0) rinv[32 * br + t] = x6_pow2(-e);
+      if (bc0 == 0) sc6.rinv[32 * br + t] = x6_pow2(-e);
     }
   }
   if constexpr (SUMS) {
@@ -265,7 +283,7 @@ __global__ __launch_bounds__(256) void x6_split_kernel(const Cx<float>* __restri
       const int c = t - 128;
       const int e = x6_scale_exp(fmaxf(cmx[0][c], cmx[1][c]), kX6Top);
       csc[c] = x6_pow2(e);
-      if (br == 0) cinv[32 * bc0 + c] = x6_pow2(-e);
+      if (br == 0) sc6.cinv[32 * bc0 + c] = x6_pow2(-e);
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -274,7 +292,7 @@ __global__ __launch_bounds__(256) void x6_split_kernel(const Cx<float>* __restri
   }
   __syncthreads();
   if constexpr (SUMS) {
-    if (t < 32) rsum[(bc0 / 4) * d + 32 * br + t] = ((rs[0][t] + rs[1][t]) + rs[2][t]) + rs[3][t];
+    if (t < 32) sc6.rsum[(bc0 / 4) * d + 32 * br + t] = ((rs[0][t] + rs[1][t]) + rs[2][t]) + rs[3][t];
   }
   if constexpr (ROWS) {
     const float sc = rsc[row];
@@ -303,6 +321,19 @@ __global__ __launch_bounds__(256) void x6_split_kernel(const Cx<float>* __restri
       write_unit_block(PT + (bc * nkb + 2 * br + h) * kX6BlockVecs + lane, re, im, sc);
     }
   }
+}
+
+// T for T T^dagger, and with TT T^T for G' T of the same call.
+template <bool TT>
+__global__ __launch_bounds__(256) void x6_split_t_kernel(const Cx<float>* __restrict__ T, int64_t ld, int d, X6Scales sc,
+                                                         u16x8* __restrict__ P, u16x8* __restrict__ PT) {
+  x6_split<true, TT, true>(T, ld, d, sc, P, PT);
+}
+
+// G' (blockIdx.y 0) and T^T (1) for G' T.
+__global__ __launch_bounds__(256) void x6_split_gt_kernel(X6Pair p, int d) {
+  if (blockIdx.y == 0) x6_split<true, false, false>(p.X[0], p.ld[0], d, p.sc[0], p.P[0], nullptr);
+  else x6_split<false, true, false>(p.X[1], p.ld[1], d, p.sc[1], nullptr, p.P[1]);
 }
 
 // ---------------------------------------------------------------------------
@@ -688,6 +719,9 @@ __device__ __forceinline__ void x6_epilogue(const XArgs& a, int tr, int tc, cons
           C[r * a.ldc + c] = Cx<float>{xr, xi};
           if (HERK && tr != tc) C[c * a.ldc + r] = Cx<float>{xr, -xi};
         }
+    if constexpr (HERK) {
+      if (tr == tc) __syncthreads();  // the sums are read before the next segment's copies take their place
+    }
   } else {
     constexpr int G = X0G;
     constexpr int S = 64 >> G;
@@ -1052,12 +1086,12 @@ hipError_t launch_x6_herk(const void* T, int64_t ldt, void* rho, int64_t ldr, in
     const Cx<float>* Tf = static_cast<const Cx<float>*>(T);
     const float* ff = static_cast<const float*>(f);
     u16x8* PT = static_cast<u16x8*>(tt_planes);
-    if (f) x6_absmax_kernel<true, true><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, tau_partials, ff);
-    else x6_absmax_kernel<true, false><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, tau_partials, ff);
+    if (f) x6_absmax_t_kernel<true><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, tau_partials, ff);
+    else x6_absmax_t_kernel<false><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, tau_partials, ff);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const auto split = PT ? x6_split_kernel<true, true, true> : x6_split_kernel<true, false, true>;
-    split<<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, sc.rinv, sc.cinv, sc.rsum, P, PT);
+    if (PT) x6_split_t_kernel<true><<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, sc, P, PT);
+    else x6_split_t_kernel<false><<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, sc, P, PT);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   ProfScope prof("herk_x6", s);
@@ -1101,22 +1135,18 @@ hipError_t launch_x6_hemm(const void* G, int64_t ldg, const void* T, int64_t ldt
     a.sb = ready->tcinv;
   } else {
     ProfScope prof("x6_split_gt", s);
-    const X6Scales sg = x6_scales_of(x6_hemm_scales(planes, n, 0), n);
-    const X6Scales st = x6_scales_of(x6_hemm_scales(planes, n, 1), n);
-    const Cx<float>* Gf = static_cast<const Cx<float>*>(G);
-    const Cx<float>* Tf = static_cast<const Cx<float>*>(T);
+    const X6Pair p{{static_cast<const Cx<float>*>(G), static_cast<const Cx<float>*>(T)},
+                   {ldg, ldt},
+                   {x6_scales_of(x6_hemm_scales(planes, n, 0), n), x6_scales_of(x6_hemm_scales(planes, n, 1), n)},
+                   {PG, PT}};
     const unsigned mg = unsigned(std::min<int64_t>(kReduceBlocks, int64_t(d / 64) * (d / 64)));
-    x6_absmax_kernel<false, false><<<mg, 256, 0, s>>>(Gf, ldg, d, sg.rowp, sg.colp, nullptr, nullptr);
-    x6_absmax_kernel<false, false><<<mg, 256, 0, s>>>(Tf, ldt, d, st.rowp, st.colp, nullptr, nullptr);
+    x6_absmax_gt_kernel<<<dim3(mg, 2), 256, 0, s>>>(p, d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    x6_split_kernel<true, false, false><<<x6_split_grid(d), 256, 0, s>>>(Gf, ldg, d, sg.rowp, sg.colp, sg.rinv, sg.cinv,
-                                                                         nullptr, PG, nullptr);
-    x6_split_kernel<false, true, false><<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, st.rowp, st.colp, st.rinv, st.cinv,
-                                                                         nullptr, nullptr, PT);
+    x6_split_gt_kernel<<<dim3(x6_split_grid(d), 2), 256, 0, s>>>(p, d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    a.sa = sg.rinv;
+    a.sa = p.sc[0].rinv;
     a.sa_stride = 1;
-    a.sb = st.cinv;
+    a.sb = p.sc[1].cinv;
   }
   if ((e = x6_allow_lds<x6_hemm_kernel>()) != hipSuccess) return e;
   a.A = PG;

@@ -641,7 +641,8 @@ qst_status qst_likelihood_grad(int n, qst_prec prec, const void* T, int64_t ldT,
   // QST_F32X6 with the tetrahedral POVM and a plan whose adjoint pass 0
   // writes planes: both operands' planes are formed inside the likelihood
   // (the same bits as the split kernels would write from G' and T)
-  const bool in_call = use_x6(prec, n) && povm_host == nullptr && fused_likelihood(pl, prec) &&
+  // (QST_F32 takes the two stages: its combined call equals them bitwise)
+  const bool in_call = prec == QST_F32X6 && use_x6(prec, n) && povm_host == nullptr && fused_likelihood(pl, prec) &&
                        pass0_writes_planes(pl) && tp != nullptr;
   if (in_call) {
     unsigned char* gpl = static_cast<unsigned char*>(tp);

@@ -65,7 +65,7 @@ struct CxPolicy {
   // waves per SIMD the register allocation must allow (fp64 3M: 2, which
   // caps a lane at 256 registers; it would take 260 unconstrained)
   static constexpr int kMinWaves = 2;
-  static constexpr bool kStreamK = true;
+  static constexpr bool kStreamK = sizeof(R) == 8;  // FP32 products of stream-K size run split (k_xgemm.hip)
   struct Smem {
     Cx<R> As[DB ? 2 : 1][KP][BM + PADC];
     Cx<R> Bs[DB ? 2 : 1][KP][BM + PADC];

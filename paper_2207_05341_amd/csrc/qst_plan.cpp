@@ -179,7 +179,7 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
     return at;
   };
   const bool x6 = use_x6(prec, n);
-  // stream-K partial tiles: the QST_F32X6 T T^dagger always, the other
+  // stream-K partial tiles: the split T T^dagger always, the other
   // products from kStreamKMinQubits
   const bool sk = x6 || n >= kStreamKMinQubits;
   const size_t sk_bytes = x6 ? x6_partial_bytes(n) : stream_k_partial_bytes(prec);
@@ -188,7 +188,7 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
   // the BF16 path's bf16 planes (2 for T T^dagger, 8 for G' T), or the
   // split products' planes and scales
   const size_t herk_planes = x6 ? x6_herk_bytes(n) : 2 * D * sizeof(uint16_t);
-  const size_t hemm_plane_bytes = x6 ? x6_hemm_bytes(n) : 8 * D * sizeof(uint16_t);
+  const size_t hemm_plane_bytes = x6 ? x6_hemm_bytes(prec, n) : 8 * D * sizeof(uint16_t);
   auto take_planes = [&](size_t bytes) {
     w.planes = take(bytes);
     w.has_planes = true;
@@ -253,7 +253,7 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
       break;
     case QST_OP_LIKELIHOOD_GRAD: {
       // the likelihood's layout (same offsets), then G' for the routes that
-      // form it, and the planes of the gradient product (QST_F32X6: G''s
+      // form it, and the planes of the gradient product (split products: G''s
       // then T^T's; BF16 path from d = 1024: split planes of G' and T^T);
       // the likelihood's partial tiles serve the gradient product too
       w = workspace_layout(n, prec, QST_OP_LIKELIHOOD, false);

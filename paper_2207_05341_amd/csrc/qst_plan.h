@@ -26,7 +26,16 @@ inline qst_prec storage_prec(qst_prec p) { return p == QST_F32X6 ? QST_F32 : p; 
 // followed by the scales they were split with (X6Scales).
 constexpr int kX6Tile = 128;
 constexpr int kX6MaxGrid = 256;
-inline bool use_x6(qst_prec p, int n) { return p == QST_F32X6 && (int64_t(1) << n) >= kX6Tile; }
+// QST_F32X6 from d = kX6Tile; QST_F32 from kX6F32MinQubits, where the
+// split products take over from the FP32 MFMA products: at N = 10 a
+// likelihood and gradient takes 124 us against 153 us, at N = 11 356 against
+// 673, at N = 12 2320 against 4932, with smaller errors at each.  Below,
+// d = 512 gives 16 tiles of 128 x 128 for 256 compute units, and QST_F32's
+// gradient product has no workspace.
+constexpr int kX6F32MinQubits = 10;
+inline bool use_x6(qst_prec p, int n) {
+  return (p == QST_F32X6 && (int64_t(1) << n) >= kX6Tile) || (p == QST_F32 && n >= kX6F32MinQubits);
+}
 // Schedule of the QST_F32X6 T T^dagger (lower 128 x 128 tiles) on P
 // workgroups, one per CU.  Each tile's K range is cut into sk equal parts
 // ("units"; sk the smallest power of two with tiles x sk >= P, each unit at
@@ -113,10 +122,12 @@ inline X6Scales x6_scales_of(void* base, int n) {
   return X6Scales{r, b, b + np, b + 2 * np, b + 2 * np + d};
 }
 // T T^dagger: T's planes, then its scales.  G' T: G''s planes, T^T's
-// planes, then G''s scales and T's.  36 bytes per element is more than both
-// need from d = kX6Tile; the size is part of the workspace contract.
+// planes, then G''s scales and T's; QST_F32X6 takes 36 bytes per element,
+// more than that from d = kX6Tile, the size its workspace has had.
 inline size_t x6_herk_bytes(int n) { return x6_plane_bytes(n) + x6_scale_bytes(n); }
-inline size_t x6_hemm_bytes(int n) { return (size_t(1) << (2 * n)) * 36; }
+inline size_t x6_hemm_bytes(qst_prec p, int n) {
+  return p == QST_F32X6 ? (size_t(1) << (2 * n)) * 36 : 2 * (x6_plane_bytes(n) + x6_scale_bytes(n));
+}
 inline void* x6_herk_scales(void* planes, int n) { return static_cast<char*>(planes) + x6_plane_bytes(n); }
 inline void* x6_hemm_scales(void* planes, int n, int which) {
   return static_cast<char*>(planes) + 2 * x6_plane_bytes(n) + which * x6_scale_bytes(n);

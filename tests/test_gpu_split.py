@@ -45,7 +45,7 @@ def abs1(x):
 
 
 @pytest.mark.parametrize("pattern", ["plain", "rows", "columns", "zeros", "tiny", "large"])
-@pytest.mark.parametrize("n,pad", [(7, 1), (8, 0), (10, 3), (11, 0)])
+@pytest.mark.parametrize("n,pad", [(7, 1), (8, 0), (10, 3), (11, 0), (12, 0)])
 def test_split_products_entrywise(n, pad, pattern):
     print(f"split products n={n} pad={pad} {pattern}", flush=True)
     d = 1 << n
