@@ -542,8 +542,7 @@ namespace {
 GeneralBufs general_bufs(void* ws, const GeneralLayout& L) {
   return GeneralBufs{reinterpret_cast<double*>(ws_at(ws, L.partials)), reinterpret_cast<double*>(ws_at(ws, L.scal)),
                      L.inter0 ? ws_at(ws, L.inter0) : nullptr, L.inter1 ? ws_at(ws, L.inter1) : nullptr,
-                     ws_at(ws, L.e), L.h ? ws_at(ws, L.h) : nullptr, ws_at(ws, L.bufA), ws_at(ws, L.bufB),
-                     L.p ? ws_at(ws, L.p) : nullptr};
+                     ws_at(ws, L.e), L.h ? ws_at(ws, L.h) : nullptr, ws_at(ws, L.bufA), ws_at(ws, L.bufB)};
 }
 
 }  // namespace

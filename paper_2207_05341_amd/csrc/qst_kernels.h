@@ -169,11 +169,6 @@ hipError_t launch_povm(bool adjoint, qst_prec prec, const PovmPlan& pl, const do
                        const double* F_dev, void* inter0, void* inter1, hipStream_t s,
                        bool use_fast = true);
 
-// Stage 1 of the NLL over D entries of p and f: FP64 partials [4][kReduceBlocks]
-// (L, F, bad0, bad1) as launch_nll's.
-hipError_t launch_nll_partials(qst_prec prec, const void* p, const void* f, int64_t D, double* partials,
-                               hipStream_t s);
-
 // Workspace pieces of the general-POVM calls (general_layout).
 struct GeneralBufs {
   double* partials;  // kReduceBlocks x 4
@@ -181,7 +176,6 @@ struct GeneralBufs {
   void *inter0, *inter1;  // product-POVM pass intermediates
   void *e, *h;            // 4^N reals: Pauli coordinates of rho; summed adjoint input
   void *bufA, *bufB;      // max(4, K)^N reals each: the real passes
-  void* p;                // K^N reals: one setting's probabilities
 };
 
 // p (K^N reals) of a product POVM with real Pauli factors C[i][k][b]

@@ -506,7 +506,6 @@ GeneralLayout general_layout(int n, qst_prec prec, int K, bool with_state) {
   w.bufB = take(M * rb);
   if (with_state) {
     w.h = take(D * rb);
-    w.p = take((DK < 0 ? 0 : size_t(DK)) * rb);
     w.rho = take(D * cb);
     if (use_x6(prec, n)) {
       w.planes = take(x6_herk_bytes(n));

@@ -305,7 +305,7 @@ void pauli_mode_matrices(double W[32], double V[32]);
 // otherwise qst_povm_probs_general (Pauli passes and the real passes).
 struct GeneralLayout {
   size_t partials = 0, scal = 0, sk = 0, planes = 0, rho = 0, inter0 = 0, inter1 = 0;
-  size_t e = 0, h = 0, bufA = 0, bufB = 0, p = 0, total = 0;
+  size_t e = 0, h = 0, bufA = 0, bufB = 0, total = 0;
   bool has_sk = false, has_planes = false;
 };
 GeneralLayout general_layout(int n, qst_prec prec, int K, bool with_state);
