@@ -765,13 +765,11 @@ __device__ __forceinline__ void x6_zero(float (&re)[2][2][16], float (&im)[2][2]
       for (int v = 0; v < 16; ++v) re[i][j][v] = im[i][j][v] = 0.f;
 }
 
-// G' T: one tile per workgroup.
-__global__ __launch_bounds__(256, 1) void x6_hemm_kernel(XArgs a) {
-  extern __shared__ __align__(16) char lds[];
-  const int ts = a.d / XT;
+// Tile of this workgroup in a ts x ts grid: blocks of 4 x 8 tiles per 32
+// consecutive logical workgroups.
+__device__ __forceinline__ void x6_hemm_tile(int ts, int& tr, int& tc) {
   const int lb = int(xcd_order(blockIdx.x, gridDim.x));
-  int tr, tc;
-  if (ts % 8 == 0) {  // blocks of 4 x 8 tiles per 32 consecutive logical workgroups
+  if (ts % 8 == 0) {
     const int grp = lb / 32, within = lb % 32;
     tr = (grp / (ts / 8)) * 4 + within / 8;
     tc = (grp % (ts / 8)) * 8 + within % 8;
@@ -779,6 +777,13 @@ __global__ __launch_bounds__(256, 1) void x6_hemm_kernel(XArgs a) {
     tr = lb / ts;
     tc = lb % ts;
   }
+}
+
+// G' T: one tile per workgroup.
+__global__ __launch_bounds__(256, 1) void x6_hemm_kernel(XArgs a) {
+  extern __shared__ __align__(16) char lds[];
+  int tr, tc;
+  x6_hemm_tile(a.d / XT, tr, tc);
   double scale = 2.0 / *a.tau;
   if (a.up) scale *= *a.up;
   float re[2][2][16], im[2][2][16];
@@ -1031,6 +1036,202 @@ __global__ __launch_bounds__(256, 3) void x6_fixup_kernel(XArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// 64 x 64 tiles (d <= 1024): at d = 1024 G' T has 64 tiles of 128 x 128 for
+// 256 compute units, and T T^dagger 36, which only a split of K could spread
+// (54.7 us, and 25.6 us with 15.9 us to add the partials); 256 and 136 tiles
+// of 64 x 64 need no split.  Per MFMA they read twice the LDS bytes and
+// stream twice the operand bytes, still below what the LDS and the L2 give.
+// Four waves of one 32 x 32 block each; the slabs are 16 KB, and the copies
+// run seven of them ahead.  Fragments alternate between two buffers.
+// ---------------------------------------------------------------------------
+constexpr int YT = kX6SmallTile;
+constexpr int YSLOT = 16 * 1024;      // 16 units: 2 row blocks of A and of B
+constexpr int YNSLOT = 8;
+constexpr int YDIST = YNSLOT - 1;
+constexpr int YCOPY = 4;              // units copied per wave and slab
+static_assert(YSLOT * YNSLOT == XLDS, "one dynamic LDS size");
+static_assert((YDIST - 1) * YCOPY < 64, "vmcnt immediate");
+
+// All panels of output tile (tr, tc): (re, im) of the wave's block.
+template <bool HERK>
+__device__ __forceinline__ void x6_tile64(const XArgs& a, char* lds, int tr, int tc, float (&re)[16], float (&im)[16]) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = w >> 1, wc = w & 1;
+  const int npan = a.d / 16;
+  const uint32_t lbase = __builtin_amdgcn_readfirstlane(lds_address(lds));
+  uint32_t voff[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) voff[u] = uint32_t(lane) * 16 + u * 1024;
+  const u16x8* cbase =
+      uniform_ptr((w >= 2 ? a.B : a.A) + (int64_t(w >= 2 ? tc : tr) * (YT / 32) + (w & 1)) * npan * kX6BlockVecs);
+  auto copy = [&](int kp, int i) {
+    dma16(cbase + int64_t(min(kp, npan - 1)) * kX6BlockVecs, voff[i],
+          lbase + uint32_t((kp % YNSLOT) * YSLOT) + uint32_t(w * 4096 + i * 1024));
+  };
+  const h16x8* ring = reinterpret_cast<const h16x8*>(lds);
+  auto read = [&](int kp, int rb, int pl) { return ring[(kp % YNSLOT) * (YSLOT / 16) + (rb * 4 + pl) * XUNIT + lane]; };
+  enum { RH, RL, IH, IL };
+  h16x8 fa[2][4], fb[2][4];  // [buffer][plane]
+  f16v R, I, K;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    re[v] = im[v] = 0.f;
+    R[v] = I[v] = K[v] = 0.f;
+  }
+#pragma unroll
+  for (int s = 0; s < YDIST; ++s)
+#pragma unroll
+    for (int i = 0; i < YCOPY; ++i) copy(s, i);
+  QST_VMCNT((YDIST - 1) * YCOPY);
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int pl = 0; pl < 4; ++pl) {
+    fa[0][pl] = read(0, wr, pl);
+    fb[0][pl] = read(0, 2 + wc, pl);
+  }
+  auto panel = [&](auto buf_c, int kp) {
+    constexpr int BUF = decltype(buf_c)::value;
+    QST_VMCNT((YDIST - 2) * YCOPY);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const h16x8(&A)[4] = fa[BUF];
+    const h16x8(&B)[4] = fb[BUF];
+    h16x8 sh, sl, dh, dl, nh, nl, nb, mr;
+#pragma unroll
+    for (int m = 0; m < 10; ++m) {
+      if constexpr (HERK) {
+        if (m == 0) R = mfma32(A[RH], B[RH], R);
+        if (m == 1) I = mfma32(A[IH], B[RH], I);
+        if (m == 2) R = mfma32(A[IH], B[IH], R);
+        if (m == 3) I = mfma32(A[RH], nb, I);
+        if (m == 5) R = mfma32(A[IH], dl, R);
+        if (m == 6) I = mfma32(A[RH], nl, I);
+        if (m == 8) R = mfma32(A[IL], dh, R);
+        if (m == 9) I = mfma32(A[RL], nh, I);
+      } else {
+        if (m == 0) I = mfma32(A[RH], B[IH], I);
+        if (m == 1) R = mfma32(A[RH], B[RH], R);
+        if (m == 2) I = mfma32(A[IH], B[RH], I);
+        if (m == 3) R = mfma32(A[IH], nb, R);
+        if (m == 5) I = mfma32(A[RH], dl, I);
+        if (m == 6) R = mfma32(A[IH], nl, R);
+        if (m == 8) I = mfma32(A[RL], dh, I);
+        if (m == 9) R = mfma32(A[IL], nh, R);
+      }
+      if (m == 4) K = mfma32(sh, B[RL], K);
+      if (m == 7) K = mfma32(sl, B[RH], K);
+      if (m == 0) nb = negated(B[IH]);
+      if (m == 1) mr = negated(B[RL]);
+      if (m == 2) dl = B[IL] + mr;
+      if (m == 2) sh = A[RH] + A[IH];
+      if (m == 3) nl = negated(B[IL]);
+      if (m == 4) nl = nl + mr;
+      if (m == 5) mr = negated(B[RH]);
+      if (m == 5) sl = A[RL] + A[IL];
+      if (m == 6) dh = B[IH] + mr;
+      if (m == 7) nh = nb + mr;
+      // the next slab's fragments first: they are needed right after this panel
+      if (m < 4) {
+        fa[1 - BUF][m] = read(kp + 1, wr, m);
+        fb[1 - BUF][m] = read(kp + 1, 2 + wc, m);
+      } else if (m < 4 + YCOPY) {
+        copy(kp + YDIST, m - 4);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  constexpr std::integral_constant<int, 0> b0{};
+  constexpr std::integral_constant<int, 1> b1{};
+  for (int c0 = 0; c0 < npan; c0 += XCHAIN) {  // npan is a multiple of 2
+    const int end = min(npan, c0 + XCHAIN);
+    for (int kp = c0; kp < end; kp += 2) {
+      panel(b0, kp);
+      panel(b1, kp + 1);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      re[v] += R[v];
+      im[v] += I[v];
+      R[v] = I[v] = 0.f;
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    re[v] += K[v];
+    im[v] += K[v];
+  }
+  QST_VMCNT(0);
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(256, 1) void x6_hemm64_kernel(XArgs a) {
+  extern __shared__ __align__(16) char lds[];
+  int tr, tc;
+  x6_hemm_tile(a.d / YT, tr, tc);
+  double scale = 2.0 / *a.tau;
+  if (a.up) scale *= *a.up;
+  float re[16], im[16];
+  x6_tile64<false>(a, lds, tr, tc, re, im);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t r0 = int64_t(tr) * YT + (w >> 1) * 32 + 4 * (lane >> 5), c = int64_t(tc) * YT + (w & 1) * 32 + (lane & 31);
+  const float cs = float(scale * double(a.sb[c]));
+  Cx<float>* C = static_cast<Cx<float>*>(a.C);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int64_t r = r0 + 8 * (v >> 2) + (v & 3);
+    const float rs = a.sa[r * a.sa_stride];
+    C[r * a.ldc + c] = Cx<float>{re[v] * cs * rs, im[v] * cs * rs};
+  }
+}
+
+// One lower tile per workgroup: rho (X0G 0), or the first POVM pass.
+template <int X0G>
+__global__ __launch_bounds__(256, 1) void x6_herk64_kernel(XArgs a) {
+  extern __shared__ __align__(16) char lds[];
+  int tr, tc;
+  tri_decode(xcd_order(blockIdx.x, gridDim.x), tr, tc);
+  float re[16], im[16];
+  x6_tile64<true>(a, lds, tr, tc, re, im);
+  const double tau = x6_tau(a, lds);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && a.tau_out) *a.tau_out = tau;
+  const double scale = 1.0 / tau;
+  const int64_t R0 = int64_t(tr) * YT, C0 = int64_t(tc) * YT;
+  double* diag = reinterpret_cast<double*>(lds + 64 * 64 * sizeof(Cx<float>));
+  if (tr == tc) {
+    x6_diag_sums<64>(a, R0, diag);
+    __syncthreads();
+  }
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int rl = (w >> 1) * 32 + 4 * (lane >> 5), c = (w & 1) * 32 + (lane & 31);
+  const float cs = float(scale * double(a.sb[C0 + c]));
+  Cx<float>* L = reinterpret_cast<Cx<float>*>(lds);
+  Cx<float>* C = static_cast<Cx<float>*>(a.C);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int r = rl + 8 * (v >> 2) + (v & 3);
+    const float rs = a.sa[R0 + r];
+    Cx<float> x{re[v] * cs * rs, im[v] * cs * rs};
+    if (tr == tc && r == c) x = Cx<float>{x6_diag<64>(diag, r, scale), 0.f};
+    if constexpr (X0G == 0) {
+      C[(R0 + r) * a.ldc + C0 + c] = x;
+      if (tr != tc) C[(C0 + c) * a.ldc + R0 + r] = Cx<float>{x.re, -x.im};
+    } else {
+      constexpr int G = X0G, S = 64 >> G, TG = 1 << (2 * G), M = (1 << G) - 1;
+      L[((r >> G) * S + (c >> G)) * TG + swz<G>(r & M, c & M)] = x;
+    }
+  }
+  if constexpr (X0G != 0) {
+    __syncthreads();
+    gemm::GemmArgs g{};
+    g.x0 = a.x0;
+    g.x0g = a.x0g;
+    g.x0up = a.x0up;
+    gemm::x0_rounds<float, X0G>(g, tr, tc, L);
+  }
+}
+
 // The product kernels use more LDS than the static limit: raise the
 // per-kernel limit once per device before the first launch.
 template <auto K>
@@ -1061,6 +1262,13 @@ int x6_cus() {
 
 template <int X0G>
 hipError_t x6_run_herk(XArgs a, int n, hipStream_t s) {
+  if (x6_small_tiles(n)) {
+    hipError_t e = x6_allow_lds<x6_herk64_kernel<X0G>>();
+    if (e != hipSuccess) return e;
+    const int ts = a.d / YT;
+    x6_herk64_kernel<X0G><<<unsigned(ts * (ts + 1) / 2), 256, XLDS, s>>>(a);
+    return hipGetLastError();
+  }
   hipError_t e = x6_allow_lds<x6_herk_kernel<X0G>>();
   if (e != hipSuccess) return e;
   a.sc = x6_herk_sched(n, x6_cus());
@@ -1148,7 +1356,8 @@ hipError_t launch_x6_hemm(const void* G, int64_t ldg, const void* T, int64_t ldt
     a.sa_stride = 1;
     a.sb = p.sc[1].cinv;
   }
-  if ((e = x6_allow_lds<x6_hemm_kernel>()) != hipSuccess) return e;
+  const bool small = x6_small_tiles(n);
+  if ((e = small ? x6_allow_lds<x6_hemm64_kernel>() : x6_allow_lds<x6_hemm_kernel>()) != hipSuccess) return e;
   a.A = PG;
   a.B = PT;
   a.C = out;
@@ -1157,9 +1366,9 @@ hipError_t launch_x6_hemm(const void* G, int64_t ldg, const void* T, int64_t ldt
   a.tau = tau_dev;
   a.up = upstream_dev;
   a.kIters = d / 16;
-  const int ts = d / XT;
+  const int ts = d / (small ? YT : XT);
   ProfScope prof("hemm_x6", s, true);
-  hipExtLaunchKernelGGL(x6_hemm_kernel, dim3(unsigned(ts * ts)), dim3(256), XLDS, s, prof.start(), prof.stop(), 0, a);
+  hipExtLaunchKernelGGL(small ? x6_hemm64_kernel : x6_hemm_kernel, dim3(unsigned(ts * ts)), dim3(256), XLDS, s, prof.start(), prof.stop(), 0, a);
   return hipGetLastError();
 }
 

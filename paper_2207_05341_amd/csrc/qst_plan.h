@@ -26,6 +26,10 @@ inline qst_prec storage_prec(qst_prec p) { return p == QST_F32X6 ? QST_F32 : p; 
 // followed by the scales they were split with (X6Scales).
 constexpr int kX6Tile = 128;
 constexpr int kX6MaxGrid = 256;
+// Up to d = 1024 the products take 64 x 64 tiles, which need no split of K
+// to spread over the compute units (the 64-tile kernels of k_xgemm.hip).
+constexpr int kX6SmallTile = 64;
+inline bool x6_small_tiles(int n) { return n <= 10; }
 // QST_F32X6 from d = kX6Tile; QST_F32 from kX6F32MinQubits, where the
 // split products take over from the FP32 MFMA products: at N = 10 a
 // likelihood and gradient takes 124 us against 153 us, at N = 11 356 against
@@ -94,6 +98,7 @@ inline X6HerkSched x6_herk_sched(int n, int cus) {
   return s;
 }
 inline size_t x6_partial_bytes(int n) {
+  if (x6_small_tiles(n)) return 0;
   // the largest schedule over devices with up to kX6MaxGrid compute units
   size_t most = 0;
   for (int cus = 1; cus <= kX6MaxGrid; ++cus) {
