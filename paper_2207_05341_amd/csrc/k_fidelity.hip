@@ -7,11 +7,11 @@
 // matrix C = M M^dagger / (tau tw), M = W^dagger T (r x d), so
 // F_q = (sum_i sqrt(lambda_i(C)))^2.  Four launches:
 //   1. fid_partial_kernel: M over row blocks of T (FP64 sums; also the
-//      partial sums of |T|^2 for tau) -- reads T once per 8 or 16 target
-//      columns;
+//      partial sums of |T|^2 for tau and of |W|^2 for tw) -- reads T once per
+//      8 or 16 target columns;
 //   2. fid_mreduce_kernel: M from the row-block sums, in order;
 //   3. fid_gram_kernel: C_ab = sum_j M_aj conj(M_bj), one workgroup per pair;
-//   4. fid_jacobi_kernel: tau, tw, C / (tau tw), parallel cyclic Jacobi
+//   4. fid_jacobi_kernel: tau, tw, C / Tr C, parallel cyclic Jacobi
 //      eigenvalues of the Hermitian C (FP64, one workgroup), F_q.
 // Classical fidelity (Eq. F_CF): F_c = (sum_k sqrt(p_hat_k p_k))^2 (negative
 // entries read as 0), a two-stage FP64 reduction.
@@ -39,12 +39,14 @@ struct Zd {
 // chunk of AC target columns a0.., W's rows of the chunk are staged in LDS
 // and every thread adds conj(W_ia) T_ij over its rows; the quarters are
 // summed in order and P[rb][a][j] written.  In the first pass the thread
-// also sums |T_ij|^2 (tau), written per workgroup to taup[rb * ncb + cb].
+// also sums |T_ij|^2 (tau), written per workgroup to taup[rb * ncb + cb];
+// the workgroups of column block 0 also sum |W|^2 of their rows (twp[rb]).
 // AC target columns per pass over T (8 for ranks up to 8, else 16).
 template <typename R, int AC>
 __global__ __launch_bounds__(256) void fid_partial_kernel(const Cx<R>* __restrict__ T, int64_t ldT,
                                                           const Cx<R>* __restrict__ W, int64_t ldW, int r, int d,
-                                                          int RB, Zd* __restrict__ P, double* __restrict__ taup) {
+                                                          int RB, Zd* __restrict__ P, double* __restrict__ taup,
+                                                          double* __restrict__ twp) {
   __shared__ Zd wl[kRowChunk][AC];
   __shared__ Zd red[3][64][AC];
   __shared__ double rtau[4];
@@ -55,7 +57,7 @@ __global__ __launch_bounds__(256) void fid_partial_kernel(const Cx<R>* __restric
   const bool col = j < d;
   const int64_t r0 = int64_t(rb) * RB;
   const int chunk = RB < kRowChunk ? RB : kRowChunk;
-  double tsum = 0.0;
+  double tsum = 0.0, wsum = 0.0;
   for (int a0 = 0; a0 < r; a0 += AC) {
     Zd acc[AC];
 #pragma unroll
@@ -67,6 +69,7 @@ __global__ __launch_bounds__(256) void fid_partial_kernel(const Cx<R>* __restric
         Cx<R> w{R(0), R(0)};
         if (a0 + a < r) w = W[(r0 + i0 + ii) * ldW + a0 + a];
         wl[ii][a] = Zd{double(w.re), double(w.im)};
+        wsum += double(w.re) * double(w.re) + double(w.im) * double(w.im);
       }
       __syncthreads();
       if (col) {
@@ -117,6 +120,10 @@ __global__ __launch_bounds__(256) void fid_partial_kernel(const Cx<R>* __restric
   }
   const double ts = block_sum256(tsum, rtau);
   if (t == 0) taup[blockIdx.x] = ts;
+  if (cb == 0) {
+    const double wsm = block_sum256(wsum, rtau);
+    if (t == 0) twp[rb] = wsm;
+  }
 }
 
 // M_aj = sum_rb P[rb][a][j] (row blocks in order), one entry per thread.
@@ -153,139 +160,144 @@ __global__ __launch_bounds__(256) void fid_gram_kernel(const Zd* __restrict__ M,
   }
 }
 
-// tau (the workgroup partials, in order), tw = sum |W|^2, then the
-// eigenvalues of C / (tau tw) by parallel cyclic Jacobi and F_q.  A sweep
-// takes the r(r-1)/2 pairs in r' - 1 steps of r'/2 disjoint pairs (round-robin
-// order, r' = r rounded up to even; pairs with the padding index are
-// skipped).  A rotation of the pair (p, q) with C_pq = |c| e, e = c / |c|,
-// uses t = sign(x)/(|x| + sqrt(1 + x^2)), x = (C_qq - C_pp) / (2|c|),
-// cs = 1/sqrt(1 + t^2), sn = t cs and the unitary G with G_pp = G_qq = cs,
-// G_pq = sn e, G_qp = -sn conj(e): C <- G^dagger C G zeroes C_pq.  The
-// rotations of one step touch disjoint rows and columns, and each one's
-// parameters depend only on its own rows and columns, so applying them
-// together equals applying them one after another.  Sweeps stop when the
-// off-diagonal mass is below 1e-30 of the diagonal's, or after 40.
-__global__ __launch_bounds__(256) void fid_jacobi_kernel(const double* __restrict__ taup, int ntaup,
-                                                         const void* __restrict__ Wv, int64_t ldW, int r, int d,
-                                                         int f64, const Zd* __restrict__ Cin, double* __restrict__ F) {
-  constexpr int RM = kFidelityMaxRank;
+// tau and tw (the workgroup partials, in order), then the eigenvalues of
+// C / Tr C by parallel cyclic Jacobi and F_q = Tr C / (tau tw) (sum_i
+// sqrt(lambda_i))^2.  A sweep takes the r(r-1)/2 pairs in r' - 1 steps of
+// r'/2 disjoint pairs (round-robin order, r' = r rounded up to even; pairs
+// with the padding index are not rotated).  The rotation of a pair (p, q)
+// with c = C_pq, h = (C_qq - C_pp) / 2 and g = 1 / sqrt(h^2 + |c|^2):
+// cs^2 = (1 + |h| g) / 2, sn e = sign(h) c g / (2 cs) with e = c / |c|, and the
+// unitary G with G_pp = G_qq = cs, G_pq = sn e, G_qp = -sn conj(e):
+// C <- G^dagger C G zeroes C_pq.  The rotations of one step touch disjoint
+// rows and columns, so a step is the 2 x 2 blocks G_k^dagger C_kl G_l of its
+// pairs (k, l), one thread each, with the two rotations formed by the thread
+// itself.  Sweeps stop when the off-diagonal mass is below 1e-30 of the
+// diagonal's, or after 40.
+//
+// Bound by the chain of each step (two reciprocal square roots and the LDS
+// round trip; r <= 16 runs in one wave, whose barriers are free): 8 sweeps of
+// 7 steps at r = 8.  Rotations formed by one thread per pair with divisions,
+// columns and rows updated between barriers, and tw summed here: 67 us; now 38.
+struct Rot {
+  double cs, sr, si;  // cs, sn e
+};
+__device__ __forceinline__ Rot fid_rotation(Zd c, double dp, double dq) {
+  const double a = c.re * c.re + c.im * c.im;
+  if (!(a > 0.0)) return Rot{1.0, 0.0, 0.0};
+  const double h = 0.5 * (dq - dp);
+  const double g = rsqrt(h * h + a);
+  const double c2 = 0.5 + 0.5 * fabs(h) * g;
+  const double rc = rsqrt(c2);
+  const double f = (h >= 0.0 ? 0.5 : -0.5) * g * rc;
+  return Rot{c2 * rc, f * c.re, f * c.im};
+}
+template <int NT>
+__global__ __launch_bounds__(NT) void fid_jacobi_kernel(const double* __restrict__ taup, int ntaup,
+                                                        const double* __restrict__ twp, int ntw, int r,
+                                                        const Zd* __restrict__ Cin, double* __restrict__ F) {
+  constexpr int RM = NT == 64 ? 16 : kFidelityMaxRank;
   __shared__ Zd C[RM][RM + 1];
-  __shared__ double red[4];
-  __shared__ double rot[RM / 2][4];  // cs, sn, e.re, e.im per pair
-  __shared__ int pq[RM / 2][2];
-  __shared__ double colmass[RM];
-  __shared__ double scale_sh;
-  __shared__ int flag;
+  __shared__ double mass[2][NT];
   const int t = threadIdx.x;
-  double s = 0.0;
-  for (int k = t; k < ntaup; k += 256) s += taup[k];
-  const double tau = block_sum256(s, red);
-  s = 0.0;
-  for (int64_t e = t; e < int64_t(d) * r; e += 256) {
-    const int64_t i = e / r, a = e % r;
-    double wr, wi;
-    if (f64) {
-      const Cx<double> w = static_cast<const Cx<double>*>(Wv)[i * ldW + a];
-      wr = w.re;
-      wi = w.im;
-    } else {
-      const Cx<float> w = static_cast<const Cx<float>*>(Wv)[i * ldW + a];
-      wr = double(w.re);
-      wi = double(w.im);
-    }
-    s += wr * wr + wi * wi;
+  // tau in lane order of one wave, tw and the trace by every thread
+  double tau = 0.0, tw = 0.0, tr = 0.0;
+  if (t < 64) {
+    for (int k = t; k < ntaup; k += 64) tau += taup[k];
+    tau = wave_sum(tau);
   }
-  const double tw = block_sum256(s, red);
-  if (t == 0) scale_sh = 1.0 / (tau * tw);
-  __syncthreads();
-  const double scale = scale_sh;
-  for (int e = t; e < r * r; e += 256) {
+  for (int k = 0; k < ntw; ++k) tw += twp[k];
+  for (int k = 0; k < r; ++k) tr += Cin[k * r + k].re;
+  const double inv = tr > 0.0 ? 1.0 / tr : 0.0;
+  for (int e = t; e < r * r; e += NT) {
     const Zd v = Cin[e];
-    C[e / r][e % r] = Zd{v.re * scale, v.im * scale};
+    C[e / r][e % r] = Zd{v.re * inv, v.im * inv};
   }
   __syncthreads();
   const int rp = r + (r & 1), np = rp / 2;
+  const int k = t / np, l = t % np;
+  const bool act = t < np * np;
   for (int sweep = 0; sweep < 40; ++sweep) {
-    if (t < r) {
-      double off = 0.0;
-      for (int i = 0; i < r; ++i)
-        if (i != t) off += C[i][t].re * C[i][t].re + C[i][t].im * C[i][t].im;
-      colmass[t] = off;
+    double off = 0.0, diag = 0.0;
+    for (int e = t; e < r * r; e += NT) {
+      const Zd v = C[e / r][e % r];
+      const double m = v.re * v.re + v.im * v.im;
+      if (e / r == e % r) diag += m;
+      else off += m;
     }
-    __syncthreads();
-    if (t == 0) {
-      double o = 0.0, g = 0.0;
-      for (int k = 0; k < r; ++k) {
-        o += colmass[k];
-        g += C[k][k].re * C[k][k].re;
+    if constexpr (NT == 64) {
+      off = wave_sum(off);
+      diag = wave_sum(diag);
+    } else {
+      mass[0][t] = off;
+      mass[1][t] = diag;
+      __syncthreads();
+      off = diag = 0.0;
+      for (int i = 0; i < NT; i += 64) {
+        off += mass[0][i + (t & 63)];
+        diag += mass[1][i + (t & 63)];
       }
-      flag = (o == 0.0 || o <= 1e-30 * g) ? 1 : 0;
+      off = wave_sum(off);
+      diag = wave_sum(diag);
     }
-    __syncthreads();
-    if (flag) break;
+    if (off == 0.0 || off <= 1e-30 * diag) break;  // the same value in every thread
     for (int step = 0; step < rp - 1; ++step) {
-      if (t < np) {
-        // round-robin positions t and rp - 1 - t; position 0 stays
-        const int u = t, v = rp - 1 - t;
-        const int iu = u == 0 ? 0 : ((u - 1 + step) % (rp - 1)) + 1;
-        const int iv = ((v - 1 + step) % (rp - 1)) + 1;
-        const int p = iu < iv ? iu : iv, q = iu < iv ? iv : iu;
-        double cs = 1.0, sn = 0.0, er = 1.0, ei = 0.0;
-        if (q < r) {
-          const Zd c = C[p][q];
-          const double ac = sqrt(c.re * c.re + c.im * c.im);
-          if (ac > 1e-300) {
-            const double dba = C[q][q].re - C[p][p].re;
-            double tt;
-            if (fabs(dba) > 1e10 * ac) {
-              tt = ac / dba;
-            } else {
-              const double x = dba / (2.0 * ac);
-              tt = (x >= 0.0 ? 1.0 : -1.0) / (fabs(x) + sqrt(1.0 + x * x));
-            }
-            cs = 1.0 / sqrt(1.0 + tt * tt);
-            sn = tt * cs;
-            er = c.re / ac;
-            ei = c.im / ac;
+      // round-robin positions u and rp - 1 - u; position 0 stays
+      auto pair = [&](int u, int& p, int& q) {
+        const int m = rp - 1, xu = u - 1 + step, xv = m - u - 1 + step;  // below 2 m
+        const int iu = u == 0 ? 0 : (xu >= m ? xu - m : xu) + 1;
+        const int iv = (xv >= m ? xv - m : xv) + 1;
+        p = iu < iv ? iu : iv;
+        q = iu < iv ? iv : iu;
+      };
+      int pk, qk, pl, ql;
+      pair(k, pk, qk);
+      pair(l, pl, ql);
+      Zd a[2][2];
+      Rot G{1.0, 0.0, 0.0}, H{1.0, 0.0, 0.0};
+      const bool rk = act && qk < r, rl = act && ql < r;
+      if (act) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int x = i ? qk : pk, y = j ? ql : pl;
+            a[i][j] = (x < r && y < r) ? C[x][y] : Zd{0.0, 0.0};
           }
+        if (rk) G = fid_rotation(C[pk][qk], C[pk][pk].re, C[qk][qk].re);
+        if (rl) H = fid_rotation(C[pl][ql], C[pl][pl].re, C[ql][ql].re);
+      }
+      __syncthreads();
+      if (act) {
+        Zd b[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {  // columns: (cs cp - sn conj(e) cq, sn e cp + cs cq)
+          const Zd cp = a[i][0], cq = a[i][1];
+          b[i][0] = Zd{H.cs * cp.re - (H.sr * cq.re + H.si * cq.im), H.cs * cp.im - (H.sr * cq.im - H.si * cq.re)};
+          b[i][1] = Zd{(H.sr * cp.re - H.si * cp.im) + H.cs * cq.re, (H.sr * cp.im + H.si * cp.re) + H.cs * cq.im};
         }
-        rot[t][0] = cs;
-        rot[t][1] = sn;
-        rot[t][2] = er;
-        rot[t][3] = ei;
-        pq[t][0] = p;
-        pq[t][1] = (q < r && sn != 0.0) ? q : -1;
-      }
-      __syncthreads();
-      for (int task = t; task < np * r; task += 256) {  // columns p, q: C G
-        const int k = task / r, i = task % r, p = pq[k][0], q = pq[k][1];
-        if (q < 0) continue;
-        const double cs = rot[k][0], sn = rot[k][1], er = rot[k][2], ei = rot[k][3];
-        const Zd cp = C[i][p], cq = C[i][q];
-        // cs cp - sn conj(e) cq ;  sn e cp + cs cq
-        C[i][p] = Zd{cs * cp.re - sn * (er * cq.re + ei * cq.im), cs * cp.im - sn * (er * cq.im - ei * cq.re)};
-        C[i][q] = Zd{sn * (er * cp.re - ei * cp.im) + cs * cq.re, sn * (er * cp.im + ei * cp.re) + cs * cq.im};
-      }
-      __syncthreads();
-      for (int task = t; task < np * r; task += 256) {  // rows p, q: G^dagger (C G)
-        const int k = task / r, j = task % r, p = pq[k][0], q = pq[k][1];
-        if (q < 0) continue;
-        const double cs = rot[k][0], sn = rot[k][1], er = rot[k][2], ei = rot[k][3];
-        const Zd rp_ = C[p][j], rq = C[q][j];
-        // cs rp - sn e rq ;  sn conj(e) rp + cs rq; the rotated pair's own
-        // off-diagonal entries are zero by construction and stored as such
-        C[p][j] = j == q ? Zd{0.0, 0.0}
-                         : Zd{cs * rp_.re - sn * (er * rq.re - ei * rq.im), cs * rp_.im - sn * (er * rq.im + ei * rq.re)};
-        C[q][j] = j == p ? Zd{0.0, 0.0}
-                         : Zd{sn * (er * rp_.re + ei * rp_.im) + cs * rq.re, sn * (er * rp_.im - ei * rp_.re) + cs * rq.im};
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {  // rows: (cs rp - sn e rq, sn conj(e) rp + cs rq)
+          const Zd x = b[0][j], y = b[1][j];
+          a[0][j] = Zd{G.cs * x.re - (G.sr * y.re - G.si * y.im), G.cs * x.im - (G.sr * y.im + G.si * y.re)};
+          a[1][j] = Zd{(G.sr * x.re + G.si * x.im) + G.cs * y.re, (G.sr * x.im - G.si * x.re) + G.cs * y.im};
+        }
+        // the rotated pair's own off-diagonal entries are zero by construction
+        if (k == l && rk) a[0][1] = a[1][0] = Zd{0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const int x = i ? qk : pk, y = j ? ql : pl;
+            if (x < r && y < r) C[x][y] = a[i][j];
+          }
       }
       __syncthreads();
     }
   }
   if (t == 0) {
     double sq = 0.0;
-    for (int k = 0; k < r; ++k) sq += sqrt(fmax(C[k][k].re, 0.0));
-    *F = sq * sq;
+    for (int i = 0; i < r; ++i) sq += sqrt(fmax(C[i][i].re, 0.0));
+    *F = tr / (tau * tw) * (sq * sq);
   }
 }
 
@@ -332,15 +344,16 @@ hipError_t run_fidelity_lowrank(const void* T, int64_t ldT, const void* W, int64
   Zd* P = reinterpret_cast<Zd*>(base + fl.mpart);
   Zd* C = reinterpret_cast<Zd*>(base + fl.gram);
   double* taup = reinterpret_cast<double*>(base + fl.taup);
+  double* twp = reinterpret_cast<double*>(base + fl.twp);
   const int ncb = d < 64 ? 1 : d / 64;
   if (r <= 8)
     fid_partial_kernel<R, 8><<<unsigned(ncb * fl.nrb), 256, 0, s>>>(static_cast<const Cx<R>*>(T), ldT,
                                                                     static_cast<const Cx<R>*>(W), ldW, r, d,
-                                                                    d / fl.nrb, P, taup);
+                                                                    d / fl.nrb, P, taup, twp);
   else
     fid_partial_kernel<R, 16><<<unsigned(ncb * fl.nrb), 256, 0, s>>>(static_cast<const Cx<R>*>(T), ldT,
                                                                      static_cast<const Cx<R>*>(W), ldW, r, d,
-                                                                     d / fl.nrb, P, taup);
+                                                                     d / fl.nrb, P, taup, twp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   Zd* M = reinterpret_cast<Zd*>(base + fl.mrow);
@@ -348,7 +361,8 @@ hipError_t run_fidelity_lowrank(const void* T, int64_t ldT, const void* W, int64
   if ((e = hipGetLastError()) != hipSuccess) return e;
   fid_gram_kernel<<<unsigned(r * (r + 1) / 2), 256, 0, s>>>(M, r, d, C);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  fid_jacobi_kernel<<<1, 256, 0, s>>>(taup, ncb * fl.nrb, W, ldW, r, d, sizeof(R) == 8, C, F);
+  if (r <= 16) fid_jacobi_kernel<64><<<1, 64, 0, s>>>(taup, ncb * fl.nrb, twp, fl.nrb, r, C, F);
+  else fid_jacobi_kernel<256><<<1, 256, 0, s>>>(taup, ncb * fl.nrb, twp, fl.nrb, r, C, F);
   return hipGetLastError();
 }
 

@@ -199,12 +199,23 @@ __global__ __launch_bounds__(256) void nll_finish_kernel(const double* __restric
                                                          double* __restrict__ nll,
                                                          unsigned long long* __restrict__ bad) {
   __shared__ double red[4];
-  double sums[4];
-  for (int i = 0; i < 4; ++i) {
-    double acc = 0.0;
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) acc += partials[int64_t(i) * nb + b];
-    sums[i] = block_sum256(acc, red);
+  // the loads of all four arrays issued U at a time before any of the adds
+  // (latency-bound: 7.2 us array by array)
+  constexpr int U = 4;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0}, sums[4];
+  for (int b0 = threadIdx.x; b0 < nb; b0 += 256 * U) {
+    double v[4][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i][u] = partials[int64_t(i) * nb + (b0 + 256 * u < nb ? b0 + 256 * u : nb - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (b0 + 256 * u < nb) acc[i] += v[i][u];
   }
+  for (int i = 0; i < 4; ++i) sums[i] = block_sum256(acc[i], red);
   if (threadIdx.x == 0) {
     double L = sums[0];
     if (sums[1] != sums[1] || sums[3] > 0.0) {

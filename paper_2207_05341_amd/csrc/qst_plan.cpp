@@ -86,6 +86,7 @@ FidelityLayout fidelity_layout(int n) {
   f.mrow = take(size_t(kFidelityMaxRank) * d * 2 * sizeof(double));
   f.gram = take(size_t(kFidelityMaxRank) * kFidelityMaxRank * 2 * sizeof(double));
   f.taup = take(ncb * f.nrb * sizeof(double));
+  f.twp = take(f.nrb * sizeof(double));
   f.cpart = take(size_t(kReduceBlocks) * sizeof(double));
   f.total = off;
   return f;

@@ -247,12 +247,12 @@ inline size_t stream_k_partial_bytes(qst_prec p) {
 
 // Fidelity workspace (qst_fidelity_lowrank / qst_fidelity_classical):
 // W^dagger T partial sums over nrb row blocks and their total M (complex
-// FP64, sized for the largest rank), the r x r Gram matrix, per-workgroup |T|^2 partials and the
+// FP64, sized for the largest rank), the r x r Gram matrix, per-workgroup |T|^2 and |W|^2 partials and the
 // classical-fidelity partials.
 constexpr int kFidelityMaxRank = QST_FIDELITY_MAX_RANK;
 struct FidelityLayout {
   int nrb = 1;
-  size_t mpart = 0, mrow = 0, gram = 0, taup = 0, cpart = 0, total = 0;
+  size_t mpart = 0, mrow = 0, gram = 0, taup = 0, twp = 0, cpart = 0, total = 0;
 };
 FidelityLayout fidelity_layout(int n);
 
