@@ -498,6 +498,13 @@ qst_status likelihood_impl(int n, qst_prec prec, const void* T, int64_t ldT, con
   const bool tetra = povm_host == nullptr;
   const PovmPlan pl = make_povm_plan(n, prec);
   const int64_t d = int64_t(1) << n;
+  if (n <= kSmallMaxQubits && prec != QST_BF16GEMM) {
+    const hipError_t e =
+        launch_small_likelihood(prec, n, tetra, T, ldT, f, W, V, tau_dev, nll_dev, bad_dev, G, ldG, pt, fc_dev, s);
+    if (e != hipSuccess) return hip_fail(e, "likelihood");
+    clear_error();
+    return QST_OK;
+  }
   void* rho = ws_at(ws, L.rho);
   const bool fused = fused_likelihood(pl, prec);
   // tetrahedral POVM: the first pass runs in the epilogue of T T^dagger, so

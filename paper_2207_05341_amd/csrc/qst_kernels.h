@@ -137,6 +137,14 @@ hipError_t launch_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T,
                        void* out, int64_t ldo, int n, const double* tau_dev,
                        const double* upstream_dev, void* sk_partial, hipStream_t s, void* planes = nullptr);
 
+// The whole of qst_likelihood for n <= kSmallMaxQubits in one launch (FP64,
+// FP32): tau, L and F, the counters (bad may be NULL) and, with G, G' in full;
+// W and V: the POVM's forward and adjoint mode matrices; with pt, F_c.
+hipError_t launch_small_likelihood(qst_prec prec, int n, bool tetra, const void* T, int64_t ldT, const void* f,
+                                   const double* W, const double* V, double* tau_dev, double* nll_dev,
+                                   unsigned long long* bad_dev, void* G, int64_t ldG, const void* pt, double* fc_dev,
+                                   hipStream_t s);
+
 // Split products (k_xgemm.hip), d >= kX6Tile.  T T^dagger: planes
 // x6_herk_bytes(n) and partials x6_partial_bytes(n) of workspace; the
 // kernel that finds T's scales also writes the kReduceBlocks partial sums of

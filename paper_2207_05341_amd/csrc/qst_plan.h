@@ -228,6 +228,10 @@ struct WsLayout {
 
 WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute);
 
+// Up to this many qubits the likelihood runs as one launch of one workgroup
+// (k_small.hip), in every precision but QST_BF16GEMM.
+constexpr int kSmallMaxQubits = 5;
+
 constexpr int kReduceBlocks = 1024;  // stage-1 blocks of every FP64 reduction
 constexpr int kReduceThreads = 256;
 
