@@ -85,7 +85,8 @@ typedef enum {
    * diagonal of T T^dagger is the FP64 sum of its squares.  The products are
    * more accurate than FP32 MFMA products (measured against FP64) and several
    * times as fast.  Below d = 128 the products are those of QST_F32.  The
-   * batched form runs it as QST_F32. */
+   * batched form runs it as QST_F32, whose instances with d >= 128 take
+   * the same split products (at 512 threads). */
   QST_F32X6 = 3
 } qst_prec;
 

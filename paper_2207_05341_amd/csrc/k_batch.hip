@@ -6,7 +6,8 @@
 // processing-time schedule).  One workgroup carries one instance through
 // every step of the path:
 //   tau (FP64 block reduction) -> T T^dagger / tau (MFMA tiles of the product
-//   kernels, or per-entry loops below d = 64) -> POVM passes -> L, F (FP64
+//   kernels, split fp16 tiles for FP32 at 512 threads and d >= 128, or
+//   per-entry loops below d = 64) -> POVM passes -> L, F (FP64
 //   block reduction) -> cotangent + adjoint passes -> (2/tau) G' T,
 // keeping rho / G', the POVM intermediate and p in a per-workgroup scratch
 // region.  Every reduction has a fixed order, so results do not depend on
@@ -26,6 +27,7 @@
 #include <map>
 #include <sstream>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "qst_gemm_tiles.h"
@@ -33,6 +35,7 @@
 #include "qst_plan.h"
 #include "qst_povm_fast.h"
 #include "qst_povm_generic.h"
+#include "qst_xtile.h"
 
 namespace qst {
 
@@ -204,6 +207,268 @@ __device__ __forceinline__ void fast_fused_form(const BatchArgs& b, int n, int f
     fast_fused<R, TETRA, 3, 64, SUB, POOL>(b, n, inter, f, F, pool, sub, tid, L, bad0, bad1);
 }
 
+// ---------------------------------------------------------------------------
+// Split products of the FP32 instances with d >= 128 at 512 threads (the
+// arithmetic of k_xgemm.hip: rows scaled by powers of two, two fp16 parts,
+// ten MFMA products per complex product, T T^dagger's diagonal from FP64
+// sums).  Bound by what one workgroup gets from the matrix cores: an N = 8
+// FP32 instance spent 385 of its 550 us in FP32 MFMA products at 55% of one
+// CU's rate.  Measured with every CU at work: N = 8 550 -> 430 us, and
+// 1024 instances of N = 3..8 583 -> 460 us.  The line lies at d = 128, the
+// tile; 64 x 64 instances stay on the FP32 tiles (17 of their 50 us).  No
+// scratch beyond the passes' own: T's planes take the POVM
+// intermediate's place (free until the first pass), G''s planes their own
+// (each 32-row strip is as large as its planes), T^T's planes the
+// intermediate's again (free after the last adjoint pass), the scales p's.
+// ---------------------------------------------------------------------------
+constexpr int kBX6MinDim = 128;
+
+// The thread's index, renewed: addresses made from it are computed where
+// they are used, not kept (and spilled) over the whole instance loop.
+__device__ __forceinline__ int fresh_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Planes of X (d x d, d = 128 or 256) as a row operand, or with COLS of X^T:
+// strips of 32 rows (columns) through LDS, the next strip's loads in flight
+// while one is split.  inv: what takes the rows' scales out; with SUMS the
+// rows' FP64 sums of |x|^2.  P may be X itself without COLS.
+template <bool COLS, bool SUMS>
+__device__ __forceinline__ void batch_split(const Cx<float>* X, int n, u16x8* P, float* inv, double* rsum,
+                                            unsigned char* pool) {
+  constexpr int NT = 512, UMAX = 256 * 32 / NT;
+  const int d = 1 << n, ld = d + 1, t = fresh_thread(), per = d * 32 / NT;
+  Cx<float>* L = reinterpret_cast<Cx<float>*>(pool);
+  float* scl = reinterpret_cast<float*>(L + 32 * ld);
+  Cx<float> v[UMAX];
+  auto load = [&](int rb) {
+#pragma unroll
+    for (int u = 0; u < UMAX; ++u)
+      if (u < per) {
+        const int e = u * NT + t;
+        v[u] = COLS ? X[uint32_t((e >> 5) * d + 32 * rb + (e & 31))] : X[uint32_t(32 * rb * d + e)];
+      }
+  };
+  load(0);
+  for (int rb = 0; rb < d / 32; ++rb) {
+    __syncthreads();  // the pool's previous user, or the previous strip, is done
+#pragma unroll
+    for (int u = 0; u < UMAX; ++u)
+      if (u < per) {
+        const int e = u * NT + t;
+        L[COLS ? (e & 31) * ld + (e >> 5) : (e >> n) * ld + (e & (d - 1))] = v[u];
+      }
+    __syncthreads();
+    if (rb + 1 < d / 32) load(rb + 1);
+    const int row = t >> 4, part = t & 15;
+    float m = 0.f;
+    double s2 = 0.0;
+    for (int i = 0; i < d / 16; ++i) {
+      const Cx<float> x = L[row * ld + part + 16 * i];
+      m = fmaxf(m, fmaxf(fabsf(x.re), fabsf(x.im)));
+      if constexpr (SUMS) s2 += double(x.re) * double(x.re) + double(x.im) * double(x.im);
+    }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      m = fmaxf(m, __shfl_xor(m, o, 64));
+      if constexpr (SUMS) s2 += __shfl_xor(s2, o, 64);
+    }
+    if (part == 0) {
+      const int e = x6_scale_exp(m, kX6Top);
+      scl[row] = x6_pow2(e);
+      inv[32 * rb + row] = x6_pow2(-e);
+      if constexpr (SUMS) rsum[32 * rb + row] = s2;
+    }
+    __syncthreads();
+    const int slots = (d / 16) * 64;  // 512 or 1024
+    for (int z = t; z < slots; z += NT) {
+      const int kb = z >> 6, ln = z & 63, r = ln & 31, k0 = kb * 16 + 8 * (ln >> 5);
+      float re[8], im[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const Cx<float> x = L[r * ld + k0 + e];
+        re[e] = x.re;
+        im[e] = x.im;
+      }
+      write_unit_block(P + (rb * (d / 16) + kb) * kX6BlockVecs + ln, re, im, scl[r]);
+    }
+  }
+  __syncthreads();
+}
+
+// One 128 x 128 output tile by eight waves of 64 x 32 (row half w / 4, column
+// block w % 4): slabs of one 16-deep panel (32 KB) copied global -> LDS three
+// ahead into a ring of four, as in k_xgemm.hip.  At most 16 panels, one
+// accumulation chain.  B's fragments alternate between two buffers, A's row
+// block 0 of the next panel takes the registers it has left, its row block 1
+// is read while block 0's MFMAs run.
+template <bool HERK>
+__device__ __forceinline__ void batch_tile(const u16x8* A, const u16x8* B, int d, int tr, int tc, unsigned char* pool,
+                                           f16v (&R)[2], f16v (&I)[2]) {
+  constexpr int SLOT = 32 * 1024, NSLOT = 4, DIST = NSLOT - 1, COPY = 4;
+  const int t = fresh_thread(), lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wr = w >> 2, wc = w & 3;
+  const int npan = d / 16;
+  const uint32_t lbase = __builtin_amdgcn_readfirstlane(lds_address(reinterpret_cast<const char*>(pool)));
+  uint32_t voff[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) voff[u] = uint32_t(lane) * 16 + u * 1024;
+  const u16x8* cbase = uniform_ptr((w >= 4 ? B : A) + ((w >= 4 ? tc : tr) * 4 + (w & 3)) * npan * kX6BlockVecs);
+  auto copy = [&](int kp, int i) {
+    dma16(cbase + min(kp, npan - 1) * kX6BlockVecs, voff[i],
+          lbase + uint32_t((kp % NSLOT) * SLOT) + uint32_t(w * 4096 + i * 1024));
+  };
+  const h16x8* ring = reinterpret_cast<const h16x8*>(pool);
+  auto read = [&](int kp, int rb, int pl) {
+    return ring[(kp % NSLOT) * (SLOT / 16) + (rb * 4 + pl) * kX6UnitVecs + lane];
+  };
+  enum { RH, RL, IH, IL };
+  h16x8 fa[2][4], fb[2][4];  // [row block][plane], [buffer][plane]
+  f16v K[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) R[i][v] = I[i][v] = K[i][v] = 0.f;
+#pragma unroll
+  for (int s = 0; s < DIST; ++s)
+#pragma unroll
+    for (int i = 0; i < COPY; ++i) copy(s, i);
+  QST_VMCNT((DIST - 1) * COPY);
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int pl = 0; pl < 4; ++pl) {
+    fa[0][pl] = read(0, wr * 2, pl);
+    fb[0][pl] = read(0, 4 + wc, pl);
+  }
+  auto panel = [&](auto buf_c, int kp) {
+    constexpr int BUF = decltype(buf_c)::value;
+    QST_VMCNT((DIST - 2) * COPY);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const h16x8(&Bf)[4] = fb[BUF];
+    h16x8 sh, sl, dh, dl, nh, nl, nb, mr;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const h16x8(&Af)[4] = fa[i];
+#pragma unroll
+      for (int m = 0; m < 10; ++m) {
+        if constexpr (HERK) {
+          if (m == 0) R[i] = mfma32(Af[RH], Bf[RH], R[i]);
+          if (m == 1) I[i] = mfma32(Af[IH], Bf[RH], I[i]);
+          if (m == 2) R[i] = mfma32(Af[IH], Bf[IH], R[i]);
+          if (m == 3) I[i] = mfma32(Af[RH], nb, I[i]);
+          if (m == 5) R[i] = mfma32(Af[IH], dl, R[i]);
+          if (m == 6) I[i] = mfma32(Af[RH], nl, I[i]);
+          if (m == 8) R[i] = mfma32(Af[IL], dh, R[i]);
+          if (m == 9) I[i] = mfma32(Af[RL], nh, I[i]);
+        } else {
+          if (m == 0) I[i] = mfma32(Af[RH], Bf[IH], I[i]);
+          if (m == 1) R[i] = mfma32(Af[RH], Bf[RH], R[i]);
+          if (m == 2) I[i] = mfma32(Af[IH], Bf[RH], I[i]);
+          if (m == 3) R[i] = mfma32(Af[IH], nb, R[i]);
+          if (m == 5) I[i] = mfma32(Af[RH], dl, I[i]);
+          if (m == 6) R[i] = mfma32(Af[IH], nl, R[i]);
+          if (m == 8) I[i] = mfma32(Af[RL], dh, I[i]);
+          if (m == 9) R[i] = mfma32(Af[IL], nh, R[i]);
+        }
+        if (m == 4) K[i] = mfma32(sh, Bf[RL], K[i]);
+        if (m == 7) K[i] = mfma32(sl, Bf[RH], K[i]);
+        if (i == 0) {
+          if (m == 0) nb = negated(Bf[IH]);
+          if (m == 1) mr = negated(Bf[RL]);
+          if (m == 2) dl = Bf[IL] + mr;
+          if (m == 3) nl = negated(Bf[IL]);
+          if (m == 4) nl = nl + mr;
+          if (m == 5) mr = negated(Bf[RH]);
+          if (m == 6) dh = Bf[IH] + mr;
+          if (m == 7) nh = nb + mr;
+          if (m < 4) fa[1][m] = read(kp, wr * 2 + 1, m);
+          else if (m < 4 + COPY) copy(kp + DIST, m - 4);
+        } else {
+          if (m < 4) fa[0][m] = read(kp + 1, wr * 2, m);
+          else if (m < 8) fb[1 - BUF][m - 4] = read(kp + 1, 4 + wc, m - 4);
+        }
+        if (m == 2) sh = Af[RH] + Af[IH];
+        if (m == 5) sl = Af[RL] + Af[IL];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  constexpr std::integral_constant<int, 0> b0{};
+  constexpr std::integral_constant<int, 1> b1{};
+  for (int kp = 0; kp < npan; kp += 2) {
+    panel(b0, kp);
+    panel(b1, kp + 1);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      R[i][v] += K[i][v];
+      I[i][v] += K[i][v];
+    }
+  QST_VMCNT(0);
+  __syncthreads();
+}
+
+// rho = T T^dagger / tau (planes in `planes`) of one instance.
+__device__ __forceinline__ void batch_herk_x6(const Cx<float>* T, int n, double tau, Cx<float>* rho, u16x8* planes,
+                                              float* scales, unsigned char* pool) {
+  const int d = 1 << n;
+  float* inv = scales;
+  double* rsum = reinterpret_cast<double*>(scales + 256);
+  batch_split<false, true>(T, n, planes, inv, rsum, pool);
+  const double it = 1.0 / tau;
+  for (int tr = 0; tr < d / 128; ++tr)
+    for (int tc = 0; tc <= tr; ++tc) {
+      f16v R[2], I[2];
+      batch_tile<true>(planes, planes, d, tr, tc, pool, R, I);
+      const int t = fresh_thread(), lane = t & 63, w = t >> 6, wr = w >> 2, wc = w & 3;
+      const int c = tc * 128 + wc * 32 + (lane & 31);
+      const float cs = float(it * double(inv[c]));
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int r = tr * 128 + wr * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+          const float rs = inv[uint32_t(r)];
+          Cx<float> x{R[i][v] * cs * rs, I[i][v] * cs * rs};
+          if (r == c) x = Cx<float>{float(rsum[uint32_t(r)] * it), 0.f};
+          rho[uint32_t(r * d + c)] = x;
+          if (tr != tc) rho[uint32_t(c * d + r)] = Cx<float>{x.re, -x.im};
+        }
+    }
+}
+
+// grad = scale G' T; G' (in G) is overwritten by its planes.
+__device__ __forceinline__ void batch_hemm_x6(Cx<float>* G, const Cx<float>* T, int n, double scale, Cx<float>* grad,
+                                              u16x8* tplanes, float* scales, unsigned char* pool) {
+  const int d = 1 << n;
+  float *ginv = scales, *tinv = scales + 256;
+  u16x8* gplanes = reinterpret_cast<u16x8*>(G);
+  batch_split<false, false>(G, n, gplanes, ginv, nullptr, pool);
+  batch_split<true, false>(T, n, tplanes, tinv, nullptr, pool);
+  for (int tr = 0; tr < d / 128; ++tr)
+    for (int tc = 0; tc < d / 128; ++tc) {
+      f16v R[2], I[2];
+      batch_tile<false>(gplanes, tplanes, d, tr, tc, pool, R, I);
+      const int t = fresh_thread(), lane = t & 63, w = t >> 6, wr = w >> 2, wc = w & 3;
+      const int c = tc * 128 + wc * 32 + (lane & 31);
+      const float cs = float(scale * double(tinv[c]));
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int r = tr * 128 + wr * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+          const float rs = ginv[uint32_t(r)];
+          grad[uint32_t(r * d + c)] = Cx<float>{R[i][v] * cs * rs, I[i][v] * cs * rs};
+        }
+    }
+}
+
 template <bool BF16>
 constexpr int kBatchPoolBytes = BF16 ? 65536 : 131072;
 
@@ -301,7 +566,12 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
     const double Fsum = block_sum_bcast<NW>(facc, red, slotp);
 
     // 2. rho = T T^dagger / tau
-    if (BF16 && d >= 64 && d <= kBf16SplitMaxDim) {
+    constexpr bool kX6 = sizeof(R) == 4 && !BF16 && THREADS == 512;
+    const bool x6 = kX6 && d >= kBX6MinDim;
+    if (x6) {
+      if constexpr (kX6)
+        batch_herk_x6(T, n, tau, rho, reinterpret_cast<u16x8*>(inter), reinterpret_cast<float*>(pvec), pool);
+    } else if (BF16 && d >= 64 && d <= kBf16SplitMaxDim) {
       gemm::GemmArgs g{};
       g.A = T;
       g.lda = d;
@@ -477,7 +747,10 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
 
     // 6. grad = (2/tau) G' T
     const double scale = 2.0 / tau;
-    if (d >= 64) {
+    if (x6) {
+      if constexpr (kX6)
+        batch_hemm_x6(rho, T, n, scale, grad, reinterpret_cast<u16x8*>(inter), reinterpret_cast<float*>(pvec), pool);
+    } else if (d >= 64) {
       gemm::GemmArgs g{};
       g.A = rho;
       g.lda = d;
