@@ -213,9 +213,10 @@ __device__ __forceinline__ void fast_fused_form(const BatchArgs& b, int n, int f
 // ten MFMA products per complex product, T T^dagger's diagonal from FP64
 // sums).  Bound by what one workgroup gets from the matrix cores: an N = 8
 // FP32 instance spent 385 of its 550 us in FP32 MFMA products at 55% of one
-// CU's rate.  Measured with every CU at work: N = 8 550 -> 430 us, and
-// 1024 instances of N = 3..8 583 -> 460 us.  The line lies at d = 128, the
-// tile; 64 x 64 instances stay on the FP32 tiles (17 of their 50 us).  No
+// CU's rate.  Measured with every CU at work: N = 8 550 -> 400 us, and
+// 1024 instances of N = 3..8 583 -> 439 us; now half of an instance's time is
+// its 9 MB of traffic between stages (256 of them exceed the caches).  The line lies at d = 128, the
+// tile; 64 x 64 instances stay on the FP32 tiles (11 of their 50 us).  No
 // scratch beyond the passes' own: T's planes take the POVM
 // intermediate's place (free until the first pass), G''s planes their own
 // (each 32-row strip is as large as its planes), T^T's planes the
@@ -303,23 +304,27 @@ __device__ __forceinline__ void batch_split(const Cx<float>* X, int n, u16x8* P,
 // ahead into a ring of four, as in k_xgemm.hip.  At most 16 panels, one
 // accumulation chain.  B's fragments alternate between two buffers, A's row
 // block 0 of the next panel takes the registers it has left, its row block 1
-// is read while block 0's MFMAs run.
-template <bool HERK>
+// is read while block 0's MFMAs run.  A DIAG tile's rows serve both operands:
+// slabs of 16 KB.
+template <bool HERK, bool DIAG>
 __device__ __forceinline__ void batch_tile(const u16x8* A, const u16x8* B, int d, int tr, int tc, unsigned char* pool,
                                            f16v (&R)[2], f16v (&I)[2]) {
-  constexpr int SLOT = 32 * 1024, NSLOT = 4, DIST = NSLOT - 1, COPY = 4;
+  constexpr int SLOT = DIAG ? 16 * 1024 : 32 * 1024, NSLOT = 4, DIST = NSLOT - 1, COPY = DIAG ? 2 : 4;
+  constexpr int BROW = DIAG ? 0 : 4;  // B's first 32-row block in a slab
   const int t = fresh_thread(), lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wr = w >> 2, wc = w & 3;
   const int npan = d / 16;
   const uint32_t lbase = __builtin_amdgcn_readfirstlane(lds_address(reinterpret_cast<const char*>(pool)));
-  uint32_t voff[4];
+  const int cw = DIAG ? w >> 1 : w;  // the block this wave copies, or half of it
+  const uint32_t half = DIAG ? uint32_t(w & 1) * 2048 : 0;
+  uint32_t voff[COPY];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) voff[u] = uint32_t(lane) * 16 + u * 1024;
-  const u16x8* cbase = uniform_ptr((w >= 4 ? B : A) + ((w >= 4 ? tc : tr) * 4 + (w & 3)) * npan * kX6BlockVecs);
+  for (int u = 0; u < COPY; ++u) voff[u] = uint32_t(lane) * 16 + u * 1024 + half;
+  const u16x8* cbase = uniform_ptr((cw >= 4 ? B : A) + ((cw >= 4 ? tc : tr) * 4 + (cw & 3)) * npan * kX6BlockVecs);
   auto copy = [&](int kp, int i) {
     dma16(cbase + min(kp, npan - 1) * kX6BlockVecs, voff[i],
-          lbase + uint32_t((kp % NSLOT) * SLOT) + uint32_t(w * 4096 + i * 1024));
+          lbase + uint32_t((kp % NSLOT) * SLOT) + uint32_t(cw * 4096 + i * 1024) + half);
   };
   const h16x8* ring = reinterpret_cast<const h16x8*>(pool);
   auto read = [&](int kp, int rb, int pl) {
@@ -341,7 +346,7 @@ __device__ __forceinline__ void batch_tile(const u16x8* A, const u16x8* B, int d
 #pragma unroll
   for (int pl = 0; pl < 4; ++pl) {
     fa[0][pl] = read(0, wr * 2, pl);
-    fb[0][pl] = read(0, 4 + wc, pl);
+    fb[0][pl] = read(0, BROW + wc, pl);
   }
   auto panel = [&](auto buf_c, int kp) {
     constexpr int BUF = decltype(buf_c)::value;
@@ -389,7 +394,7 @@ __device__ __forceinline__ void batch_tile(const u16x8* A, const u16x8* B, int d
           else if (m < 4 + COPY) copy(kp + DIST, m - 4);
         } else {
           if (m < 4) fa[0][m] = read(kp + 1, wr * 2, m);
-          else if (m < 8) fb[1 - BUF][m - 4] = read(kp + 1, 4 + wc, m - 4);
+          else if (m < 8) fb[1 - BUF][m - 4] = read(kp + 1, BROW + wc, m - 4);
         }
         if (m == 2) sh = Af[RH] + Af[IH];
         if (m == 5) sl = Af[RL] + Af[IL];
@@ -414,33 +419,49 @@ __device__ __forceinline__ void batch_tile(const u16x8* A, const u16x8* B, int d
   __syncthreads();
 }
 
-// rho = T T^dagger / tau (planes in `planes`) of one instance.
-__device__ __forceinline__ void batch_herk_x6(const Cx<float>* T, int n, double tau, Cx<float>* rho, u16x8* planes,
-                                              float* scales, unsigned char* pool) {
+// rho = T T^dagger / tau (T's planes in `planes`, its rows' FP64 sums of
+// |x|^2 in rsum) of one instance.  An off-diagonal tile's mirror image is
+// written as 32-byte pieces: a lane's four values of consecutive rows.
+__device__ __forceinline__ void batch_herk_x6(int n, double tau, Cx<float>* rho, const u16x8* planes,
+                                              const float* inv, const double* rsum, unsigned char* pool) {
   const int d = 1 << n;
-  float* inv = scales;
-  double* rsum = reinterpret_cast<double*>(scales + 256);
-  batch_split<false, true>(T, n, planes, inv, rsum, pool);
   const double it = 1.0 / tau;
-  for (int tr = 0; tr < d / 128; ++tr)
-    for (int tc = 0; tc <= tr; ++tc) {
-      f16v R[2], I[2];
-      batch_tile<true>(planes, planes, d, tr, tc, pool, R, I);
-      const int t = fresh_thread(), lane = t & 63, w = t >> 6, wr = w >> 2, wc = w & 3;
-      const int c = tc * 128 + wc * 32 + (lane & 31);
-      const float cs = float(it * double(inv[c]));
+  auto store = [&](int tr, int tc, const f16v(&R)[2], const f16v(&I)[2]) {
+    const int t = fresh_thread(), lane = t & 63, w = t >> 6, wr = w >> 2, wc = w & 3;
+    const int c = tc * 128 + wc * 32 + (lane & 31);
+    const float cs = float(it * double(inv[uint32_t(c)]));
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int r = tr * 128 + wr * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+      for (int q = 0; q < 4; ++q) {
+        const int r0 = tr * 128 + wr * 64 + i * 32 + 8 * q + 4 * (lane >> 5);
+        float4 m[2];
+        Cx<float>* mx = reinterpret_cast<Cx<float>*>(m);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = r0 + v;
           const float rs = inv[uint32_t(r)];
-          Cx<float> x{R[i][v] * cs * rs, I[i][v] * cs * rs};
+          Cx<float> x{R[i][4 * q + v] * cs * rs, I[i][4 * q + v] * cs * rs};
           if (r == c) x = Cx<float>{float(rsum[uint32_t(r)] * it), 0.f};
           rho[uint32_t(r * d + c)] = x;
-          if (tr != tc) rho[uint32_t(c * d + r)] = Cx<float>{x.re, -x.im};
+          mx[v] = Cx<float>{x.re, -x.im};
         }
-    }
+        if (tr != tc) {
+          float4* o = reinterpret_cast<float4*>(rho + uint32_t(c * d + r0));
+          o[0] = m[0];
+          o[1] = m[1];
+        }
+      }
+  };
+  f16v R[2], I[2];
+  for (int tr = 0; tr < d / 128; ++tr) {
+    batch_tile<true, true>(planes, planes, d, tr, tr, pool, R, I);
+    store(tr, tr, R, I);
+  }
+  if (d > 128) {
+    batch_tile<true, false>(planes, planes, d, 1, 0, pool, R, I);
+    store(1, 0, R, I);
+  }
 }
 
 // grad = scale G' T; G' (in G) is overwritten by its planes.
@@ -454,7 +475,7 @@ __device__ __forceinline__ void batch_hemm_x6(Cx<float>* G, const Cx<float>* T, 
   for (int tr = 0; tr < d / 128; ++tr)
     for (int tc = 0; tc < d / 128; ++tc) {
       f16v R[2], I[2];
-      batch_tile<false>(gplanes, tplanes, d, tr, tc, pool, R, I);
+      batch_tile<false, false>(gplanes, tplanes, d, tr, tc, pool, R, I);
       const int t = fresh_thread(), lane = t & 63, w = t >> 6, wr = w >> 2, wc = w & 3;
       const int c = tc * 128 + wc * 32 + (lane & 31);
       const float cs = float(scale * double(tinv[c]));
@@ -467,6 +488,15 @@ __device__ __forceinline__ void batch_hemm_x6(Cx<float>* G, const Cx<float>* T, 
           grad[uint32_t(r * d + c)] = Cx<float>{R[i][v] * cs * rs, I[i][v] * cs * rs};
         }
     }
+}
+
+// A d x d operand, d <= 32, in LDS with rows of d + 1: the per-entry product
+// loops read each value d times (d = 32, FP32: T T^dagger 18 -> 4 us, G' T
+// 12 -> 4 us against loads through L1).
+template <int THREADS, typename R>
+__device__ __forceinline__ void small_to_lds(const Cx<R>* X, int n, Cx<R>* L) {
+  const int d = 1 << n;
+  for (int e = threadIdx.x; e < d * d; e += THREADS) L[(e >> n) * (d + 1) + (e & (d - 1))] = X[e];
 }
 
 template <bool BF16>
@@ -492,6 +522,7 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
   static_assert(sizeof(typename PH::Smem) <= sizeof(pool) && sizeof(typename PM::Smem) <= sizeof(pool) &&
                     sizeof(gemm::HerkBf16x3Policy::Smem) <= sizeof(pool),
                 "product panels exceed the LDS pool");
+  static_assert(2 * 32 * 33 * sizeof(Cx<R>) <= sizeof(pool), "two 32 x 32 operands must fit the pool");
   static_assert(SUB * sizeof(typename PH::Smem) <= sizeof(pool) && SUB * sizeof(typename PM::Smem) <= sizeof(pool),
                 "one set of panel buffers per 256-thread group must fit the pool");
   double* const red = reinterpret_cast<double*>(pool);
@@ -534,6 +565,8 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
     // and FP64: with the general 4 x 4 form, or beside the BF16 products,
     // they would cost registers -- spills, or the second BF16 workgroup per CU)
     const int fastp = (TETRA && !BF16 && b.fast_forms) ? fast_plan(b.plan, n, sizeof(R) == 8) : 0;
+    constexpr bool kX6 = sizeof(R) == 4 && !BF16 && THREADS == 512;
+    const bool x6 = kX6 && d >= kBX6MinDim;
     double acc = 0.0, facc = 0.0;
     for (int64_t e0 = 0; e0 < D; e0 += kBatch * THREADS) {
       Cx<R> v[kBatch];
@@ -541,13 +574,14 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int64_t e = e0 + u * THREADS + t;
-        v[u] = T[e < D ? e : D - 1];
+        if (!x6) v[u] = T[e < D ? e : D - 1];
         fv[u] = f[e < D ? e : D - 1];
       }
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         if (e0 + u * THREADS + t >= D) continue;
         facc += double(fv[u]);
+        if (x6) continue;  // tau from the split's row sums
         double x = double(v[u].re), y = double(v[u].im);
         if constexpr (BF16) {
           const float hr = bf16_value(float(v[u].re)), hi = bf16_value(float(v[u].im));
@@ -562,15 +596,20 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
         acc += x * x + y * y;
       }
     }
+    R* const scales = pvec;  // p's place: free before the passes and after the adjoint's
+    double* const rsum = reinterpret_cast<double*>(scales + 256);
+    if constexpr (kX6) {
+      if (x6) {
+        batch_split<false, true>(T, n, reinterpret_cast<u16x8*>(inter), scales, rsum, pool);
+        if (t < d) acc = rsum[t];
+      }
+    }
     const double tau = block_sum_bcast<NW>(acc, red, slotp);
     const double Fsum = block_sum_bcast<NW>(facc, red, slotp);
 
     // 2. rho = T T^dagger / tau
-    constexpr bool kX6 = sizeof(R) == 4 && !BF16 && THREADS == 512;
-    const bool x6 = kX6 && d >= kBX6MinDim;
     if (x6) {
-      if constexpr (kX6)
-        batch_herk_x6(T, n, tau, rho, reinterpret_cast<u16x8*>(inter), reinterpret_cast<float*>(pvec), pool);
+      if constexpr (kX6) batch_herk_x6(n, tau, rho, reinterpret_cast<u16x8*>(inter), scales, rsum, pool);
     } else if (BF16 && d >= 64 && d <= kBf16SplitMaxDim) {
       gemm::GemmArgs g{};
       g.A = T;
@@ -613,11 +652,14 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
         if (tile < ntl) gemm::epilogue<PH>(g, tr, tc, aR, aI, 1.0 / tau);
       }
     } else {
+      Cx<R>* const lt = reinterpret_cast<Cx<R>*>(pool);
+      small_to_lds<THREADS>(T, n, lt);
+      __syncthreads();
       for (int64_t e = t; e < D; e += THREADS) {
         const int r = int(e >> n), c = int(e & (d - 1));
         R sr = 0, si = 0;
         for (int k = 0; k < d; ++k) {
-          const Cx<R> x = T[int64_t(r) * d + k], y = T[int64_t(c) * d + k];
+          const Cx<R> x = lt[r * (d + 1) + k], y = lt[c * (d + 1) + k];
           if constexpr (BF16) {  // d < 64: split bf16 x 3
             const float ahr = bf16_value(float(x.re)), ahi = bf16_value(float(x.im));
             const float alr = bf16_value(float(x.re) - ahr), ali = bf16_value(float(x.im) - ahi);
@@ -749,7 +791,7 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
     const double scale = 2.0 / tau;
     if (x6) {
       if constexpr (kX6)
-        batch_hemm_x6(rho, T, n, scale, grad, reinterpret_cast<u16x8*>(inter), reinterpret_cast<float*>(pvec), pool);
+        batch_hemm_x6(rho, T, n, scale, grad, reinterpret_cast<u16x8*>(inter), scales, pool);
     } else if (d >= 64) {
       gemm::GemmArgs g{};
       g.A = rho;
@@ -771,11 +813,16 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
         if (tile < ntl) gemm::epilogue<PM>(g, tr, tc, aR, aI, scale);
       }
     } else {
+      Cx<R>* const lg = reinterpret_cast<Cx<R>*>(pool);
+      Cx<R>* const lt = lg + d * (d + 1);
+      small_to_lds<THREADS>(rho, n, lg);
+      small_to_lds<THREADS>(T, n, lt);
+      __syncthreads();
       for (int64_t e = t; e < D; e += THREADS) {
         const int r = int(e >> n), c = int(e & (d - 1));
         R sr = 0, si = 0;
         for (int k = 0; k < d; ++k) {
-          const Cx<R> x = rho[int64_t(r) * d + k], y = T[int64_t(k) * d + c];
+          const Cx<R> x = lg[r * (d + 1) + k], y = lt[k * (d + 1) + c];
           if constexpr (BF16) {
             const float ahr = bf16_value(float(x.re)), ahi = bf16_value(float(x.im));
             const float alr = bf16_value(float(x.re) - ahr), ali = bf16_value(float(x.im) - ahi);
