@@ -213,11 +213,11 @@ __device__ __forceinline__ void fast_fused_form(const BatchArgs& b, int n, int f
 // ten MFMA products per complex product, T T^dagger's diagonal from FP64
 // sums).  Bound by what one workgroup gets from the matrix cores: an N = 8
 // FP32 instance spent 385 of its 550 us in FP32 MFMA products at 55% of one
-// CU's rate.  Measured with every CU at work: N = 8 550 -> 400 us, and
-// 1024 instances of N = 3..8 583 -> 439 us; now half of an instance's time is
-// its 9 MB of traffic between stages (256 of them exceed the caches).  The line lies at d = 128, the
-// tile; 64 x 64 instances stay on the FP32 tiles (11 of their 50 us).  No
-// scratch beyond the passes' own: T's planes take the POVM
+// CU's rate.  Measured with every CU at work: N = 8 550 -> 400 us, and 1024
+// instances of N = 3..8 583 -> 439 us; now half of an instance's time is its
+// 9 MB of traffic between stages (256 of them exceed the caches).  The line
+// lies at d = 128, the tile; 64 x 64 instances stay on the FP32 tiles (11 of
+// their 50 us).  No scratch beyond the passes' own: T's planes take the POVM
 // intermediate's place (free until the first pass), G''s planes their own
 // (each 32-row strip is as large as its planes), T^T's planes the
 // intermediate's again (free after the last adjoint pass), the scales p's.

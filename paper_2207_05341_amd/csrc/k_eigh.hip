@@ -90,14 +90,10 @@ __device__ __forceinline__ double block_sum_allN(double v, double* red) {
 }
 
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_fold(v, [](double a, double b) { return fmax(a, b); });
 }
 __device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_fold(v, [](double a, double b) { return fmin(a, b); });
 }
 
 // ---------------------------------------------------------------------------

@@ -86,10 +86,41 @@ __device__ __forceinline__ u16x8 bf16_neg(u16x8 a) { return a ^ (uint16_t)0x8000
 // --------------------------------------------------------------------------
 // Deterministic reductions (fixed order for a fixed launch shape).
 // --------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+
+// A value from another lane by a DPP control word.
+template <int CTRL>
+__device__ __forceinline__ double dpp_lane(double v) {
+  const uint2 u = __builtin_bit_cast(uint2, v);
+  return __builtin_bit_cast(double, make_uint2(__builtin_amdgcn_update_dpp(0, u.x, CTRL, 0xf, 0xf, true),
+                                               __builtin_amdgcn_update_dpp(0, u.y, CTRL, 0xf, 0xf, true)));
+}
+
+// op over the 64 lanes of a wave (all of them active, op commutative), the
+// result in every lane: the butterfly over lane distances 32, 16, ..., 1, in
+// the vector registers (half and row swaps, then rotations within rows of 16
+// lanes, which are the butterfly's partners since the values already have
+// that period).  The same sums as through __shfl_xor bit for bit, but each
+// exchange takes a few cycles where a trip through LDS takes about a hundred:
+// a step of the tridiagonal reduction at d = 1024 has five such sums in a row.
+template <typename Op>
+__device__ __forceinline__ double wave_fold(double v, Op op) {
+  uint2 u = __builtin_bit_cast(uint2, v);
+  auto a = __builtin_amdgcn_permlane32_swap(u.x, u.x, false, false);
+  auto b = __builtin_amdgcn_permlane32_swap(u.y, u.y, false, false);
+  v = op(__builtin_bit_cast(double, make_uint2(a[0], b[0])), __builtin_bit_cast(double, make_uint2(a[1], b[1])));
+  u = __builtin_bit_cast(uint2, v);
+  a = __builtin_amdgcn_permlane16_swap(u.x, u.x, false, false);
+  b = __builtin_amdgcn_permlane16_swap(u.y, u.y, false, false);
+  v = op(__builtin_bit_cast(double, make_uint2(a[0], b[0])), __builtin_bit_cast(double, make_uint2(a[1], b[1])));
+  v = op(v, dpp_lane<0x128>(v));  // row_ror:8
+  v = op(v, dpp_lane<0x124>(v));  // row_ror:4
+  v = op(v, dpp_lane<0x122>(v));  // row_ror:2
+  v = op(v, dpp_lane<0x121>(v));  // row_ror:1
   return v;
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+  return wave_fold(v, [](double a, double b) { return a + b; });
 }
 
 // Sum over a 256-thread block; result valid in thread 0.
