@@ -66,16 +66,6 @@ __device__ __forceinline__ C64 conjg(C64 a) { return C64{a.re, -a.im}; }
 constexpr double kEps = DBL_EPSILON;
 constexpr double kClusterTol = 1e-7;  // relative gap below which eigenvalues form a cluster
 
-// Sum over a 256-thread block, the result returned to every thread.
-__device__ __forceinline__ double block_sum_all(double v, double* lds4) {
-  v = wave_sum(v);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  __syncthreads();
-  if (l == 0) lds4[w] = v;
-  __syncthreads();
-  return ((lds4[0] + lds4[1]) + lds4[2]) + lds4[3];
-}
-
 // Sum over a workgroup of NW waves, the result returned to every thread.
 template <int NW>
 __device__ __forceinline__ double block_sum_allN(double v, double* red) {
@@ -109,29 +99,231 @@ struct TrdArgs {
   int d, groups;
 };
 
-// Step k (0 <= k <= d - 2), d <= DMAX, NT threads (NT / 64 waves) per
-// workgroup.  CACHE: v_{k-1} and w_{k-1} are staged in LDS next to v_k
-// (3 DMAX complex values); otherwise w_{k-1} is formed from global memory
-// where it is used.  yprev / pprev: A22 v_{k-1} (entries k .. d-1) and its
-// partial sums from step k - 1; ynext / pnext are this step's.  Rows
-// r >= k + 1 belong to workgroup r % groups, and wave w of it takes its
-// rows first + (w + i NT/64) groups.  Every load that does not depend on
-// this step's arithmetic (the partial sums, row k, v_{k-1} and A22 v_{k-1},
-// and with PRE the wave's first row) is issued before any of it, so the
-// step waits on memory about once.
-template <int DMAX, int NT, bool CACHE>
+// What step k needs of row k once the previous update is in: the reflector
+// H_k = I - t v v^dagger from the column's leading entry al = x[k + 1] and
+// nrm = sum of |x[c]|^2 over c >= k + 2; v[c] = sc x[c], v[k + 1] = 1.
+struct Reflector {
+  double beta;
+  C64 t, sc;
+};
+__device__ __forceinline__ Reflector reflector(C64 al, double nrm) {
+  Reflector h{al.re, C64{0.0, 0.0}, C64{0.0, 0.0}};
+  if (nrm == 0.0 && al.im == 0.0) return h;
+  h.beta = -copysign(sqrt(al.re * al.re + al.im * al.im + nrm), al.re);
+  // two divisions, side by side: 1 / beta and 1 / |alpha - beta|^2
+  const C64 den{al.re - h.beta, al.im};
+  const double ib = 1.0 / h.beta, id = 1.0 / (den.re * den.re + den.im * den.im);
+  h.t = C64{-den.re * ib, -al.im * ib};
+  h.sc = C64{den.re * id, -den.im * id};
+  return h;
+}
+
+// Sums of eight values over a wave: lane l returns the sum of v[l / 8].  Each
+// exchange halves the number of values instead of repeating the sum.
+__device__ __forceinline__ double wave_sum8(const double (&v)[8]) {
+  auto pair = [](double lo, double hi, auto swap) {
+    const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
+    const uint2 x = swap(a.x, b.x), y = swap(a.y, b.y);
+    return __builtin_bit_cast(double, make_uint2(x.x, y.x)) + __builtin_bit_cast(double, make_uint2(x.y, y.y));
+  };
+  auto swap32 = [](uint32_t a, uint32_t b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    return make_uint2(r[0], r[1]);
+  };
+  auto swap16 = [](uint32_t a, uint32_t b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    return make_uint2(r[0], r[1]);
+  };
+  double h[4], q[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) h[i] = pair(v[i], v[i + 4], swap32);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) q[i] = pair(h[i], h[i + 2], swap16);
+  const bool up = threadIdx.x & 8;
+  double x = (up ? q[1] : q[0]) + dpp_lane<0x128>(up ? q[0] : q[1]);
+  x += dpp_lane<0x141>(x);  // the mirror image in the eight lanes
+  x += dpp_lane<0x4e>(x);   // lane ^ 2
+  x += dpp_lane<0xb1>(x);   // lane ^ 1
+  return x;
+}
+
+// Step k (0 <= k <= d - 2), d <= DMAX <= 2048, NT threads per workgroup.
+// yprev / pprev: A22 v_{k-1} (entries k .. d-1) and its partial sums from
+// step k - 1; ynext / pnext are this step's.  Rows r >= k + 1 belong to
+// workgroup r % groups, at most RB of them to one, and thread t of it takes
+// the columns k + t + NT j of all its rows: the entries of v_{k-1}, w_{k-1}
+// and v_k that it needs stay in its registers.  Bound by latency (the
+// operands of d = 1024 are in the caches and take 0.5 us to compute with; a
+// step 7.6 -> 6.7 us against vectors in LDS, eight barriers and sums through
+// LDS; with 256 threads 7.0):
+// every load is issued at the start, the partial sums of the previous step
+// are added by each wave for itself, and the workgroup meets at two barriers
+// only, for the norm of the column and for its rows' sums.
+template <int DMAX, int NT, int RB>
 __global__ __launch_bounds__(NT) void trd_step_kernel(TrdArgs g, int k, const C64* __restrict__ yprev,
+                                                      C64* __restrict__ ynext, const double* __restrict__ pprev,
+                                                      double* __restrict__ pnext) {
+  constexpr int NW = NT / 64, J = DMAX / NT;
+  static_assert(RB % 4 == 0 && J * NT == DMAX, "rows are summed four at a time");
+  __shared__ double red[NW];
+  __shared__ C64 head[2];             // x[k], x[k + 1]
+  __shared__ double ysum[2 * RB][NW];  // the waves' parts of y, rows' re then im in fours
+  __shared__ C64 vown[RB];            // v_k at the workgroup's rows
+  const int d = g.d, P = g.groups, wg = blockIdx.x, tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int r1 = k + 1;
+  const int first = r1 + ((wg - r1 % P) + P) % P;  // first owned row >= k + 1
+  if (first >= d && wg != 0) {
+    if (tid == 0) pnext[wg] = 0.0;
+    return;
+  }
+  const bool prev = k > 0;
+  const C64* vprow = g.V + int64_t(k - 1) * d;  // v_{k-1}; used only when prev
+  const C64* rowk = g.A + int64_t(k) * d;
+  // ---- loads
+  double pp = 0.0;
+  C64 tp{0.0, 0.0}, vpk{0.0, 0.0}, ypk{0.0, 0.0};
+  C64 vpr[RB], ypr[RB];
+  if (prev) {
+    tp = g.tau[k - 1];
+    vpk = vprow[k];
+    ypk = yprev[k];
+    for (int p = lane; p < P; p += 64) pp += pprev[p];
+  }
+  C64 x[J], vp[J], w[J], a[RB][J];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int c = k + tid + NT * j;
+    x[j] = vp[j] = w[j] = C64{0.0, 0.0};
+    if (c < d) {
+      x[j] = rowk[c];
+      if (prev) {
+        vp[j] = vprow[c];
+        w[j] = yprev[c];
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    const int r = first + i * P;
+    vpr[i] = ypr[i] = C64{0.0, 0.0};
+    if (r < d && prev) {
+      vpr[i] = vprow[r];
+      ypr[i] = yprev[r];
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int c = k + tid + NT * j;
+      a[i][j] = (r < d && c > k && c < d) ? g.A[int64_t(r) * d + c] : C64{0.0, 0.0};
+    }
+  }
+  // ---- the previous step's alpha and w; row k with its update applied
+  // (x_c = conj(row_c) is column k)
+  double ap = 0.0;
+  if (prev) ap = -0.5 * (tp.re * tp.re + tp.im * tp.im) * wave_sum(pp);
+  auto wfrom = [&](C64 v, C64 y) -> C64 {
+    const C64 ty = cmul(tp, y);
+    return C64{ty.re + ap * v.re, ty.im + ap * v.im};
+  };
+  const C64 wpk = wfrom(vpk, ypk);
+  double nrm = 0.0;
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int c = k + tid + NT * j;
+    w[j] = wfrom(vp[j], w[j]);
+    const C64 t1 = cmulc(w[j], vpk);   // v[k] conj(w[c])
+    const C64 t2 = cmulc(vp[j], wpk);  // w[k] conj(v[c])
+    x[j] = C64{x[j].re - (t1.re + t2.re), -(x[j].im - (t1.im + t2.im))};
+    if (c >= k + 2 && c < d) nrm += x[j].re * x[j].re + x[j].im * x[j].im;
+  }
+  if (tid < 2) head[tid] = x[0];
+  nrm = wave_sum(nrm);
+  if (lane == 0) red[wave] = nrm;
+  __syncthreads();
+  nrm = 0.0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) nrm += red[i];
+  const Reflector h = reflector(head[1], nrm);
+  C64* vrow = g.V + int64_t(k) * d;
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int c = k + tid + NT * j;
+    C64 v = cmul(x[j], h.sc);
+    if (c == k + 1) v = C64{1.0, 0.0};
+    if (c <= k || c >= d) v = C64{0.0, 0.0};
+    x[j] = v;
+    if (wg == 0 && c > k && c < d) vrow[c] = v;
+  }
+  if (wg == 0 && tid == 0) {
+    g.diag[k] = head[0].re;
+    g.off[k] = h.beta;
+    g.tau[k] = h.t;
+  }
+  // ---- own rows: update with (v_{k-1}, w_{k-1}) on columns >= k + 1, and
+  // y_k[r] = sum_c A22[r][c] v_k[c]
+#pragma unroll
+  for (int b = 0; b < RB; b += 4) {
+    double y[8];
+#pragma unroll
+    for (int i = b; i < b + 4; ++i) {
+      const int r = first + i * P;
+      double yr = 0.0, yi = 0.0;
+      if (r < d) {
+        C64* row = g.A + int64_t(r) * d;
+        const C64 wpr = wfrom(vpr[i], ypr[i]);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+          const int c = k + tid + NT * j;
+          C64 e = a[i][j];
+          if (prev) {
+            const C64 t1 = cmulc(w[j], vpr[i]), t2 = cmulc(vp[j], wpr);
+            e.re -= t1.re + t2.re;
+            e.im -= t1.im + t2.im;
+            if (c > k && c < d) row[c] = e;
+          }
+          yr += e.re * x[j].re - e.im * x[j].im;
+          yi += e.re * x[j].im + e.im * x[j].re;
+          if (c == r) vown[i] = x[j];
+        }
+      }
+      y[i - b] = yr;
+      y[4 + i - b] = yi;
+    }
+    const double sum = wave_sum8(y);
+    if ((lane & 7) == 0) ysum[2 * b + (lane >> 3)][wave] = sum;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  double part = 0.0;
+  const int r = first + lane * P;
+  if (lane < RB && r < d) {
+    const int q = 2 * (lane & ~3) + (lane & 3);
+    double yr = 0.0, yi = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      yr += ysum[q][i];
+      yi += ysum[q + 4][i];
+    }
+    ynext[r] = C64{yr, yi};
+    const C64 v = vown[lane];
+    part = v.re * yr + v.im * yi;  // Re(conj(v_r) y_r)
+  }
+  part = wave_sum(part);
+  if (lane == 0) pnext[wg] = part;
+}
+
+// The same step for d > 2048 (d <= DMAX), where a thread's columns no longer
+// fit its registers: v_k in LDS, w_{k-1} formed from global memory where it
+// is used, and wave w of a workgroup takes its rows first + (w + i NT/64)
+// groups.
+template <int DMAX, int NT>
+__global__ __launch_bounds__(NT) void trd_step_wide_kernel(TrdArgs g, int k, const C64* __restrict__ yprev,
                                                       C64* __restrict__ ynext, const double* __restrict__ pprev,
                                                       double* __restrict__ pnext) {
   constexpr int NW = NT / 64;
   constexpr int J2 = (DMAX + NT - 1) / NT;  // row-k slots per thread
-  constexpr bool PRE = DMAX <= 2048;        // prefetch the wave's first row
-  constexpr int JR = PRE ? DMAX / 64 : 1;   // row slots per lane
-  __shared__ C64 lds[(CACHE ? 3 : 1) * DMAX];
+  __shared__ C64 vs[DMAX];  // v_k (column index), with x_k before scaling
   __shared__ double red[NW];
-  C64* vs = lds;  // v_k (column index), with x_k before scaling
-  C64* vps = lds + (CACHE ? DMAX : 0);
-  C64* wps = lds + (CACHE ? 2 * DMAX : 0);
   const int d = g.d, P = g.groups, wg = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int r1 = k + 1;
@@ -171,14 +363,6 @@ __global__ __launch_bounds__(NT) void trd_step_kernel(TrdArgs g, int k, const C6
       yr0 = yprev[r0];
     }
   }
-  C64 ar[JR];
-  if (PRE) {
-#pragma unroll
-    for (int j = 0; j < JR; ++j) {
-      const int c = k + 1 + lane + 64 * j;
-      ar[j] = (r0 < d && c < d) ? g.A[int64_t(r0) * d + c] : C64{0.0, 0.0};
-    }
-  }
   // ---- the previous step's alpha and w
   C64 tp{0.0, 0.0};
   double ap = 0.0;
@@ -201,10 +385,6 @@ __global__ __launch_bounds__(NT) void trd_step_kernel(TrdArgs g, int k, const C6
       C64 r = rk[j];
       if (prev) {
         const C64 wc = wfrom(vl[j], yl[j]);
-        if (CACHE) {
-          vps[c] = vl[j];
-          wps[c] = wc;
-        }
         const C64 t1 = cmulc(wc, vpk);     // v[k] conj(w[c])
         const C64 t2 = cmulc(vl[j], wpk);  // w[k] conj(v[c])
         r.re -= t1.re + t2.re;
@@ -215,39 +395,27 @@ __global__ __launch_bounds__(NT) void trd_step_kernel(TrdArgs g, int k, const C6
       if (c >= k + 2) nrm += r.re * r.re + r.im * r.im;
     }
   }
-  nrm = block_sum_allN<NW>(nrm, red);  // its barriers also publish vs, vps, wps
+  nrm = block_sum_allN<NW>(nrm, red);  // its barriers also publish vs
   const C64 al = vs[k + 1];
   const double dk = vs[k].re;
-  double beta;
-  C64 t{0.0, 0.0}, sc{0.0, 0.0};
-  if (nrm == 0.0 && al.im == 0.0) {
-    beta = al.re;
-  } else {
-    beta = -copysign(sqrt(al.re * al.re + al.im * al.im + nrm), al.re);
-    t = C64{(beta - al.re) / beta, -al.im / beta};
-    const C64 den{al.re - beta, al.im};  // 1 / (alpha - beta)
-    const double dd = den.re * den.re + den.im * den.im;
-    sc = C64{den.re / dd, -den.im / dd};
-  }
+  const Reflector h = reflector(al, nrm);
   __syncthreads();  // everyone has read vs[k], vs[k + 1]
   C64* vrow = g.V + int64_t(k) * d;
 #pragma unroll
   for (int j = 0; j < J2; ++j) {
     const int c = k + tid + NT * j;
     if (c > k && c < d) {
-      const C64 v = c == k + 1 ? C64{1.0, 0.0} : cmul(rk[j], sc);
+      const C64 v = c == k + 1 ? C64{1.0, 0.0} : cmul(rk[j], h.sc);
       vs[c] = v;
       if (wg == 0) vrow[c] = v;
     }
   }
   if (wg == 0 && tid == 0) {
     g.diag[k] = dk;
-    g.off[k] = beta;
-    g.tau[k] = t;
+    g.off[k] = h.beta;
+    g.tau[k] = h.t;
   }
   __syncthreads();
-  auto vp_at = [&](int c) -> C64 { return CACHE ? vps[c] : vprow[c]; };
-  auto wp_at = [&](int c) -> C64 { return CACHE ? wps[c] : wfrom(vprow[c], yprev[c]); };
   // own rows: update with (v_{k-1}, w_{k-1}) on columns >= k + 1, and
   // y_k[r] = sum_c A22[r][c] v_k[c]
   double part = 0.0;
@@ -261,7 +429,7 @@ __global__ __launch_bounds__(NT) void trd_step_kernel(TrdArgs g, int k, const C6
     double yr = 0.0, yi = 0.0;
     auto visit = [&](int c, C64 a) {
       if (prev) {
-        const C64 wc = wp_at(c), vc = vp_at(c);
+        const C64 vc = vprow[c], wc = wfrom(vc, yprev[c]);
         const C64 t1 = cmulc(wc, vpr), t2 = cmulc(vc, wpr);
         a.re -= t1.re + t2.re;
         a.im -= t1.im + t2.im;
@@ -271,15 +439,7 @@ __global__ __launch_bounds__(NT) void trd_step_kernel(TrdArgs g, int k, const C6
       yr += a.re * v.re - a.im * v.im;
       yi += a.re * v.im + a.im * v.re;
     };
-    if (PRE && i == 0) {
-#pragma unroll
-      for (int j = 0; j < JR; ++j) {
-        const int c = k + 1 + lane + 64 * j;
-        if (c < d) visit(c, ar[j]);
-      }
-    } else {
-      for (int c = k + 1 + lane; c < d; c += 64) visit(c, row[c]);
-    }
+    for (int c = k + 1 + lane; c < d; c += 64) visit(c, row[c]);
     yr = wave_sum(yr);
     yi = wave_sum(yi);
     if (lane == 0) {
@@ -292,24 +452,134 @@ __global__ __launch_bounds__(NT) void trd_step_kernel(TrdArgs g, int k, const C6
   if (tid == 0) pnext[wg] = part;
 }
 
-constexpr int kTrdThreads = 256;
+// A lane's value, the same lane for the whole wave.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const uint2 u = __builtin_bit_cast(uint2, v);
+  return __builtin_bit_cast(double,
+                            make_uint2(__builtin_amdgcn_readlane(u.x, lane), __builtin_amdgcn_readlane(u.y, lane)));
+}
 
-// The last diagonal entry: A[d-1][d-1] with the update of step d - 2.
-__global__ __launch_bounds__(kTrdThreads) void trd_last_kernel(TrdArgs g, const C64* __restrict__ yprev,
-                                                               const double* __restrict__ pprev) {
-  __shared__ double red[4];
-  const int d = g.d, k = d - 1;
-  double s = 0.0;
-  for (int p = threadIdx.x; p < g.groups; p += kTrdThreads) s += pprev[p];
-  s = block_sum_all(s, red);
-  if (threadIdx.x != 0) return;
-  const C64 tp = g.tau[k - 1];
-  const double ap = -0.5 * (tp.re * tp.re + tp.im * tp.im) * s;
-  const C64 v = g.V[int64_t(k - 1) * d + k], ty = cmul(tp, yprev[k]);
-  const C64 w{ty.re + ap * v.re, ty.im + ap * v.im};
-  const C64 a = g.A[int64_t(k) * d + k];
-  const C64 u = cmulc(w, v);  // v conj(w); the update is 2 Re of it on the diagonal
-  g.diag[k] = a.re - 2.0 * u.re;
+// The last steps, k0 = max(0, d - kTrdTail) on, by one workgroup with the
+// trailing matrix in LDS (144 KiB): a step in a launch of its own costs 5.5
+// us at any size, of which more than half is the launch; here it takes 3.6 us
+// on average (d = 1024, 8 waves; 4.1 with 16, whose common work shares the
+// SIMDs, 3.8 with 4).  Every wave holds the vectors in its lanes (column lane + 64 j), so a step
+// has one barrier, for y = A22 v; wave w updates and multiplies the rows
+// k + 1 + w + 8 i, four at a time.  The same steps in the same arithmetic
+// as trd_step_kernel, the update of step k0 - 1 included (yprev its A22 v).
+constexpr int kTrdTail = 96, kTailWaves = 8;
+
+__global__ __launch_bounds__(64 * kTailWaves) void trd_tail_kernel(TrdArgs g, int k0,
+                                                                   const C64* __restrict__ yprev) {
+  constexpr int J = (kTrdTail + 63) / 64;
+  __shared__ C64 S[kTrdTail * kTrdTail];
+  __shared__ C64 ys[2][kTrdTail];
+  const int d = g.d, m = d - k0, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  C64 vp[J], y[J], w[J], x[J];
+  C64 tp{0.0, 0.0};
+  if (k0 > 0) tp = g.tau[k0 - 1];
+#pragma unroll
+  for (int j = 0; j < J; ++j) {
+    const int c = lane + 64 * j;
+    vp[j] = y[j] = C64{0.0, 0.0};
+    if (k0 > 0 && c < m) {
+      vp[j] = g.V[int64_t(k0 - 1) * d + k0 + c];
+      y[j] = yprev[k0 + c];
+    }
+  }
+  for (int r = wave; r < m; r += kTailWaves)
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int c = lane + 64 * j;
+      if (c < m) S[r * kTrdTail + c] = g.A[int64_t(k0 + r) * d + k0 + c];
+    }
+  __syncthreads();
+  auto at = [&](const C64(&u)[J], int c) -> C64 {  // c uniform
+    const C64 v = c < 64 ? u[0] : u[J - 1];
+    return C64{lane_value(v.re, c & 63), lane_value(v.im, c & 63)};
+  };
+  for (int k = 0;; ++k) {
+    // the previous step's w
+    double s = 0.0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int c = lane + 64 * j;
+      if (k > 0) y[j] = c >= k && c < m ? ys[(k - 1) & 1][c] : C64{0.0, 0.0};
+      s += vp[j].re * y[j].re + vp[j].im * y[j].im;
+    }
+    const double ap = -0.5 * (tp.re * tp.re + tp.im * tp.im) * wave_sum(s);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const C64 ty = cmul(tp, y[j]);
+      w[j] = C64{ty.re + ap * vp[j].re, ty.im + ap * vp[j].im};
+    }
+    // row k with the update applied; x_c = conj(row_c) is column k
+    const C64 vpk = at(vp, k), wpk = at(w, k);
+    double nrm = 0.0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int c = lane + 64 * j;
+      x[j] = C64{0.0, 0.0};
+      if (c >= k && c < m) {
+        const C64 a = S[k * kTrdTail + c];
+        const C64 t1 = cmulc(w[j], vpk), t2 = cmulc(vp[j], wpk);
+        x[j] = C64{a.re - (t1.re + t2.re), -(a.im - (t1.im + t2.im))};
+        if (c >= k + 2) nrm += x[j].re * x[j].re + x[j].im * x[j].im;
+      }
+    }
+    const double dk = at(x, k).re;
+    if (threadIdx.x == 0) g.diag[k0 + k] = dk;
+    if (k == m - 1) break;
+    const Reflector h = reflector(at(x, k + 1), wave_sum(nrm));
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int c = lane + 64 * j;
+      C64 v = cmul(x[j], h.sc);
+      if (c == k + 1) v = C64{1.0, 0.0};
+      if (c <= k || c >= m) v = C64{0.0, 0.0};
+      x[j] = v;
+      if (wave == 0 && c > k && c < m) g.V[int64_t(k0 + k) * d + k0 + c] = v;
+    }
+    if (threadIdx.x == 0) {
+      g.off[k0 + k] = h.beta;
+      g.tau[k0 + k] = h.t;
+    }
+    for (int r0 = k + 1 + wave; r0 < m; r0 += 4 * kTailWaves) {
+      double yv[8];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = r0 + i * kTailWaves;
+        double yr = 0.0, yi = 0.0;
+        if (r < m) {
+          const C64 vpr = at(vp, r), wpr = at(w, r);
+#pragma unroll
+          for (int j = 0; j < J; ++j) {
+            if (64 * (j + 1) <= k + 1 || 64 * j >= m) continue;  // no column of this slot is left
+            const int c = lane + 64 * j;
+            if (c > k && c < m) {
+              C64 e = S[r * kTrdTail + c];
+              const C64 t1 = cmulc(w[j], vpr), t2 = cmulc(vp[j], wpr);
+              e.re -= t1.re + t2.re;
+              e.im -= t1.im + t2.im;
+              S[r * kTrdTail + c] = e;
+              yr += e.re * x[j].re - e.im * x[j].im;
+              yi += e.re * x[j].im + e.im * x[j].re;
+            }
+          }
+        }
+        yv[i] = yr;
+        yv[4 + i] = yi;
+      }
+      const double sum = wave_sum8(yv);
+      const int q = lane >> 3, r = r0 + (q & 3) * kTailWaves;
+      if ((lane & 7) == 0 && r < m) (q < 4 ? ys[k & 1][r].re : ys[k & 1][r].im) = sum;
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) vp[j] = x[j];
+    tp = h.t;
+    __syncthreads();
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -999,8 +1269,8 @@ __global__ __launch_bounds__(256) void bt_update_kernel(const C64* __restrict__ 
 
 __global__ void status_out_kernel(const TriScal* __restrict__ ts, int* __restrict__ out) { *out = ts->status; }
 
-// Workgroups of a reduction step: one row per wave at the first step (256
-// threads up to d = 1024, 512 at 2048, 1024 beyond, so at most 256 groups).
+// Workgroups of a reduction step: four rows each up to d = 1024, eight at
+// 2048 (the RB of the kernels), sixteen and more beyond, so at most 256.
 int trd_groups(int d) {
   const int waves = d <= 1024 ? 4 : (d <= 2048 ? 8 : 16);
   const int g = (d + waves - 1) / waves;
@@ -1035,19 +1305,19 @@ hipError_t launch_tridiagonalize(int n, void* A, void* V, const EighWork& w, hip
   TrdArgs g{static_cast<C64*>(A), static_cast<C64*>(V), w.diag, w.off, static_cast<C64*>(w.tau), d, P};
   C64* y[2] = {static_cast<C64*>(w.y0), static_cast<C64*>(w.y1)};
   double* p[2] = {w.p0, w.p1};
-  for (int k = 0; k <= d - 2; ++k) {
+  const int k0 = d > kTrdTail ? d - kTrdTail : 0;
+  for (int k = 0; k < k0; ++k) {
     const int a = k & 1, b = a ^ 1;  // step k reads y[b], p[b] (step k - 1) and writes y[a], p[a]
     if (d <= 512)
-      trd_step_kernel<512, 256, true><<<P, 256, 0, s>>>(g, k, y[b], y[a], p[b], p[a]);
+      trd_step_kernel<512, 256, 4><<<P, 256, 0, s>>>(g, k, y[b], y[a], p[b], p[a]);
     else if (d <= 1024)
-      trd_step_kernel<1024, 256, true><<<P, 256, 0, s>>>(g, k, y[b], y[a], p[b], p[a]);
+      trd_step_kernel<1024, 512, 4><<<P, 512, 0, s>>>(g, k, y[b], y[a], p[b], p[a]);
     else if (d <= 2048)
-      trd_step_kernel<2048, 512, true><<<P, 512, 0, s>>>(g, k, y[b], y[a], p[b], p[a]);
+      trd_step_kernel<2048, 512, 8><<<P, 512, 0, s>>>(g, k, y[b], y[a], p[b], p[a]);
     else
-      trd_step_kernel<8192, 1024, false><<<P, 1024, 0, s>>>(g, k, y[b], y[a], p[b], p[a]);
+      trd_step_wide_kernel<8192, 1024><<<P, 1024, 0, s>>>(g, k, y[b], y[a], p[b], p[a]);
   }
-  const int last = (d - 2) & 1;
-  trd_last_kernel<<<1, kTrdThreads, 0, s>>>(g, y[last], p[last]);
+  trd_tail_kernel<<<1, 64 * kTailWaves, 0, s>>>(g, k0, y[(k0 & 1) ^ 1]);
   return hipGetLastError();
 }
 
