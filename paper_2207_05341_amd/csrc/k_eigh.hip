@@ -20,7 +20,7 @@
 //    zero (a perturbation of the size of the reduction's own rounding); the
 //    unreduced blocks are then independent.
 // 3. Eigenvalues by multisection: a wave per eigenvalue evaluates the Sturm
-//    count (the number of negative pivots of T - x I) of its block at 64
+//    count (sign changes of the leading minors of T - x I) of its block at 64
 //    points of the current interval and keeps the sub-interval that holds
 //    the eigenvalue: about 6 bits per round, full precision in 9 or 10.
 // 4. Eigenvectors by twisted factorizations, one thread per eigenvalue:
@@ -674,14 +674,20 @@ __global__ __launch_bounds__(256) void tri_split_kernel(const double* __restrict
 // 3. Eigenvalues by multisection of Sturm counts
 // ---------------------------------------------------------------------------
 
-// Number of eigenvalues of the block [s, t) below x (a and the squared
-// off-diagonal e2 in LDS).
-__device__ __forceinline__ int sturm_count(const double* a, const double* e2, int s, int t, double x, double pivmin) {
-  double q = a[s] - x;
-  if (fabs(q) < pivmin) q = -pivmin;
-  int c = q < 0.0;
+// Number of eigenvalues of the block [s, t) below x: the sign changes of
+// p_k = (a_k - x) p_{k-1} - e_{k-1}^2 p_{k-2}, a and e2 = e^2 in LDS scaled to
+// ||T|| in [1, 2).  A p that is zero counts with its neighbours (the next one
+// has the sign opposite to the one before it).  No division: the chain from
+// one p to the next is one fused multiply-add where the pivots
+// q_k = p_k / p_{k-1} take a division each, and the count belongs to a matrix
+// as close to T.  In 8 steps p grows by less than 2^24 and, unreduced as the
+// block is, shrinks by less than 2^-500, so it is rescaled every 8.
+__device__ __forceinline__ int sturm_count(const double* a, const double* e2, int s, int t, double x) {
+  double p0 = 1.0, p = a[s] - x;
+  auto top = [](double v) { return uint32_t(__double2hiint(v)); };
+  uint32_t c = top(p) >> 31;
   int k = s + 1;
-  for (; k + 8 <= t; k += 8) {  // the LDS reads of 8 steps ahead of their divisions
+  for (; k + 8 <= t; k += 8) {  // the LDS reads of 8 steps ahead of their use
     double ak[8], ek[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
@@ -690,17 +696,22 @@ __device__ __forceinline__ int sturm_count(const double* a, const double* e2, in
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      q = ak[u] - ek[u] / q;
-      if (fabs(q) < pivmin) q = -pivmin;
-      c += q < 0.0;
+      const double q = fma(ak[u], p, -(ek[u] * p0));
+      c += (top(q) ^ top(p)) >> 31;
+      p0 = p;
+      p = q;
     }
+    const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(p0)));
+    p = ldexp(p, -ex);
+    p0 = ldexp(p0, -ex);
   }
   for (; k < t; ++k) {
-    q = (a[k] - x) - e2[k - 1] / q;
-    if (fabs(q) < pivmin) q = -pivmin;
-    c += q < 0.0;
+    const double q = fma(a[k] - x, p, -(e2[k - 1] * p0));
+    c += (top(q) ^ top(p)) >> 31;
+    p0 = p;
+    p = q;
   }
-  return c;
+  return int(c);
 }
 
 // A wave per index i: the (i - s)-th smallest eigenvalue of its block; the
@@ -711,9 +722,10 @@ __global__ __launch_bounds__(256) void tri_eigvals_kernel(const double* __restri
                                                           const int* __restrict__ bend,
                                                           const TriScal* __restrict__ ts, double* __restrict__ lam) {
   __shared__ double sa[DMAX], se2[DMAX];
+  const int scale = ts->tnorm > 0.0 ? ilogb(ts->tnorm) : 0;  // ||T|| 2^-scale in [1, 2)
   for (int k = threadIdx.x; k < d; k += 256) {
-    sa[k] = a[k];
-    const double ek = k < d - 1 ? e[k] : 0.0;
+    sa[k] = ldexp(a[k], -scale);
+    const double ek = k < d - 1 ? ldexp(e[k], -scale) : 0.0;
     se2[k] = ek * ek;
   }
   __syncthreads();
@@ -722,10 +734,10 @@ __global__ __launch_bounds__(256) void tri_eigvals_kernel(const double* __restri
   if (i >= d) return;
   const int s = bstart[i], t = bend[i], j = i - s, n = t - s;
   if (n == 1) {
-    if (lane == 0) lam[i] = sa[s];
+    if (lane == 0) lam[i] = a[s];
     return;
   }
-  const double pivmin = ts->pivmin;
+  const double pivmin = DBL_MIN;
   double gl = HUGE_VAL, gu = -HUGE_VAL;
   for (int k = s + lane; k < t; k += 64) {
     const double r = (k > s ? sqrt(se2[k - 1]) : 0.0) + (k < t - 1 ? sqrt(se2[k]) : 0.0);
@@ -740,7 +752,7 @@ __global__ __launch_bounds__(256) void tri_eigvals_kernel(const double* __restri
   double lo = gl, hi = gu;
   for (int it = 0; it < 64; ++it) {
     const double x = lo + (hi - lo) * (double(lane + 1) / 65.0);
-    const int cnt = sturm_count(sa, se2, s, t, x, pivmin);
+    const int cnt = sturm_count(sa, se2, s, t, x);
     const unsigned long long above = __ballot(cnt > j);  // lanes whose point lies above the eigenvalue
     const int f = above ? __ffsll(above) - 1 : 64;
     const double xl = __shfl(x, f > 0 ? f - 1 : 0, 64), xh = __shfl(x, f < 64 ? f : 63, 64);
@@ -749,7 +761,7 @@ __global__ __launch_bounds__(256) void tri_eigvals_kernel(const double* __restri
     hi = nhi;
     if (hi - lo <= 2.0 * kEps * fmax(fabs(lo), fabs(hi)) + pivmin) break;
   }
-  if (lane == 0) lam[i] = 0.5 * (lo + hi);
+  if (lane == 0) lam[i] = ldexp(0.5 * (lo + hi), scale);
 }
 
 // ---------------------------------------------------------------------------
