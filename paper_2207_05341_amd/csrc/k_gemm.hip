@@ -324,7 +324,11 @@ hipError_t launch_fixup(const GemmArgs& g, int64_t Pn, hipStream_t s) {
 template <class P, int X0G>
 hipError_t run_gemm_sk(GemmArgs g, hipStream_t s) {
   const int cus = device_cus();
-  bool sk = g.partial != nullptr && g.ntiles % cus != 0;
+  // Stream-K where whole tiles would leave the last wave of workgroups partly
+  // empty, or where one tile per CU would leave each SIMD a single wave (FP64
+  // G' T at N = 10, 256 tiles: 131.8 us whole, 124.3 us as two halves each
+  // with the fix-up).
+  bool sk = g.partial != nullptr && (g.ntiles % cus != 0 || g.ntiles == cus);
   if (sk && X0G != 0) {
     // The POVM epilogue raises the register use of the stream-K kernel.
     // When no workgroup of the plain kernel's grid can finish a whole tile
