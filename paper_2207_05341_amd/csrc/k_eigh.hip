@@ -1058,12 +1058,12 @@ __global__ __launch_bounds__(256) void bt_gram_kernel(const C64* __restrict__ V,
 
 // Workgroup b: G = the sum of block b's partial Gram matrices (fixed
 // order), then the triangular factor column by column:
-// T[j][j] = tau_j, T[0:j][j] = -tau_j T[0:j][0:j] G[0:j][j].
+// T[j][j] = tau_j, T[0:j][j] = -tau_j T[0:j][0:j] G[0:j][j], four threads to
+// a row.  Bound by the chain of columns (d = 1024: 164 -> 83 us).
 __global__ __launch_bounds__(256) void bt_tmat_kernel(const C64* __restrict__ Gp, int gchunks,
                                                       const C64* __restrict__ tau, int d, C64* __restrict__ Tall) {
   __shared__ C64 gt[kNb][kNb + 1];  // G, then T in place
-  __shared__ C64 tmp[kNb];
-  const int b = blockIdx.x, tid = threadIdx.x;
+  const int b = blockIdx.x, tid = threadIdx.x, row = tid >> 2, quarter = tid & 3;
   const int k0 = b * kNb, nk = min(kNb, d - 1 - k0);
   for (int q = tid; q < kNb * kNb; q += 256) {
     C64 g{0.0, 0.0};
@@ -1078,28 +1078,26 @@ __global__ __launch_bounds__(256) void bt_tmat_kernel(const C64* __restrict__ Gp
   for (int j = 0; j < kNb; ++j) {
     const C64 tj_ = j < nk ? tau[k0 + j] : C64{0.0, 0.0};
     C64 sum{0.0, 0.0};
-    if (tid < j) {
-      for (int q = tid; q < j; ++q) {
-        const C64 p = cmul(gt[tid][q], gt[q][j]);  // T[tid][q] G[q][j]
-        sum.re += p.re;
-        sum.im += p.im;
-      }
+    for (int q = row + quarter; q < j; q += 4) {
+      const C64 p = cmul(gt[row][q], gt[q][j]);  // T[row][q] G[q][j]
+      sum.re += p.re;
+      sum.im += p.im;
     }
+    sum.re += dpp_lane<0x4e>(sum.re);  // lane ^ 2
+    sum.im += dpp_lane<0x4e>(sum.im);
+    sum.re += dpp_lane<0xb1>(sum.re);  // lane ^ 1
+    sum.im += dpp_lane<0xb1>(sum.im);
     __syncthreads();
-    if (tid < kNb) {
-      C64 v;
-      if (tid < j) {
+    if (quarter == 0) {
+      C64 v{0.0, 0.0};
+      if (row < j) {
         const C64 p = cmul(tj_, sum);
         v = C64{-p.re, -p.im};
-      } else if (tid == j) {
+      } else if (row == j) {
         v = tj_;
-      } else {
-        v = C64{0.0, 0.0};
       }
-      tmp[tid] = v;
+      gt[row][j] = v;
     }
-    __syncthreads();
-    if (tid < kNb) gt[tid][j] = tmp[tid];
     __syncthreads();
   }
   C64* T = Tall + int64_t(b) * kNb * kNb;
@@ -1158,37 +1156,52 @@ __global__ __launch_bounds__(256) void bt_wfactor_kernel(const C64* __restrict__
 }
 
 // Partial sums of V_b^dagger Z over the row chunk y of R rows (rows from
-// k0 + 1): P[y][j][c] for j < 64 and the column tile x of 64.
+// k0 + 1): P[y][j][c] for the 32 reflectors j of half z and the column tile x
+// of 64.  The next 16 rows are loaded while 16 are summed, and half of the
+// reflectors to a workgroup occupies twice the CUs (a block of d = 1024: 29.5
+// -> 18.8 us).
 __global__ __launch_bounds__(256) void bt_partial_kernel(const C64* __restrict__ V, const C64* __restrict__ Z, int d,
                                                          int k0, int nk, int R, C64* __restrict__ P) {
-  __shared__ C64 vs[16][kNb + 1];
-  __shared__ C64 zs[16][kNb + 1];
-  const int tid = threadIdx.x, tj = tid >> 4, tc = tid & 15;
+  __shared__ C64 vs[2][16][kNb / 2 + 1];
+  __shared__ C64 zs[2][16][kNb + 1];
+  const int tid = threadIdx.x, tj = tid >> 4, tc = tid & 15, j0 = blockIdx.z * (kNb / 2);
   const int c0 = blockIdx.x * 64, rs = k0 + 1 + blockIdx.y * R, re = min(d, rs + R);
-  C64 acc[4][4];
+  C64 acc[2][4];  // reflectors j0 + 2 tj + x, columns tc + 16 y
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int y = 0; y < 4; ++y) acc[x][y] = C64{0.0, 0.0};
-  for (int r0 = rs; r0 < re; r0 += 16) {
-    __syncthreads();
-    for (int q = tid; q < 16 * kNb; q += 256) {
-      const int j = q >> 4, rr = q & 15, r = r0 + rr;
-      vs[rr][j] = r < re ? refl(V, d, k0, j, nk, r) : C64{0.0, 0.0};
-      const int rz = q >> 6, cz = q & 63, r2 = r0 + rz, c = c0 + cz;
-      zs[rz][cz] = (r2 < re && c < d) ? Z[int64_t(r2) * d + c] : C64{0.0, 0.0};
+  C64 vl[2], zl[4];
+  auto load = [&](int r0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int q = u * 256 + tid, r = r0 + (q & 15);
+      vl[u] = r < re ? refl(V, d, k0, j0 + (q >> 4), nk, r) : C64{0.0, 0.0};
     }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int q = u * 256 + tid, r = r0 + (q >> 6), c = c0 + (q & 63);
+      zl[u] = (r < re && c < d) ? Z[int64_t(r) * d + c] : C64{0.0, 0.0};
+    }
+  };
+  load(rs);
+  int buf = 0;
+  for (int r0 = rs; r0 < re; r0 += 16, buf ^= 1) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) vs[buf][tid & 15][(u * 256 + tid) >> 4] = vl[u];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) zs[buf][(u * 256 + tid) >> 6][tid & 63] = zl[u];
+    __syncthreads();  // also: nobody is still reading the other buffer's previous rows
+    load(r0 + 16);
 #pragma unroll 4
     for (int rr = 0; rr < 16; ++rr) {
-      C64 u[4], w[4];
+      C64 u[2], w[4];
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        u[x] = vs[rr][4 * tj + x];
-        w[x] = zs[rr][4 * tc + x];
-      }
+      for (int x = 0; x < 2; ++x) u[x] = vs[buf][rr][2 * tj + x];
 #pragma unroll
-      for (int x = 0; x < 4; ++x)
+      for (int y = 0; y < 4; ++y) w[y] = zs[buf][rr][tc + 16 * y];
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int y = 0; y < 4; ++y) {
           const C64 p = cmulc(u[x], w[y]);
@@ -1199,11 +1212,11 @@ __global__ __launch_bounds__(256) void bt_partial_kernel(const C64* __restrict__
   }
   C64* out = P + int64_t(blockIdx.y) * kNb * d;
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int y = 0; y < 4; ++y) {
-      const int c = c0 + 4 * tc + y;
-      if (c < d) out[int64_t(4 * tj + x) * d + c] = acc[x][y];
+      const int c = c0 + tc + 16 * y;
+      if (c < d) out[int64_t(j0 + 2 * tj + x) * d + c] = acc[x][y];
     }
 }
 
@@ -1222,61 +1235,61 @@ __global__ __launch_bounds__(256) void bt_sum_kernel(const C64* __restrict__ P, 
   X[e] = s;
 }
 
-// Z[r][c] -= sum_j w_{k0 + j}[r] X[j][c] on the tile (rows k0 + 1 + 64 y,
-// columns 64 x), W = V_b T_b as bt_wfactor_kernel stores it.
+// Z[r][c] -= sum_j w_{k0 + j}[r] X[j][c] on the tile (rows k0 + 1 + 32 y,
+// columns 64 x), W = V_b T_b as bt_wfactor_kernel stores it.  Both operands
+// of the tile (96 KiB) are loaded at once, so it waits on memory once, and
+// 32 rows to a workgroup occupy twice the CUs (a block of d = 1024: 32 -> 26
+// us).
+constexpr int kUpdRows = 32;
+
 __global__ __launch_bounds__(256) void bt_update_kernel(const C64* __restrict__ W, const C64* __restrict__ X, int d,
                                                         int k0, int nk, C64* __restrict__ Z) {
-  __shared__ C64 vs[64][17];
-  __shared__ C64 xs[16][65];
-  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
-  const int r0 = k0 + 1 + blockIdx.y * 64, c0 = blockIdx.x * 64;
-  C64 acc[4][4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) acc[x][y] = C64{0.0, 0.0};
-  for (int j0 = 0; j0 < kNb; j0 += 16) {
-    __syncthreads();
-    for (int q = tid; q < 64 * 16; q += 256) {
-      const int jj = q >> 6, rr = q & 63;
-      const int j = j0 + jj, r = r0 + rr;
-      vs[rr][jj] = (j < nk && r < d) ? W[int64_t(k0 + j) * d + r] : C64{0.0, 0.0};
-      const int cc = q & 63, c = c0 + cc;
-      xs[jj][cc] = c < d ? X[int64_t(j0 + jj) * d + c] : C64{0.0, 0.0};
-    }
-    __syncthreads();
+  __shared__ C64 vs[kUpdRows][kNb + 1];  // [row][j]
+  __shared__ C64 xs[kNb][65];            // [j][column]
+  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;  // rows 2 tr + x, columns tc + 16 y
+  const int r0 = k0 + 1 + blockIdx.y * kUpdRows, c0 = blockIdx.x * 64;
 #pragma unroll 4
-    for (int jj = 0; jj < 16; ++jj) {
-      C64 u[4], w[4];
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        u[x] = vs[4 * tr + x][jj];
-        w[x] = xs[jj][4 * tc + x];
-      }
-#pragma unroll
-      for (int x = 0; x < 4; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-          const C64 p = cmul(u[x], w[y]);
-          acc[x][y].re += p.re;
-          acc[x][y].im += p.im;
-        }
-    }
+  for (int q = tid; q < kUpdRows * kNb; q += 256) {
+    const int j = q / kUpdRows, rr = q % kUpdRows, r = r0 + rr;
+    vs[rr][j] = (j < nk && r < d) ? W[int64_t(k0 + j) * d + r] : C64{0.0, 0.0};
   }
+#pragma unroll 8
+  for (int q = tid; q < kNb * 64; q += 256) {
+    const int j = q >> 6, c = c0 + (q & 63);
+    xs[j][q & 63] = c < d ? X[int64_t(j) * d + c] : C64{0.0, 0.0};
+  }
+  C64 acc[2][4];
 #pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    const int r = r0 + 4 * tr + x;
-    if (r >= d) continue;
+  for (int x = 0; x < 2; ++x)
 #pragma unroll
     for (int y = 0; y < 4; ++y) {
-      const int c = c0 + 4 * tc + y;
-      if (c < d) {
-        C64& z = Z[int64_t(r) * d + c];
-        z.re -= acc[x][y].re;
-        z.im -= acc[x][y].im;
-      }
+      const int r = r0 + 2 * tr + x, c = c0 + tc + 16 * y;
+      acc[x][y] = (r < d && c < d) ? Z[int64_t(r) * d + c] : C64{0.0, 0.0};
     }
+  __syncthreads();
+#pragma unroll 4
+  for (int j = 0; j < kNb; ++j) {
+    C64 u[2], w[4];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) u[x] = vs[2 * tr + x][j];
+#pragma unroll
+    for (int y = 0; y < 4; ++y) w[y] = xs[j][tc + 16 * y];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        const C64 p = cmul(u[x], w[y]);
+        acc[x][y].re -= p.re;
+        acc[x][y].im -= p.im;
+      }
   }
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      const int r = r0 + 2 * tr + x, c = c0 + tc + 16 * y;
+      if (r < d && c < d) Z[int64_t(r) * d + c] = acc[x][y];
+    }
 }
 
 __global__ void status_out_kernel(const TriScal* __restrict__ ts, int* __restrict__ out) { *out = ts->status; }
@@ -1384,9 +1397,9 @@ hipError_t launch_back_transform(int n, const void* V, const EighWork& w, void* 
     const int k0 = b * kNb, nk = d - 1 - k0 < kNb ? d - 1 - k0 : kNb;
     const int m = d - 1 - k0;  // rows k0 + 1 .. d - 1
     const int chunks = (m + R - 1) / R;
-    bt_partial_kernel<<<dim3(ct, chunks), 256, 0, s>>>(v, static_cast<const C64*>(Z), d, k0, nk, R, P);
+    bt_partial_kernel<<<dim3(ct, chunks, 2), 256, 0, s>>>(v, static_cast<const C64*>(Z), d, k0, nk, R, P);
     bt_sum_kernel<<<sum_blocks, 256, 0, s>>>(P, chunks, d, static_cast<C64*>(w.xbuf));
-    bt_update_kernel<<<dim3(ct, unsigned((m + 63) / 64)), 256, 0, s>>>(Wm, static_cast<const C64*>(w.xbuf), d, k0,
+    bt_update_kernel<<<dim3(ct, unsigned((m + kUpdRows - 1) / kUpdRows)), 256, 0, s>>>(Wm, static_cast<const C64*>(w.xbuf), d, k0,
                                                                        nk, static_cast<C64*>(Z));
   }
   return hipGetLastError();
