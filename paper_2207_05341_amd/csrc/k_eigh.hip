@@ -23,7 +23,7 @@
 //    count (sign changes of the leading minors of T - x I) of its block at 64
 //    points of the current interval and keeps the sub-interval that holds
 //    the eigenvalue: about 6 bits per round, full precision in 9 or 10.
-// 4. Eigenvectors by twisted factorizations, one thread per eigenvalue:
+// 4. Eigenvectors by twisted factorizations, two threads per eigenvalue:
 //    T - lambda I = L+ D+ L+^T (top down) = U- D- U-^T (bottom up); the twist
 //    index r minimises |gamma_k| = |D+_k + D-_k - (a_k - lambda)|, and the
 //    vector follows from z_r = 1 by z_k = -L+_k z_{k+1} above r and
@@ -768,110 +768,148 @@ __global__ __launch_bounds__(256) void tri_eigvals_kernel(const double* __restri
 // 4. Eigenvectors by twisted factorizations
 // ---------------------------------------------------------------------------
 
-// Thread i: column i of Z (d x d complex, zero outside the block, written
-// as real values).  Scratch: D+ at W[k d + i] and U- at W[d^2 + k d + i];
-// the diagonal and off-diagonal staged in LDS (d <= DMAX), the scratch
-// read back in batches of 8 so that its loads overlap.
+// Column i of Z (d x d complex, zero outside the block, written as real
+// values) by lane i % 64 of the two waves of a workgroup: wave 0 takes the
+// factorization from the top and the vector above the twist index, wave 1
+// the one from the bottom and the vector below it, each half of the search
+// for the index and of the scaling.  Scratch: D+ at W[k d + i] and U- at
+// W[d^2 + k d + i]; the diagonal and off-diagonal staged in LDS (d <= DMAX).
+// Bound by latency (d = 1024: 1024 dependent divisions per wave, then the
+// scratch in batches of kVecBatch whose loads overlap): d = 1024 633 -> 472 us.
+constexpr int kVecBatch = 32;
+
 template <int DMAX>
-__global__ __launch_bounds__(64) void tri_vectors_kernel(const double* __restrict__ a_g, const double* __restrict__ e_g,
-                                                         int d, const int* __restrict__ bstart,
-                                                         const int* __restrict__ bend, const TriScal* __restrict__ ts,
-                                                         const double* __restrict__ lam, double* __restrict__ W,
-                                                         C64* __restrict__ Z) {
+__global__ __launch_bounds__(128) void tri_vectors_kernel(const double* __restrict__ a_g,
+                                                          const double* __restrict__ e_g, int d,
+                                                          const int* __restrict__ bstart,
+                                                          const int* __restrict__ bend, const TriScal* __restrict__ ts,
+                                                          const double* __restrict__ lam, double* __restrict__ W,
+                                                          C64* __restrict__ Z) {
+  constexpr int B = kVecBatch;
   __shared__ double a[DMAX], e[DMAX];
-  for (int k = threadIdx.x; k < d; k += 64) {
+  __shared__ double val[2][64];  // the waves' smallest |gamma|, then their parts of the norm
+  __shared__ int idx[2][64];
+  for (int k = threadIdx.x; k < d; k += 128) {
     a[k] = a_g[k];
     e[k] = k < d - 1 ? e_g[k] : 0.0;
   }
   __syncthreads();
-  const int i = blockIdx.x * 64 + threadIdx.x;
-  if (i >= d) return;
-  const int s = bstart[i], t = bend[i];
-  if (t - s == 1) {
-    Z[int64_t(s) * d + i] = C64{1.0, 0.0};
-    return;
+  const int lane = threadIdx.x & 63, half = threadIdx.x >> 6;
+  const int i = blockIdx.x * 64 + lane;
+  int s = 0, t = 0;  // no rows: nothing to do (past the end, or a block of one)
+  double l = 0.0;
+  if (i < d) {
+    s = bstart[i];
+    t = bend[i];
+    l = lam[i];
+    if (t - s == 1) {
+      if (half == 0) Z[int64_t(s) * d + i] = C64{1.0, 0.0};
+      t = s;
+    }
   }
-  const double pivmin = ts->pivmin, l = lam[i];
-  double* Dp = W;
-  double* Um = W + int64_t(d) * d;
-  // top down: D+_{k+1} = (a_{k+1} - l) - e_k^2 / D+_k
-  double dp = a[s] - l;
-  if (fabs(dp) < pivmin) dp = -pivmin;
-  Dp[int64_t(s) * d + i] = dp;
-  for (int k = s; k < t - 1; ++k) {
-    const double ek = e[k];
-    dp = (a[k + 1] - l) - ek * (ek / dp);
-    if (fabs(dp) < pivmin) dp = -pivmin;
-    Dp[int64_t(k + 1) * d + i] = dp;
+  const double pivmin = ts->pivmin;
+  double* Dp = W + i;
+  double* Um = W + int64_t(d) * d + i;
+  C64* z_i = Z + i;
+  if (half == 0) {
+    // top down: D+_{k+1} = (a_{k+1} - l) - e_k^2 / D+_k
+    double dp = 1.0;
+    for (int k = s; k < t; ++k) {
+      dp = k == s ? a[k] - l : (a[k] - l) - e[k - 1] * (e[k - 1] / dp);
+      if (fabs(dp) < pivmin) dp = -pivmin;
+      Dp[int64_t(k) * d] = dp;
+    }
+  } else if (t > s) {
+    // bottom up: U-_k = e_k / D-_{k+1}, D-_k = (a_k - l) - U-_k e_k
+    double dm = a[t - 1] - l;
+    if (fabs(dm) < pivmin) dm = -pivmin;
+    for (int k = t - 2; k >= s; --k) {
+      const double ek = e[k], u = ek / dm;
+      Um[int64_t(k) * d] = u;
+      dm = (a[k] - l) - u * ek;
+      if (fabs(dm) < pivmin) dm = -pivmin;
+    }
   }
-  // bottom up, with the twist index; D+ read back 8 at a time
-  double dm = a[t - 1] - l;
-  if (fabs(dm) < pivmin) dm = -pivmin;
-  double best = fabs(dp);  // gamma_{t-1} = D+_{t-1}
-  int r = t - 1;
-  for (int k0 = t - 2; k0 >= s; k0 -= 8) {
-    double dpb[8];
+  __syncthreads();
+  // the twist index: gamma_k = D+_k + D-_k - (a_k - l) = D+_k - U-_k e_k,
+  // gamma_{t-1} = D+_{t-1}; the largest k of the smallest |gamma_k|
+  const int mid = s + (t - s) / 2, lo = half == 0 ? s : mid, hi = half == 0 ? mid : t;
+  double best = HUGE_VAL;
+  int r = hi - 1;
+  for (int k0 = hi - 1; k0 >= lo; k0 -= B) {
+    double dpb[B], ub[B];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) dpb[q] = k0 - q >= s ? Dp[int64_t(k0 - q) * d + i] : 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < B; ++q) {
       const int k = k0 - q;
-      if (k >= s) {
-        const double ek = e[k];
-        const double u = ek / dm;
-        Um[int64_t(k) * d + i] = u;
-        const double ak = a[k] - l;
-        dm = ak - u * ek;
-        if (fabs(dm) < pivmin) dm = -pivmin;
-        const double gam = dpb[q] + dm - ak;
-        if (fabs(gam) < best) {
-          best = fabs(gam);
+      dpb[q] = k >= lo ? Dp[int64_t(k) * d] : 0.0;
+      ub[q] = k >= lo && k < t - 1 ? Um[int64_t(k) * d] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < B; ++q) {
+      const int k = k0 - q;
+      if (k >= lo) {
+        const double gam = fabs(dpb[q] - ub[q] * e[k]);  // e[t - 1] only with ub = 0
+        if (gam < best) {
+          best = gam;
           r = k;
         }
       }
     }
   }
+  val[half][lane] = best;
+  idx[half][lane] = r;
+  __syncthreads();
+  r = val[0][lane] < val[1][lane] ? idx[0][lane] : idx[1][lane];
+  __syncthreads();  // val is used again
   // z_r = 1; z_k = -(e_k / D+_k) z_{k+1} above r, z_{k+1} = -U-_k z_k below
-  double nrm = 1.0;
-  Z[int64_t(r) * d + i] = C64{1.0, 0.0};
-  double z = 1.0;
-  for (int k0 = r - 1; k0 >= s; k0 -= 8) {
-    double b[8];
+  double nrm = 0.0, z = 1.0;
+  if (half == 0) {
+    if (t > s) {
+      z_i[int64_t(r) * d] = C64{1.0, 0.0};
+      nrm = 1.0;
+    }
+    for (int k0 = r - 1; k0 >= s && t > s; k0 -= B) {
+      double b[B];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) b[q] = k0 - q >= s ? Dp[int64_t(k0 - q) * d + i] : 1.0;
+      for (int q = 0; q < B; ++q) b[q] = k0 - q >= s ? Dp[int64_t(k0 - q) * d] : 1.0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int k = k0 - q;
-      if (k >= s) {
-        z = -(e[k] / b[q]) * z;
-        Z[int64_t(k) * d + i] = C64{z, 0.0};
-        nrm += z * z;
+      for (int q = 0; q < B; ++q) {
+        const int k = k0 - q;
+        if (k >= s) {
+          z = -(e[k] / b[q]) * z;
+          z_i[int64_t(k) * d] = C64{z, 0.0};
+          nrm += z * z;
+        }
+      }
+    }
+  } else {
+    for (int k0 = r; k0 < t - 1; k0 += B) {
+      double b[B];
+#pragma unroll
+      for (int q = 0; q < B; ++q) b[q] = k0 + q < t - 1 ? Um[int64_t(k0 + q) * d] : 0.0;
+#pragma unroll
+      for (int q = 0; q < B; ++q) {
+        const int k = k0 + q;
+        if (k < t - 1) {
+          z = -b[q] * z;
+          z_i[int64_t(k + 1) * d] = C64{z, 0.0};
+          nrm += z * z;
+        }
       }
     }
   }
-  z = 1.0;
-  for (int k0 = r; k0 < t - 1; k0 += 8) {
-    double b[8];
+  val[half][lane] = nrm;
+  __syncthreads();
+  if (t == s) return;
+  const double inv = 1.0 / sqrt(val[0][lane] + val[1][lane]);
+  const int z0 = half == 0 ? s : r + 1, z1 = half == 0 ? r + 1 : t;  // the rows this wave wrote
+  for (int k0 = z0; k0 < z1; k0 += B) {
+    double b[B];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) b[q] = k0 + q < t - 1 ? Um[int64_t(k0 + q) * d + i] : 0.0;
+    for (int q = 0; q < B; ++q) b[q] = k0 + q < z1 ? z_i[int64_t(k0 + q) * d].re : 0.0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int k = k0 + q;
-      if (k < t - 1) {
-        z = -b[q] * z;
-        Z[int64_t(k + 1) * d + i] = C64{z, 0.0};
-        nrm += z * z;
-      }
-    }
-  }
-  const double inv = 1.0 / sqrt(nrm);
-  for (int k0 = s; k0 < t; k0 += 8) {
-    double b[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) b[q] = k0 + q < t ? Z[int64_t(k0 + q) * d + i].re : 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      if (k0 + q < t) Z[int64_t(k0 + q) * d + i].re = b[q] * inv;
+    for (int q = 0; q < B; ++q)
+      if (k0 + q < z1) z_i[int64_t(k0 + q) * d].re = b[q] * inv;
   }
 }
 
@@ -1363,10 +1401,10 @@ hipError_t launch_tri_vectors(int n, const EighWork& w, const double* lam, void*
   const TriScal* ts = static_cast<const TriScal*>(w.scal);
   zero_kernel<<<unsigned((count + 255) / 256), 256, 0, s>>>(static_cast<C64*>(Z), count);
   if (d <= 2048)
-    tri_vectors_kernel<2048><<<(d + 63) / 64, 64, 0, s>>>(w.diag, w.off, d, w.bstart, w.bend, ts, lam,
+    tri_vectors_kernel<2048><<<(d + 63) / 64, 128, 0, s>>>(w.diag, w.off, d, w.bstart, w.bend, ts, lam,
                                                           static_cast<double*>(scratch), static_cast<C64*>(Z));
   else
-    tri_vectors_kernel<8192><<<(d + 63) / 64, 64, 0, s>>>(w.diag, w.off, d, w.bstart, w.bend, ts, lam,
+    tri_vectors_kernel<8192><<<(d + 63) / 64, 128, 0, s>>>(w.diag, w.off, d, w.bstart, w.bend, ts, lam,
                                                           static_cast<double*>(scratch), static_cast<C64*>(Z));
   tri_cluster_kernel<<<d, 64, 0, s>>>(w.diag, w.off, d, w.bstart, w.bend, ts, lam, static_cast<double*>(scratch),
                                       static_cast<C64*>(Z));
