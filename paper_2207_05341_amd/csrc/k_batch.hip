@@ -224,14 +224,6 @@ __device__ __forceinline__ void fast_fused_form(const BatchArgs& b, int n, int f
 // ---------------------------------------------------------------------------
 constexpr int kBX6MinDim = 128;
 
-// The thread's index, renewed: addresses made from it are computed where
-// they are used, not kept (and spilled) over the whole instance loop.
-__device__ __forceinline__ int fresh_thread() {
-  int t = threadIdx.x;
-  asm volatile("" : "+v"(t));
-  return t;
-}
-
 // Planes of X (d x d, d = 128 or 256) as a row operand, or with COLS of X^T:
 // strips of 32 rows (columns) through LDS, the next strip's loads in flight
 // while one is split.  inv: what takes the rows' scales out; with SUMS the

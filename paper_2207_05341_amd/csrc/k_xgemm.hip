@@ -579,7 +579,7 @@ __device__ __forceinline__ int64_t x6_slice_slot(const X6HerkSched& sc, int64_t 
   return (sc.sk > 1 ? sc.main : 0) + (sc.tq ? w : 2 * w + which);
 }
 __device__ __forceinline__ void x6_store_partial(float* dst, const float (&re)[2][2][16], const float (&im)[2][2][16]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int th = fresh_thread(), lane = th & 63, w = th >> 6;
   f4v* d4 = reinterpret_cast<f4v*>(dst);
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -599,7 +599,7 @@ __device__ __forceinline__ void x6_store_partial(float* dst, const float (&re)[2
 // that factor, so value * cs * rs rounds once.
 __device__ __forceinline__ void x6_scales(const XArgs& a, int64_t r0, int64_t c0, double scale, float (&rs)[2][16],
                                           float (&cs)[2]) {
-  const int lane = threadIdx.x & 63;
+  const int lane = fresh_thread() & 63;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -642,7 +642,7 @@ __device__ __forceinline__ float x6_diag(const double* sums, int r, double scale
 template <bool HERK, int X0G>
 __device__ __forceinline__ void x6_epilogue(const XArgs& a, int tr, int tc, const float (&re)[2][2][16],
                                             const float (&im)[2][2][16], double scale, char* lds) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int th = fresh_thread(), lane = th & 63, w = th >> 6;
   const int wr = w >> 1, wc = w & 1;
   const int64_t R0 = int64_t(tr) * XT, C0 = int64_t(tc) * XT;
   // row scales of this lane's values (four rows per group of four values)

@@ -83,6 +83,15 @@ __device__ __forceinline__ f4 mfma_bf16(u16x8 a, u16x8 b, f4 c) {
 
 __device__ __forceinline__ u16x8 bf16_neg(u16x8 a) { return a ^ (uint16_t)0x8000u; }
 
+// The thread's index, renewed: what is computed from it inside a long loop
+// (addresses, LDS positions) is computed where it is used, not kept in
+// registers, and spilled, from before the loop.
+__device__ __forceinline__ int fresh_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // --------------------------------------------------------------------------
 // Deterministic reductions (fixed order for a fixed launch shape).
 // --------------------------------------------------------------------------

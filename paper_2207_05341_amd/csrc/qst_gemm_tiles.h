@@ -656,7 +656,8 @@ __device__ __forceinline__ void x0_rounds(const GemmArgs& g, int64_t tr, int64_t
   constexpr int S = BM >> G;
   constexpr int TG = 1 << (2 * G);
   constexpr int NT = 1 << (2 * (G - 2));
-  const int tl = (threadIdx.x & 255) / NT, t = (threadIdx.x & 255) % NT;
+  const int thread = fresh_thread() & 255;
+  const int tl = thread / NT, t = thread % NT;
   const int64_t Rhi = tr * S + tl / S, Chi = tc * S + tl % S;
   Cx<R>* L = lds + tl * TG;
   const int bq = t & ((1 << (G - 2)) - 1), aq = t >> (G - 2);
