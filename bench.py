@@ -70,11 +70,12 @@ PEAK_HBM_GBS = 8000.0
 # record's source files, in order, the build script with its flags among
 # them); otherwise the reported traffic is null.
 TRAFFIC_X6_SOURCES = ["paper_2207_05341_amd/csrc/k_xgemm.hip", "paper_2207_05341_amd/csrc/qst_device.h",
+                      "paper_2207_05341_amd/csrc/qst_split.h", "paper_2207_05341_amd/csrc/qst_xtile.h",
                       "paper_2207_05341_amd/csrc/qst_plan.h", "paper_2207_05341_amd/build.py"]
 TRAFFIC = {
-    # N = 11, d = 2048: 221292.0 KiB fetched x 1.9998 + 32768.0 KiB written x 1.0000
-    "hemm_x6": {"bytes": 486.72e6, "sources": TRAFFIC_X6_SOURCES,
-                "sources_sha256": "d07ab688a35ba92bf5fc8a9fcf87fd584398d052e065de90a6fb1023555d4950"},
+    # N = 11, d = 2048: 98457.0 KiB fetched x 1.9998 + 32768.0 KiB written x 1.0000
+    "hemm_x6": {"bytes": 235.17e6, "sources": TRAFFIC_X6_SOURCES,
+                "sources_sha256": "506861c4dd73eaf3fba7a1c293f3cf6fad3b8c105ba5f18bb2b38bce5cf430d3"},
 }
 
 
@@ -589,11 +590,12 @@ def general_povms(qst, prec, dev, reps=10):
     (a) the Pauli-6 POVM, M_(+-j) = (I +- sigma_j)/6, on every qubit at
     N = 10 (6^10 = 60,466,176 outcomes); (b) the three Pauli bases as three
     settings of K = 2 projectors at N = 11.  One step = qst_likelihood_general
-    + qst_grad_product.  The real per-qubit factor passes are timed by the
-    library's events (scope general_factor_pass) and their achieved GB/s is
-    from algorithmic bytes: a pass over [A][m][B] reads A m_in B values and
-    writes A m_out B (the first adjoint pass also reads f; the last one of
-    each setting after the first reads its output to accumulate)."""
+    + qst_grad_product.  The real factor passes (two or three qubits each) are
+    timed by the library's events (scope general_factor_pass) and their
+    achieved GB/s is from algorithmic bytes: a pass reads and writes the
+    array before and after its qubits once (the fused last group also reads
+    f; the last pass of each setting after the first reads its output to
+    accumulate)."""
     import numpy as np
     import torch
 
@@ -638,9 +640,17 @@ def general_povms(qst, prec, dev, reps=10):
         torch.cuda.synchronize()
         _lib.profile_enable(False)
         calls, ms = _lib.profile_report(reset=True)["general_factor_pass"]
-        fwd = sum(4 ** (j - 1) * K ** (n - j) * (4 + K) for j in range(1, n + 1))
-        adj = fwd + DK + 4 ** n  # f read by the first adjoint pass; h read back by the last
-        nbytes = rb * (Sn * (fwd + adj) - 4 ** n)  # the first setting writes h without reading it
+        # groups of qubits, forward order: every group but the last is a forward
+        # and an adjoint pass; the last one, fused, reads its input and f once
+        m = 3 if K == 2 else 2
+        full, rem = [m] * (n // m), [n % m] * (n % m > 0)
+        values, done = 0, 0
+        sizes = full + rem if K <= 4 else rem + full
+        for a in sizes[:-1]:
+            values += 2 * (4 ** (n - done) * K ** done + 4 ** (n - done - a) * K ** (done + a))
+            done += a
+        values += 2 * 4 ** (n - done) * K ** done + DK
+        nbytes = rb * (Sn * values + (Sn - 1) * 4 ** n)  # a later setting adds to h, which it reads
         gbs = nbytes * reps / (ms * 1e-3) / 1e9
         out[key] = {"n_qubits": n, "K": K, "settings": Sn, "outcomes_per_setting": DK,
                     "step_ms": round(1e3 * step_s, 3), "factor_passes_ms_per_step": round(ms / reps, 3),
