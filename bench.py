@@ -75,7 +75,7 @@ TRAFFIC_X6_SOURCES = ["paper_2207_05341_amd/csrc/k_xgemm.hip", "paper_2207_05341
 TRAFFIC = {
     # N = 11, d = 2048: 98457.0 KiB fetched x 1.9998 + 32768.0 KiB written x 1.0000
     "hemm_x6": {"bytes": 235.17e6, "sources": TRAFFIC_X6_SOURCES,
-                "sources_sha256": "506861c4dd73eaf3fba7a1c293f3cf6fad3b8c105ba5f18bb2b38bce5cf430d3"},
+                "sources_sha256": "7741f5804552b9859d2f8581c883117d5b8ac1ceeb0754f5af2875fbff072dcf"},
 }
 
 

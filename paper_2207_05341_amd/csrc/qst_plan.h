@@ -34,8 +34,9 @@ inline bool x6_small_tiles(int n) { return n <= 10; }
 // split products take over from the FP32 MFMA products: at N = 10 a
 // likelihood and gradient takes 124 us against 153 us, at N = 11 356 against
 // 673, at N = 12 2320 against 4932, with smaller errors at each.  Below,
-// d = 512 gives 16 tiles of 128 x 128 for 256 compute units, and QST_F32's
-// gradient product has no workspace.
+// QST_F32's gradient product takes no workspace, which its callers may rely
+// on, so there is no place for the planes (N = 9 with them, as QST_F32X6 in
+// one call: 66 us against 100; N = 8: 59 against 64; N = 7: 49 against 43).
 constexpr int kX6F32MinQubits = 10;
 inline bool use_x6(qst_prec p, int n) {
   return (p == QST_F32X6 && (int64_t(1) << n) >= kX6Tile) || (p == QST_F32 && n >= kX6F32MinQubits);
