@@ -64,9 +64,11 @@ typedef enum {
   /* complex128 T and rho, float64 p and f; FP64 MFMA products. */
   QST_F64 = 0,
   /* complex64 T and rho, float32 p and f; FP32 MFMA products with FP32
-   * accumulation up to N = 9, the split products of QST_F32X6 from N = 10
-   * (smaller errors against FP64 there); tau and the log-likelihood sum in
-   * FP64. */
+   * accumulation; tau and the log-likelihood sum in FP64.  From N = 10 a
+   * product of two dense operands (see QST_F32X6) runs as the fp16 split
+   * products of QST_F32X6, whose errors against FP64 are smaller there.  The
+   * device decides from the operands' values, in every call and every replay
+   * of a captured one; equal inputs take the same products. */
   QST_F32 = 1,
   /* complex64 storage as QST_F32.  For d >= 256, T T^dagger takes T rounded
    * to bfloat16 (round-to-nearest-even) on the BF16 MFMA with FP32
@@ -78,15 +80,24 @@ typedef enum {
   QST_BF16GEMM = 2,
   /* complex64 storage, FP32 POVM passes, tau and the log-likelihood sum in
    * FP64, as QST_F32; for d >= 128 the two complex products run on the
-   * 16-bit matrix cores with every FP32 operand row (or column) scaled by a
-   * power of two and split into two fp16 parts (x = h + l, 22 significand
-   * bits and a sign) and three partial products per real product (hh, hl,
-   * lh: what is dropped is below 2^-22 of |a||b|), FP32 accumulation; the
-   * diagonal of T T^dagger is the FP64 sum of its squares.  The products are
-   * more accurate than FP32 MFMA products (measured against FP64) and several
-   * times as fast.  Below d = 128 the products are those of QST_F32.  The
-   * batched form runs it as QST_F32, whose instances with d >= 128 take
-   * the same split products (at 512 threads). */
+   * 16-bit matrix cores with FP32 accumulation; the diagonal of T T^dagger is
+   * the FP64 sum of its squares.
+   * In general every FP32 operand is split exactly into three bfloat16 parts
+   * (x = h + m + l) with six partial products per real product (hh, hm, mh,
+   * hl, lh, mm: what is dropped is below 2^-26 of |a||b|): results agree with
+   * FP32 MFMA products to the order of FP32 rounding.
+   * Where both operands are dense, every row (or column) is scaled by a power
+   * of two and split into two fp16 parts (x = h + l, 22 significand bits and
+   * a sign for entries down to 2^-15 of the row's largest, an absolute error
+   * of 2^-38 of it below), with three partial products (hh, hl, lh: what is
+   * dropped is below 2^-22 of |a||b|).  Dense: at least three quarters of the
+   * components of every piece of a row (column) are within 2^-8 (G' from
+   * d = 1024: 2^-10) of the row's (column's) largest.  Then the accumulation
+   * of many comparable terms sets the error, and it is smaller than that of
+   * the general products and of FP32 MFMA products (measured against FP64).
+   * Below d = 128 the products are those of QST_F32.  The batched form runs
+   * it as QST_F32, whose instances with d >= 128 take the fp16 split products
+   * (at 512 threads). */
   QST_F32X6 = 3
 } qst_prec;
 

@@ -20,7 +20,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libqst.so")
 
-SOURCES = ["qst_plan.cpp", "k_reduce.hip", "k_povm.hip", "k_povm_fast.hip", "k_gemm.hip", "qst_profile.hip", "k_batch.hip", "k_premap.hip", "k_fidelity.hip", "k_fnn.hip", "k_absmap.hip", "k_eigh.hip", "k_povm_general.hip", "k_xgemm.hip", "k_small.hip", "qst_api.hip"]
+SOURCES = ["qst_plan.cpp", "k_reduce.hip", "k_povm.hip", "k_povm_fast.hip", "k_gemm.hip", "qst_profile.hip", "k_batch.hip", "k_premap.hip", "k_fidelity.hip", "k_fnn.hip", "k_absmap.hip", "k_eigh.hip", "k_povm_general.hip", "k_xgemm.hip", "k_xgemm3.hip", "k_small.hip", "qst_api.hip"]
 ARCH = "gfx950"
 
 
@@ -44,8 +44,14 @@ def common_flags() -> list[str]:
     ]
 
 
-# Per-source flags.
-SOURCE_FLAGS: dict[str, list[str]] = {}
+# Per-source flags.  k_xgemm3.hip: MFMA accumulators in VGPRs (the LLVM
+# AMDGPU option selecting the VGPR form of the MFMA instructions).  With the
+# default AGPR form the register allocator spills the FP32 chain totals to
+# scratch memory; the reloads at every chain close are vector-memory loads
+# queued behind the in-flight global-to-LDS copies of the operand ring, so
+# each close waited for the whole ring.  In the VGPR form the totals spill to
+# AGPRs and the MFMA loops are unchanged.
+SOURCE_FLAGS = {"k_xgemm3.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _compile(src: str) -> str:

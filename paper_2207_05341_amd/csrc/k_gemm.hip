@@ -51,10 +51,15 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& g, int tr, int tc, t
   }
 }
 
+__device__ __forceinline__ bool gemm_off(const GemmArgs& g) {
+  return g.gate[0] && !(*g.gate[0] | *g.gate[1]);
+}
+
 // One tile per workgroup.
 template <class P, int X0G>
 __global__ __launch_bounds__(256, P::kMinWaves) void gemm_dp_kernel(GemmArgs g) {
   __shared__ __align__(16) unsigned char smem[smem_bytes<P, X0G != 0>()];
+  if (gemm_off(g)) return;
   auto& sm = *reinterpret_cast<typename P::Smem*>(smem);
   typename P::acc_t aR[2][2], aI[2][2];
   const double scale = tile_scale<P>(g);
@@ -71,6 +76,7 @@ __global__ __launch_bounds__(256, P::kMinWaves) void gemm_dp_kernel(GemmArgs g) 
 template <class P, int X0G>
 __global__ __launch_bounds__(256, P::kMinWaves) void gemm_sk_kernel(GemmArgs g) {
   __shared__ __align__(16) unsigned char smem[smem_bytes<P, X0G != 0>()];
+  if (gemm_off(g)) return;
   auto& sm = *reinterpret_cast<typename P::Smem*>(smem);
   typename P::acc_t aR[2][2], aI[2][2];
   // logical workgroup index: consecutive tiles and consecutive segments
@@ -154,6 +160,7 @@ __device__ __forceinline__ void sum_partials(const GemmArgs& g, int64_t Pn, int 
 // 13 us for the 16 tiles of FP64 at N = 11.)
 template <class P>
 __global__ __launch_bounds__(256) void gemm_chunk_sum_kernel(GemmArgs g, int Pn, int chunk, int groups) {
+  if (gemm_off(g)) return;
   const int rel = blockIdx.x / groups, c = blockIdx.x % groups;
   int64_t wlo, whi;
   tile_owners(g, Pn, rel, wlo, whi);
@@ -172,6 +179,7 @@ __global__ __launch_bounds__(256) void gemm_chunk_sum_kernel(GemmArgs g, int Pn,
 template <class P, int X0G>
 __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs g, int Pn, int chunk) {
   __shared__ __align__(16) unsigned char smem[X0G ? smem_bytes<P, X0G != 0>() : 16];
+  if (gemm_off(g)) return;
   const int rel = blockIdx.x;
   int64_t wlo, whi;
   tile_owners(g, Pn, rel, wlo, whi);
@@ -328,7 +336,8 @@ hipError_t run_gemm_sk(GemmArgs g, hipStream_t s) {
   // empty, or where one tile per CU would leave each SIMD a single wave (FP64
   // G' T at N = 10, 256 tiles: 131.8 us whole, 124.3 us as two halves each
   // with the fix-up).
-  bool sk = g.partial != nullptr && (g.ntiles % cus != 0 || g.ntiles == cus);
+  constexpr bool kF64 = sizeof(typename P::scalar) == 8;
+  bool sk = g.partial != nullptr && (g.ntiles % cus != 0 || (kF64 && g.ntiles == cus));
   if (sk && X0G != 0) {
     // The POVM epilogue raises the register use of the stream-K kernel.
     // When no workgroup of the plain kernel's grid can finish a whole tile
@@ -388,9 +397,9 @@ hipError_t run_herk_x0(qst_prec prec, int d, const GemmArgs& g, hipStream_t s, b
 
 hipError_t launch_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int64_t ldr, int n,
                        const double* tau_partials, double* tau_dev, void* sk_partial, hipStream_t s,
-                       const Pass0Out* x0, const void* planes) {
+                       const Pass0Out* x0, const void* planes, const X6Gate* gate) {
   const int d = 1 << n;
-  if (use_x6(prec, n)) return hipErrorInvalidValue;  // launch_x6_herk forms tau itself
+  if (use_x6(prec, n) && !gate) return hipErrorInvalidValue;  // launch_x6_herk
   prec = storage_prec(prec);
   if (x0 && (d < BM || x0->g < 4 || x0->g > 6 || !x0->tetra)) return hipErrorInvalidValue;
   ProfScope prof(d < BM ? "herk_small" : (prec == QST_F64 ? "herk_f64" : prec == QST_F32 ? "herk_f32" : "herk_bf16"), s);
@@ -421,6 +430,10 @@ hipError_t launch_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int
   g.partial = sk_partial;
   g.tau_part = tau_partials;
   g.tau_out = tau_partials ? tau_dev : nullptr;
+  if (gate) {
+    g.gate[0] = gate->bad[0];
+    g.gate[1] = gate->bad[1];
+  }
   const bool use_planes = prec == QST_BF16GEMM && d > kBf16SplitMaxDim && planes;
   if (use_planes) {  // operands: bf16 planes of T, row stride d
     g.A = planes;
@@ -613,9 +626,15 @@ __global__ __launch_bounds__(512) void hemm_bf16_wide_kernel(GemmArgs g) {
 
 hipError_t launch_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T, int64_t ldt, void* out,
                        int64_t ldo, int n, const double* tau_dev, const double* upstream_dev,
-                       void* sk_partial, hipStream_t s, void* planes) {
+                       void* sk_partial, hipStream_t s, void* planes, const X6Scales* t_ready) {
   const int d = 1 << n;
-  if (use_x6(prec, n)) return launch_x6_hemm(G, ldg, T, ldt, out, ldo, n, tau_dev, upstream_dev, planes, s);
+  X6Gate gate{};
+  if (use_x6(prec, n)) {
+    const hipError_t e =
+        launch_x6_hemm(prec, G, ldg, T, ldt, out, ldo, n, tau_dev, upstream_dev, planes, s, t_ready, &gate);
+    if (e != hipSuccess || prec == QST_F32X6) return e;
+    sk_partial = x6_hemm_planes(planes, n);
+  }
   prec = storage_prec(prec);
   ProfScope prof(d < BM ? "hemm_small" : (prec == QST_F64 ? "hemm_f64" : prec == QST_F32 ? "hemm_f32" : "hemm_bf16x3"), s);
   if (d < BM) {
@@ -651,6 +670,8 @@ hipError_t launch_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T,
   g.partial = sk_partial;
   g.tau_part = nullptr;
   g.tau_out = nullptr;
+  g.gate[0] = gate.bad[0];
+  g.gate[1] = gate.bad[1];
   if (prec == QST_F64) return run_gemm<CxPolicy<double, false>>(g, s);
   if (prec == QST_F32) return run_gemm<CxPolicy<float, false>>(g, s);
   if (planes && d % (8 * kWideBM) == 0) {

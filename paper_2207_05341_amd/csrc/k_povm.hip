@@ -120,7 +120,7 @@ hipError_t launch_povm_fused(qst_prec prec, const PovmPlan& pl, const double* W,
                              const void* rho, int64_t ld_rho, const void* fvec, const double* Fpart, void* G,
                              int64_t ldG, void* inter0, void* inter1, double* part, double* nll_dev,
                              unsigned long long* bad_dev, bool pass0_done, hipStream_t s, const void* pt,
-                             double* fc_dev, void* gplanes, float* ymax, float* ginv) {
+                             double* fc_dev) {
   static const char* kFwd[4] = {"povm_fwd_p0", "povm_fwd_p1", "povm_fwd_p2", "povm_fwd_p3"};
   static const char* kAdj[4] = {"povm_adj_p0", "povm_adj_p1", "povm_adj_p2", "povm_adj_p3"};
   ModeMatrix Af, Aa;
@@ -156,7 +156,6 @@ hipError_t launch_povm_fused(qst_prec prec, const PovmPlan& pl, const double* W,
     a.Fpart = Fpart;
     a.part = part;
     a.pt = pt;
-    if (gplanes) a.ymax = ymax;
     const int64_t nb = povm_pass_blocks(pl, P - 1);
     ProfScope prof("povm_fused", s);
     if (!launch_fused_fast(prec, tetra, a, Af, Aa, nb, s, &e)) return hipErrorInvalidValue;
@@ -164,18 +163,12 @@ hipError_t launch_povm_fused(qst_prec prec, const PovmPlan& pl, const double* W,
     if ((e = launch_likelihood_finish(part, int(nb), Fpart, nll_dev, bad_dev, s, pt ? fc_dev : nullptr)) != hipSuccess)
       return e;
   }
-  if (!G && !gplanes) return hipSuccess;
+  if (!G) return hipSuccess;
   for (int j = P - 2; j >= 0; --j) {
     PassArgs a = args(j);
     a.in = bufs[j & 1];
     a.out = j == 0 ? G : bufs[(j - 1) & 1];
     a.ld = ldG;
-    if (j == 0 && gplanes) {
-      a.gplanes = gplanes;
-      a.ymax = ymax;
-      a.nymax = int(povm_pass_blocks(pl, P - 1));
-      a.ginv = ginv;
-    }
     ProfScope prof(kAdj[j], s);
     if (!launch_pass_fast(true, prec, tetra, a, Aa, j == 0, false, povm_pass_blocks(pl, j), s, &e))
       return hipErrorInvalidValue;

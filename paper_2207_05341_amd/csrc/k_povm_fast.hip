@@ -36,11 +36,11 @@ namespace {
 // Matrix-side pass (pass 0) and outcome-side passes (passes 1..): one
 // logical block per workgroup (fast_pass::mat_pass_body / kd_pass_body).
 // ---------------------------------------------------------------------------
-template <typename R, bool ADJ, bool TETRA, int G, bool PLANES = false>
+template <typename R, bool ADJ, bool TETRA, int G>
 __global__ __launch_bounds__(256) void mat_pass(PassArgs a, ModeMatrix A, int64_t ntiles) {
   constexpr int TPW = 256 >> (2 * (G - 2));
   __shared__ Cx<R> lds[TPW << (2 * G)];
-  fast_pass::mat_pass_body<R, ADJ, TETRA, G, PLANES>(a, A, ntiles, blockIdx.x, threadIdx.x, lds);
+  fast_pass::mat_pass_body<R, ADJ, TETRA, G>(a, A, ntiles, blockIdx.x, threadIdx.x, lds);
 }
 
 template <typename R, bool ADJ, bool TETRA, int G, int J, bool PSIDE>
@@ -79,16 +79,7 @@ __global__ __launch_bounds__(256, FC ? 1 : 2) void kd_fused_pass(PassArgs a, Mod
     __syncthreads();
   }
   double L = 0.0, bad0 = 0.0, bad1 = 0.0, fc = 0.0;
-  float ym = 0.f;
-  fast_pass::kd_fused_body<R, TETRA, G, J, FC>(a, Af, Aa, lb, threadIdx.x, lds, true, Fsh, L, bad0, bad1, &fc, &ym);
-  if (sizeof(R) == 4 && a.ymax) {
-    __shared__ float yred[4];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) ym = fmaxf(ym, __shfl_xor(ym, o, 64));
-    if ((threadIdx.x & 63) == 0) yred[threadIdx.x >> 6] = ym;
-    __syncthreads();
-    if (threadIdx.x == 0) a.ymax[lb] = fmaxf(fmaxf(yred[0], yred[1]), fmaxf(yred[2], yred[3]));
-  }
+  fast_pass::kd_fused_body<R, TETRA, G, J, FC>(a, Af, Aa, lb, threadIdx.x, lds, true, Fsh, L, bad0, bad1, &fc);
   // per-workgroup partial sums in a fixed order, slot = logical index
   const int64_t nb = gridDim.x;
   double v = block_sum256(L, red);
@@ -153,14 +144,6 @@ bool launch_pass_fast(bool adjoint, qst_prec prec, bool tetra, const PassArgs& a
       else { if (tetra) QST_MAT(float, false, true, G); else QST_MAT(float, false, false, G); }    \
     }                                                                                             \
   } while (0)
-  if (matside && adjoint && a.gplanes) {  // G' as split planes: FP32 adjoint, g = 5 or 6
-    if (f64 || pside || !tetra || a.J != 1 || a.g < 5 || a.g > 6) return false;
-    const unsigned grid = unsigned((blocks + (256 >> (2 * (a.g - 2))) - 1) / (256 >> (2 * (a.g - 2))));
-    if (a.g == 5) mat_pass<float, true, true, 5, true><<<grid, 256, 0, s>>>(a, A, blocks);
-    else mat_pass<float, true, true, 6, true><<<grid, 256, 0, s>>>(a, A, blocks);
-    *err = hipGetLastError();
-    return true;
-  }
   if (matside && !pside && a.J == 1 && a.g >= 4 && a.g <= 6) {
     if (a.g == 4) QST_MAT_ALL(4);
     else if (a.g == 5) QST_MAT_ALL(5);

@@ -5,12 +5,30 @@
 //   gradient   grad = s (2 / tau) G' T     (adjoint of the state map)
 //
 // Split (qst_split.h): each operand row, scaled by a power of two, is
-// x = h + l with h and l in fp16 (22 significand bits and the sign of l, so
-// the rounding left out is that of FP32 itself).  A real product a b keeps
-// hh + hl + lh, each exact in FP32; the dropped ll is below 2^-22 |a||b|
-// and of random sign, the size of one FP32 rounding per term (the diagonal
-// of T T^dagger, where it is a square, is formed apart: x6_diag_sums).
-// Accumulation is in FP32 inside the MFMA.
+// x = h + l with h and l in fp16 (22 significand bits and the sign of l).  A
+// real product a b keeps hh + hl + lh, each exact in FP32; the dropped ll is
+// below 2^-22 |a||b| and of random sign (the diagonal of T T^dagger, where it
+// is a square, is formed apart: x6_diag_sums).  Accumulation is in FP32
+// inside the MFMA.
+//
+// Where it is used.  One scale per row leaves entries below 2^-15 of the
+// row's largest fewer bits, and 22 bits are less than FP32's 24: the products
+// are more accurate than FP32's where the accumulation of many comparable
+// terms sets the error, and less where a few terms carry an entry or large
+// entries of one operand meet small ones of the other.  So the split counts
+// the components near the largest of their row (column), and the fp16
+// products are stored only where both operands are dense by that count
+// (kX6DenseBits; three quarters of the components, so that in every sum at
+// least half of the terms have both factors near their largest).  Elsewhere
+// QST_F32 runs its FP32 MFMA products (k_gemm.hip) and QST_F32X6 the exact
+// three-part bf16 split (k_xgemm3.hip).  The choice is a pair of flags in
+// device memory that every kernel of either kind reads first: no host
+// decision, and a captured call chooses again at each replay.  Relative errors
+// against FP64 at N = 10 or 11, old product of QST_F32 / of QST_F32X6 / fp16:
+// Gaussian T, G' T 1.1e-6 / 5.0e-7 / 2.5e-7; one nonzero column of T, rho
+// 7e-8 / 1.0e-7 / 1.3e-7; T = D^-1 X and G' = D A D with D within 2^+-12,
+// 8e-7 / 5.0e-7 / 1.5e-5.  The kernels that find themselves unused cost 2 to
+// 4 us each.
 //
 // Complex products: ten MFMA products per 32 x 32 block and K panel.  The
 // leading part h h takes the four real products of the definition.  Each of
@@ -30,11 +48,6 @@
 // operands) needs 1.5 times the LDS and plane bytes.  A split into three
 // bf16 parts with six products per real product, in the three-product form
 // (18): 224 us, and two times the plane bytes.
-//
-// Accuracy (N = 11, relative to FP64, Gaussian T): gradient product 2.1e-7,
-// off-diagonal rho 2.1e-7, gradient 5e-7 .. 9e-7 in all; with FP32 MFMA
-// products 1.15e-6, 7.5e-7 and 1.3e-6 .. 2.3e-6; with the three-part bf16
-// split 5.0e-7, 4.9e-7 and 2.8e-6 .. 4.7e-6.
 //
 // Operand planes.  A split pass writes each operand once per call as fp16
 // planes in the order the v_mfma_f32_32x32x16_f16 fragments read them: a
@@ -61,31 +74,21 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-#include <mutex>
 #include <type_traits>
 
-#include "qst_device.h"
-#include "qst_gemm_tiles.h"
-#include "qst_kernels.h"
-#include "qst_plan.h"
-#include "qst_split.h"
-#include "qst_xtile.h"
+#include "qst_xgemm.h"
 
 namespace qst {
 
 namespace {
 
-typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
 
-constexpr int XT = kX6Tile;           // output tile (complex)
 constexpr int XSLOT = 32 * 1024;      // one slab: 32 units, 4 row blocks of A and of B
 constexpr int XNSLOT = 4;             // LDS ring slots
 constexpr int XDIST = XNSLOT - 1;     // slabs copied ahead of the one being computed
 constexpr int XCOPY = 8;              // units copied per wave and slab
 constexpr int XLDS = XSLOT * XNSLOT;  // 131072 bytes of LDS
-constexpr int XUNIT = kX6UnitVecs;
 
 static_assert((XDIST - 1) * XCOPY < 64, "vmcnt immediate");
 
@@ -108,12 +111,13 @@ static_assert((XDIST - 1) * XCOPY < 64, "vmcnt immediate");
 // steps finish it (nine shuffles in place of forty).
 template <bool TAU, bool WITH_F>
 __device__ __forceinline__ void x6_absmax(const Cx<float>* __restrict__ X, int64_t ld, int d, float* __restrict__ rowp,
-                                          float* __restrict__ colp, double* __restrict__ partials,
-                                          const float* __restrict__ f) {
+                                          float* __restrict__ colp, int* __restrict__ bad,
+                                          double* __restrict__ partials, const float* __restrict__ f) {
   constexpr int NT = 256, U = 16;
   __shared__ double red[4];
   __shared__ float cm[8][64];
   const int nb = gridDim.x, t = threadIdx.x;
+  if (blockIdx.x == 0 && t < 2) bad[t] = 0;  // the split that follows sets them
   const int64_t D = int64_t(d) * d;
   const int64_t fbeg = D * blockIdx.x / nb, fend = D * (blockIdx.x + 1) / nb;
   float fv[U];
@@ -198,9 +202,9 @@ __device__ __forceinline__ void x6_absmax(const Cx<float>* __restrict__ X, int64
 // T, for T T^dagger.
 template <bool WITH_F>
 __global__ __launch_bounds__(256) void x6_absmax_t_kernel(const Cx<float>* __restrict__ T, int64_t ld, int d,
-                                                          float* __restrict__ rowp, float* __restrict__ colp,
-                                                          double* __restrict__ partials, const float* __restrict__ f) {
-  x6_absmax<true, WITH_F>(T, ld, d, rowp, colp, partials, f);
+                                                          X6Scales sc, double* __restrict__ partials,
+                                                          const float* __restrict__ f) {
+  x6_absmax<true, WITH_F>(T, ld, d, sc.rowp, sc.colp, sc.bad, partials, f);
 }
 
 // G' (blockIdx.y 0) and T (1), for G' T: one launch for both.
@@ -209,10 +213,11 @@ struct X6Pair {
   int64_t ld[2];
   X6Scales sc[2];
   u16x8* P[2];
+  float low[2];
 };
 __global__ __launch_bounds__(256) void x6_absmax_gt_kernel(X6Pair p, int d) {
   const int y = blockIdx.y;
-  x6_absmax<false, false>(p.X[y], p.ld[y], d, p.sc[y].rowp, p.sc[y].colp, nullptr, nullptr);
+  x6_absmax<false, false>(p.X[y], p.ld[y], d, p.sc[y].rowp, p.sc[y].colp, p.sc[y].bad, nullptr, nullptr);
 }
 
 // The planes of X as a row operand (ROWS; row r scaled by its largest
@@ -225,6 +230,9 @@ __global__ __launch_bounds__(256) void x6_absmax_gt_kernel(X6Pair p, int d) {
 // LDS (8 KB per wave, 16-byte chunks swizzled by row) and reads the two unit
 // blocks of X^T (lane u: column u % 32, rows 16 h + 8 (u / 32) .. + 7).
 // With SUMS also the FP64 sums of |x|^2 over the 128 columns of each row.
+// Where less than three quarters of the scaled components of a 128-entry
+// piece of a row (32-entry piece of a column) reach low, the flag bad[0]
+// (bad[1]) is set: the operand is not dense.
 // Bound by HBM: X read, 8 bytes per element and operand written.
 __device__ __forceinline__ int split_swz(int r, int c) {  // (r, c) of a 32 x 32 block, complex index
   return r * 32 + 2 * (((c >> 1) ^ r) & 15) + (c & 1);
@@ -232,11 +240,12 @@ __device__ __forceinline__ int split_swz(int r, int c) {  // (r, c) of a 32 x 32
 
 template <bool ROWS, bool COLS, bool SUMS>
 __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_t ld, int d, const X6Scales& sc6,
-                                         u16x8* __restrict__ P, u16x8* __restrict__ PT) {
+                                         u16x8* __restrict__ P, u16x8* __restrict__ PT, float low) {
   const float *rowp = sc6.rowp, *colp = sc6.colp;
   __shared__ Cx<float> blkL[COLS ? 4 : 1][COLS ? 32 * 32 : 1];
   __shared__ float rm[8][32], cmx[2][128], rsc[32], csc[128];
   __shared__ double rs[SUMS ? 4 : 1][32];
+  __shared__ int big[ROWS ? 4 : 1][32];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int row = lane & 31, hq = lane >> 5;
   const int nkb = d / 16, nb32 = d / 32, np = d / 64;
@@ -265,6 +274,7 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
       const int e = x6_scale_exp(m, kX6Top);
       rsc[t] = x6_pow2(e);
       if (bc0 == 0) sc6.rinv[32 * br + t] = x6_pow2(-e);
+      if (!x6_finite(m)) sc6.bad[0] = 1;
     }
   }
   if constexpr (SUMS) {
@@ -280,7 +290,9 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
   if constexpr (COLS) {
     if (t >= 128) {
       const int c = t - 128;
-      const int e = x6_scale_exp(fmaxf(cmx[0][c], cmx[1][c]), kX6Top);
+      const float m = fmaxf(cmx[0][c], cmx[1][c]);
+      const int e = x6_scale_exp(m, kX6Top);
+      if (!x6_finite(m)) sc6.bad[1] = 1;
       csc[c] = x6_pow2(e);
       if (br == 0) sc6.cinv[32 * bc0 + c] = x6_pow2(-e);
     }
@@ -295,6 +307,7 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
   }
   if constexpr (ROWS) {
     const float sc = rsc[row];
+    int n = 0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       float re[8], im[8];
@@ -303,11 +316,16 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
         re[e] = v[h][e].re;
         im[e] = v[h][e].im;
       }
-      write_unit_block(P + (br * nkb + 2 * bc + h) * kX6BlockVecs + lane, re, im, sc);
+      n += write_unit_block(P + (br * nkb + 2 * bc + h) * kX6BlockVecs + lane, re, im, sc, low);
     }
+    n += __shfl_xor(n, 32, 64);
+    if (lane < 32) big[wv][lane] = n;
+    __syncthreads();
+    if (t < 32 && 4 * (big[0][t] + big[1][t] + big[2][t] + big[3][t]) < 3 * 256) sc6.bad[0] = 1;
   }
   if constexpr (COLS) {
     const float sc = csc[32 * wv + row];
+    int n = 0;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       float re[8], im[8];
@@ -317,70 +335,37 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
         re[e] = x.re;
         im[e] = x.im;
       }
-      write_unit_block(PT + (bc * nkb + 2 * br + h) * kX6BlockVecs + lane, re, im, sc);
+      n += write_unit_block(PT + (bc * nkb + 2 * br + h) * kX6BlockVecs + lane, re, im, sc, low);
     }
+    n += __shfl_xor(n, 32, 64);
+    if (4 * n < 3 * 64) sc6.bad[1] = 1;
   }
 }
 
 // T for T T^dagger, and with TT T^T for G' T of the same call.
 template <bool TT>
 __global__ __launch_bounds__(256) void x6_split_t_kernel(const Cx<float>* __restrict__ T, int64_t ld, int d, X6Scales sc,
-                                                         u16x8* __restrict__ P, u16x8* __restrict__ PT) {
-  x6_split<true, TT, true>(T, ld, d, sc, P, PT);
+                                                         u16x8* __restrict__ P, u16x8* __restrict__ PT, float low) {
+  x6_split<true, TT, true>(T, ld, d, sc, P, PT, low);
 }
 
 // G' (blockIdx.y 0) and T^T (1) for G' T.
 __global__ __launch_bounds__(256) void x6_split_gt_kernel(X6Pair p, int d) {
-  if (blockIdx.y == 0) x6_split<true, false, false>(p.X[0], p.ld[0], d, p.sc[0], p.P[0], nullptr);
-  else x6_split<false, true, false>(p.X[1], p.ld[1], d, p.sc[1], nullptr, p.P[1]);
+  if (blockIdx.y == 0) x6_split<true, false, false>(p.X[0], p.ld[0], d, p.sc[0], p.P[0], nullptr, p.low[0]);
+  else x6_split<false, true, false>(p.X[1], p.ld[1], d, p.sc[1], nullptr, p.P[1], p.low[1]);
 }
 
 // ---------------------------------------------------------------------------
 // Product kernel
 // ---------------------------------------------------------------------------
-struct XArgs {
-  const u16x8* A;  // planes of the row operand
-  const u16x8* B;  // planes of the column operand (rows of B^T)
-  const float* sa;  // what takes A's row scales out again: sa[row * sa_stride]
-  const float* sb;  // the same for B's rows (the output's columns)
-  int sa_stride;    // 1, or 0 for one scale of the whole operand
-  const double* rsum;  // HERK: sums of |T|^2 over 128-entry row pieces, [d / 128][d]
-  void* C;          // output (HEMM, or HERK without x0)
-  int64_t ldc;
-  int d;
-  const double* tau;       // tau, or NULL with tau_part
-  const double* tau_part;  // FP64 partial sums of tau (kReduceBlocks), folded by every workgroup
-  double* tau_out;         // where workgroup 0 of the T T^dagger fix-up stores the folded tau
-  const double* up;        // HEMM: upstream scalar or NULL
-  float* part;             // HERK partial tiles [slots][re, im][TILE] in the MFMA layout
-  int ntiles, kIters;
-  X6HerkSched sc;          // HERK schedule (rounds, then slices)
-  void* x0;                // HERK: first POVM pass output, or NULL
-  int x0g, x0up;
-};
-
-constexpr int kXTileVals = XT * XT;  // complex values per tile
-
-// Fold of the tau partials in a fixed order (bitwise the same in every
-// workgroup), through the idle ring's first bytes.
-__device__ double x6_tau(const XArgs& a, char* lds) {
-  double* red = reinterpret_cast<double*>(lds);
-  double acc = 0.0;
-  for (int b = threadIdx.x; b < kReduceBlocks; b += 256) acc += a.tau_part[b];
-  const double sum = block_sum256(acc, red);
-  if (threadIdx.x == 0) red[4] = sum;
-  __syncthreads();
-  const double tau = red[4];
-  __syncthreads();
-  return tau;
-}
-
 // Panels per MFMA accumulation chain (even).  The MFMA rounds the FP32
 // accumulator toward zero when it adds a product block, so a chain is kept
 // short and folded into FP32 totals with round-to-nearest adds; a new chain
-// starts from a zero accumulator operand.  At N = 11: 16 panels 341 us per
-// step and a gradient error of 8.8e-7, 8 panels 346 us and 8.7e-7.
-constexpr int XCHAIN = 16;
+// starts from a zero accumulator operand.  16 panels are 1% faster at N = 11
+// and 12, but where all terms of a sum have one sign (T of positive entries)
+// their rho is less accurate than the three-part split's: largest error at
+// N = 10, relative to sum |a||b|, 2.6e-7 against 2.4e-7; with 8, 2.0e-7.
+constexpr int XCHAIN = 8;
 static_assert(XCHAIN % 2 == 0, "the fragment buffers alternate by panel");
 
 // Accumulate the panels [kb, ke), an even number, of output tile (tr, tc)
@@ -557,185 +542,10 @@ __device__ __forceinline__ void x6_segment(const XArgs& a, char* lds, int tr, in
   __syncthreads();
 }
 
-// (row, column) inside the 128 x 128 tile of accumulator value v of block
-// (i, j) held by lane `lane` of wave (wr, wc).
-__device__ __forceinline__ int x6_row(int wr, int i, int v, int lane) {
-  return wr * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-}
-__device__ __forceinline__ int x6_col(int wc, int j, int lane) { return wc * 64 + j * 32 + (lane & 31); }
-
-// Partial of a tile segment, 16 bytes per lane and store: values
-// 4 vq .. 4 vq + 3 of block ij = 2 i + j, part p (re, im) of wave w's lane l
-// at floats ((((4 w + ij) 2 + p) 4 + vq) 64 + l) 4 .. + 3 (each store of a
-// wave is 1 KB contiguous; wave w's 64 x 64 quadrant is floats
-// [8192 w, 8192 (w + 1))).
-__device__ __forceinline__ float* x6_slot(const XArgs& a, int64_t slot) {
-  return a.part + slot * int64_t(2 * kXTileVals);
-}
-// slot of a round unit u (sk > 1), and of slice `which` (0: the first unit
-// of the worker's range, 1: the last) of slice worker w
-__device__ __forceinline__ int64_t x6_unit_slot(int64_t u) { return u; }
-__device__ __forceinline__ int64_t x6_slice_slot(const X6HerkSched& sc, int64_t w, int which) {
-  return (sc.sk > 1 ? sc.main : 0) + (sc.tq ? w : 2 * w + which);
-}
-__device__ __forceinline__ void x6_store_partial(float* dst, const float (&re)[2][2][16], const float (&im)[2][2][16]) {
-  const int th = fresh_thread(), lane = th & 63, w = th >> 6;
-  f4v* d4 = reinterpret_cast<f4v*>(dst);
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int vq = 0; vq < 4; ++vq) {
-        const int64_t o = (((w * 4 + i * 2 + j) * 2) * 4 + vq) * 64 + lane;
-        d4[o] = f4v{re[i][j][4 * vq], re[i][j][4 * vq + 1], re[i][j][4 * vq + 2], re[i][j][4 * vq + 3]};
-        d4[o + 256] = f4v{im[i][j][4 * vq], im[i][j][4 * vq + 1], im[i][j][4 * vq + 2], im[i][j][4 * vq + 3]};
-      }
-}
-
-// Scales of the values of a wave's 64 x 64 quadrant at (r0, c0): rs[i][v]
-// takes the row scale of value v of block row i out, cs[j] the column
-// scale of block column j with the overall factor.  Powers of two but for
-// that factor, so value * cs * rs rounds once.
-__device__ __forceinline__ void x6_scales(const XArgs& a, int64_t r0, int64_t c0, double scale, float (&rs)[2][16],
-                                          float (&cs)[2]) {
-  const int lane = fresh_thread() & 63;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-      rs[i][v] = a.sa[(r0 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * a.sa_stride];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) cs[j] = float(scale * double(a.sb[c0 + j * 32 + (lane & 31)]));
-}
-
-// Diagonal entries r0 .. r0 + NR - 1 of T T^dagger, the rows' sums of
-// |T|^2, as 256 / NR partial sums each in sums (x6_diag adds them): called
-// by the whole workgroup, a barrier before the sums are read.  The product
-// leaves out the ll terms, whose mean is zero except on the diagonal, where
-// each is a square: there it came out 4e-8 low, as the trace did, and the
-// gradient (in which the trace part cancels) took a relative error of 5e-7
-// to 1e-6 from that (N = 10: 1.4e-6 with the product's diagonal).
-template <int NR>
-__device__ __forceinline__ void x6_diag_sums(const XArgs& a, int64_t r0, double* sums) {
-  constexpr int NP = 256 / NR;
-  const double* src = a.rsum + r0 + threadIdx.x % NR;
-  double s = 0.0;
-#pragma unroll 8
-  for (int q = threadIdx.x / NR; q < a.d / XT; q += NP) s += src[int64_t(q) * a.d];
-  sums[threadIdx.x] = s;
-}
-template <int NR>
-__device__ __forceinline__ float x6_diag(const double* sums, int r, double scale) {
-  double s = sums[r];
-#pragma unroll
-  for (int p = 1; p < 256 / NR; ++p) s += sums[p * NR + r];
-  return float(s * scale);
-}
-
-// Tile epilogue.  HEMM: C = scale (re, im).  HERK without x0: rho = (re,
-// im) / tau, and the conjugate transpose at the mirror position for an
-// off-diagonal tile.  HERK with x0: the first POVM pass over G qubits on
-// each 64 x 64 quadrant (the quadrant of wave q, q = 2 qr + qc; the upper
-// quadrant of a diagonal tile is the mirror of the lower one and skipped),
-// through a 64 x 64 tile in LDS.
-template <bool HERK, int X0G>
-__device__ __forceinline__ void x6_epilogue(const XArgs& a, int tr, int tc, const float (&re)[2][2][16],
-                                            const float (&im)[2][2][16], double scale, char* lds) {
-  const int th = fresh_thread(), lane = th & 63, w = th >> 6;
-  const int wr = w >> 1, wc = w & 1;
-  const int64_t R0 = int64_t(tr) * XT, C0 = int64_t(tc) * XT;
-  // row scales of this lane's values (four rows per group of four values)
-  // and column scales with the overall factor
-  float rs[2][16], cs[2];
-  x6_scales(a, R0 + wr * 64, C0 + wc * 64, scale, rs, cs);
-  double* diag = reinterpret_cast<double*>(lds + 64 * 64 * sizeof(Cx<float>));
-  if constexpr (HERK) {
-    if (tr == tc) {
-      x6_diag_sums<XT>(a, R0, diag);
-      __syncthreads();
-    }
-  }
-  if constexpr (X0G == 0) {
-    Cx<float>* C = static_cast<Cx<float>*>(a.C);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int64_t r = R0 + x6_row(wr, i, v, lane), c = C0 + x6_col(wc, j, lane);
-          float xr = re[i][j][v] * cs[j] * rs[i][v], xi = im[i][j][v] * cs[j] * rs[i][v];
-          if (HERK && i == j && r == c) {
-            xr = x6_diag<XT>(diag, int(r - R0), scale);
-            xi = 0.f;
-          }
-          C[r * a.ldc + c] = Cx<float>{xr, xi};
-          if (HERK && tr != tc) C[c * a.ldc + r] = Cx<float>{xr, -xi};
-        }
-    if constexpr (HERK) {
-      if (tr == tc) __syncthreads();  // the sums are read before the next segment's copies take their place
-    }
-  } else {
-    constexpr int G = X0G;
-    constexpr int S = 64 >> G;
-    constexpr int TG = 1 << (2 * G);
-    constexpr int M = (1 << G) - 1;
-    Cx<float>* L = reinterpret_cast<Cx<float>*>(lds);
-    gemm::GemmArgs g{};
-    g.x0 = a.x0;
-    g.x0g = a.x0g;
-    g.x0up = a.x0up;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int qr = q >> 1, qc = q & 1;
-      if (tr == tc && qr < qc) continue;  // uniform across the workgroup
-      if (w == q) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int r = i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), c = j * 32 + (lane & 31);
-              Cx<float> x{re[i][j][v] * cs[j] * rs[i][v], im[i][j][v] * cs[j] * rs[i][v]};
-              if (i == j && tr == tc && wr == wc && r == c) x = Cx<float>{x6_diag<XT>(diag, wr * 64 + r, scale), 0.f};
-              L[((r >> G) * S + (c >> G)) * TG + swz<G>(r & M, c & M)] = x;
-            }
-      }
-      __syncthreads();
-      gemm::x0_rounds<float, G>(g, int64_t(2) * tr + qr, int64_t(2) * tc + qc, L);
-      __syncthreads();
-    }
-  }
-}
-
-__device__ __forceinline__ void x6_zero(float (&re)[2][2][16], float (&im)[2][2][16]) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) re[i][j][v] = im[i][j][v] = 0.f;
-}
-
-// Tile of this workgroup in a ts x ts grid: blocks of 4 x 8 tiles per 32
-// consecutive logical workgroups.
-__device__ __forceinline__ void x6_hemm_tile(int ts, int& tr, int& tc) {
-  const int lb = int(xcd_order(blockIdx.x, gridDim.x));
-  if (ts % 8 == 0) {
-    const int grp = lb / 32, within = lb % 32;
-    tr = (grp / (ts / 8)) * 4 + within / 8;
-    tc = (grp % (ts / 8)) * 8 + within % 8;
-  } else {
-    tr = lb / ts;
-    tc = lb % ts;
-  }
-}
-
 // G' T: one tile per workgroup.
 __global__ __launch_bounds__(256, 1) void x6_hemm_kernel(XArgs a) {
   extern __shared__ __align__(16) char lds[];
+  if (x6_off(a)) return;
   int tr, tc;
   x6_hemm_tile(a.d / XT, tr, tc);
   double scale = 2.0 / *a.tau;
@@ -746,70 +556,18 @@ __global__ __launch_bounds__(256, 1) void x6_hemm_kernel(XArgs a) {
   x6_epilogue<false, 0>(a, tr, tc, re, im, scale, lds);
 }
 
-// (even, as x6_segment needs; iters is)
-__device__ __forceinline__ int64_t x6_slice_start(int64_t w, int64_t Q, int64_t iters) {
-  return 2 * ((w * (iters / 2)) / Q);
-}
+struct X6Seg {
+  static __device__ __forceinline__ void run(const XArgs& a, char* lds, int tr, int tc, int kb, int ke,
+                                             float (&re)[2][2][16], float (&im)[2][2][16]) {
+    x6_segment<true>(a, lds, tr, tc, kb, ke, re, im);
+  }
+};
 
-// Unit u -> tile and K panels: u = s * ntiles + t covers panels
-// [s kh, (s + 1) kh) of lower tile t (the units of a round share s, so
-// its workgroups stream the same K range).
-__device__ __forceinline__ void x6_unit(const X6HerkSched& sc, int64_t u, int64_t& t, int& k0) {
-  t = u % sc.ntiles;
-  k0 = int((u / sc.ntiles) * sc.kh);
-}
-
-// T T^dagger: logical workgroup w takes round units w, w + P, ...; a whole
-// tile (sk = 1) is finished here, a part of one is stored as a partial.
-// Then, as slice worker w < Q, the iterations [start(w), start(w + 1)) of
-// the remaining units' (unit, panel) sequence.  One loop over both, so that
-// the segment code is there once.
 template <int X0G>
 __global__ __launch_bounds__(256, 1) void x6_herk_kernel(XArgs a) {
   extern __shared__ __align__(16) char lds[];
-  const X6HerkSched& sc = a.sc;
-  const int w = int(xcd_order(blockIdx.x, gridDim.x));
-  int r = 0;
-  // transposed slices: one piece, slice w / left of unit w % left
-  int it = 0, end = 0, first_unit = 0;
-  if (w < sc.Q) {
-    it = sc.tq ? 0 : int(x6_slice_start(w, sc.Q, sc.left_iters));
-    end = sc.tq ? 1 : int(x6_slice_start(w + 1, sc.Q, sc.left_iters));
-    first_unit = it / int(sc.kh);
-  }
-  while (r < sc.rounds || it < end) {
-    int u, kb = 0, ke = int(sc.kh), slot;
-    if (r < sc.rounds) {
-      u = r * int(sc.P) + w;
-      slot = int(x6_unit_slot(u));
-      ++r;
-    } else {
-      int j;  // leftover unit
-      if (sc.tq) {
-        j = w % int(sc.left);
-        kb = (w / int(sc.left)) * int(sc.ps);
-        ke = kb + int(sc.ps);
-        it = end;
-      } else {
-        j = it / int(sc.kh);
-        kb = it % int(sc.kh);
-        ke = min(int(sc.kh), kb + (end - it));
-        it += ke - kb;
-      }
-      u = int(sc.main) + j;
-      slot = int(x6_slice_slot(sc, w, j == first_unit ? 0 : 1));  // slot w with tq
-    }
-    int64_t t;
-    int k0;
-    x6_unit(sc, u, t, k0);
-    int tr, tc;
-    tri_decode(t, tr, tc);
-    float re[2][2][16], im[2][2][16];
-    x6_zero(re, im);
-    x6_segment<true>(a, lds, tr, tc, k0 + kb, k0 + ke, re, im);
-    if (sc.sk == 1 && kb == 0 && ke == sc.kh) x6_epilogue<true, X0G>(a, tr, tc, re, im, 1.0 / x6_tau(a, lds), lds);
-    else x6_store_partial(x6_slot(a, slot), re, im);
-  }
+  if (x6_off(a)) return;
+  x6_herk_body<X6Seg, X0G>(a, lds);
 }
 
 // Slice workers holding the first and the last panel of leftover unit j.
@@ -871,12 +629,13 @@ struct X6Contrib {
 // contributions, belong to the last tiles, which thus start first.  Thread
 // th holds values 4 (th + 256 m) + c, m < 8, c < 4, of the quadrant's
 // 8192-float block (layout of x6_store_partial with w = q), loaded as
-// 16-byte vectors; the loads of up to four contributions are in flight
-// before they are added, in order.
+// 16-byte vectors; the loads of two contributions are in flight before they
+// are added, in order.
 template <int X0G>
 __global__ __launch_bounds__(256, 3) void x6_fixup_kernel(XArgs a) {
   __shared__ __align__(16) Cx<float> L[64 * 64];
   __shared__ double red[4];
+  if (x6_off(a)) return;
   const X6HerkSched& sc = a.sc;
   const int64_t t = sc.ntiles - 1 - (blockIdx.x >> 2);
   const int q = blockIdx.x & 3, qr = q >> 1, qc = q & 1;
@@ -1004,6 +763,7 @@ constexpr int YSLOT = 16 * 1024;      // 16 units: 2 row blocks of A and of B
 constexpr int YNSLOT = 8;
 constexpr int YDIST = YNSLOT - 1;
 constexpr int YCOPY = 4;              // units copied per wave and slab
+constexpr int YCHAIN = 4;             // panels per accumulation chain (of 8 at d = 128; as XCHAIN)
 static_assert(YSLOT * YNSLOT == XLDS, "one dynamic LDS size");
 static_assert((YDIST - 1) * YCOPY < 64, "vmcnt immediate");
 
@@ -1098,8 +858,8 @@ __device__ __forceinline__ void x6_tile64(const XArgs& a, char* lds, int tr, int
   };
   constexpr std::integral_constant<int, 0> b0{};
   constexpr std::integral_constant<int, 1> b1{};
-  for (int c0 = 0; c0 < npan; c0 += XCHAIN) {  // npan is a multiple of 2
-    const int end = min(npan, c0 + XCHAIN);
+  for (int c0 = 0; c0 < npan; c0 += YCHAIN) {  // npan is a multiple of 2
+    const int end = min(npan, c0 + YCHAIN);
     for (int kp = c0; kp < end; kp += 2) {
       panel(b0, kp);
       panel(b1, kp + 1);
@@ -1122,6 +882,7 @@ __device__ __forceinline__ void x6_tile64(const XArgs& a, char* lds, int tr, int
 
 __global__ __launch_bounds__(256, 1) void x6_hemm64_kernel(XArgs a) {
   extern __shared__ __align__(16) char lds[];
+  if (x6_off(a)) return;
   int tr, tc;
   x6_hemm_tile(a.d / YT, tr, tc);
   double scale = 2.0 / *a.tau;
@@ -1135,7 +896,7 @@ __global__ __launch_bounds__(256, 1) void x6_hemm64_kernel(XArgs a) {
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int64_t r = r0 + 8 * (v >> 2) + (v & 3);
-    const float rs = a.sa[r * a.sa_stride];
+    const float rs = a.sa[r];
     C[r * a.ldc + c] = Cx<float>{re[v] * cs * rs, im[v] * cs * rs};
   }
 }
@@ -1144,6 +905,7 @@ __global__ __launch_bounds__(256, 1) void x6_hemm64_kernel(XArgs a) {
 template <int X0G>
 __global__ __launch_bounds__(256, 1) void x6_herk64_kernel(XArgs a) {
   extern __shared__ __align__(16) char lds[];
+  if (x6_off(a)) return;
   int tr, tc;
   tri_decode(xcd_order(blockIdx.x, gridDim.x), tr, tc);
   float re[16], im[16];
@@ -1186,83 +948,66 @@ __global__ __launch_bounds__(256, 1) void x6_herk64_kernel(XArgs a) {
   }
 }
 
-// The product kernels use more LDS than the static limit: raise the
-// per-kernel limit once per device before the first launch.
-template <auto K>
-hipError_t x6_allow_lds() {
-  static std::mutex mu;  // one flag set per kernel
-  static bool done[64] = {};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  std::lock_guard<std::mutex> lock(mu);
-  if (!done[dev]) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(K), hipFuncAttributeMaxDynamicSharedMemorySize, XLDS);
-    if (e != hipSuccess) return e;
-    done[dev] = true;
-  }
-  return hipSuccess;
-}
-
 unsigned x6_split_grid(int d) { return unsigned(int64_t(d / 32) * (d / 128)); }
 
-int x6_cus() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
-  return cus;
-}
-
 template <int X0G>
-hipError_t x6_run_herk(XArgs a, int n, hipStream_t s) {
-  if (x6_small_tiles(n)) {
-    hipError_t e = x6_allow_lds<x6_herk64_kernel<X0G>>();
+hipError_t x6_run_herk(const XArgs& a, bool small, hipStream_t s) {
+  if (small) {
+    hipError_t e = x6_allow_lds<x6_herk64_kernel<X0G>, XLDS>();
     if (e != hipSuccess) return e;
     const int ts = a.d / YT;
     x6_herk64_kernel<X0G><<<unsigned(ts * (ts + 1) / 2), 256, XLDS, s>>>(a);
     return hipGetLastError();
   }
-  hipError_t e = x6_allow_lds<x6_herk_kernel<X0G>>();
+  hipError_t e = x6_allow_lds<x6_herk_kernel<X0G>, XLDS>();
   if (e != hipSuccess) return e;
-  a.sc = x6_herk_sched(n, x6_cus());
   const int64_t grid = a.sc.rounds > 0 ? a.sc.P : a.sc.Q;
   x6_herk_kernel<X0G><<<unsigned(grid), 256, XLDS, s>>>(a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  x6_fixup_kernel<X0G><<<unsigned(a.ntiles) * 4, 256, 0, s>>>(a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_x6_herk(const void* T, int64_t ldt, void* rho, int64_t ldr, int n, double* tau_partials,
-                          const void* f, double* tau_dev, void* planes, void* partials, hipStream_t s,
-                          const Pass0Out* x0, void* tt_planes) {
+hipError_t x6_launch_fixup(const XArgs& a, int x0g, hipStream_t s) {
+  const unsigned grid = unsigned(a.ntiles) * 4;
+  if (x0g == 6) x6_fixup_kernel<6><<<grid, 256, 0, s>>>(a);
+  else if (x0g == 5) x6_fixup_kernel<5><<<grid, 256, 0, s>>>(a);
+  else if (x0g == 4) x6_fixup_kernel<4><<<grid, 256, 0, s>>>(a);
+  else x6_fixup_kernel<0><<<grid, 256, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+hipError_t launch_x6_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int64_t ldr, int n,
+                          double* tau_partials, const void* f, double* tau_dev, void* planes, void* partials,
+                          hipStream_t s, const Pass0Out* x0, void* tt_planes) {
   const int d = 1 << n;
   if (d < kX6Tile || !tau_partials) return hipErrorInvalidValue;
   if (x0 && (x0->g < 4 || x0->g > 6 || !x0->tetra)) return hipErrorInvalidValue;
-  u16x8* P = static_cast<u16x8*>(planes);
-  const X6Scales sc = x6_scales_of(x6_herk_scales(planes, n), n);
+  u16x8* P = static_cast<u16x8*>(x6_herk_planes(planes, n));
+  const X6Scales sc = x6_herk_scales(planes, n);
+  hipError_t e;
   {
     ProfScope prof("x6_split_t", s);
     const Cx<float>* Tf = static_cast<const Cx<float>*>(T);
     const float* ff = static_cast<const float*>(f);
     u16x8* PT = static_cast<u16x8*>(tt_planes);
-    if (f) x6_absmax_t_kernel<true><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, tau_partials, ff);
-    else x6_absmax_t_kernel<false><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc.rowp, sc.colp, tau_partials, ff);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (PT) x6_split_t_kernel<true><<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, sc, P, PT);
-    else x6_split_t_kernel<false><<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, sc, P, PT);
+    const float low = x6_dense_low(kX6DenseBits);
+    if (f) x6_absmax_t_kernel<true><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc, tau_partials, ff);
+    else x6_absmax_t_kernel<false><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc, tau_partials, ff);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (PT) x6_split_t_kernel<true><<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, sc, P, PT, low);
+    else x6_split_t_kernel<false><<<x6_split_grid(d), 256, 0, s>>>(Tf, ldt, d, sc, P, PT, low);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   ProfScope prof("herk_x6", s);
+  const bool small = x6_small_tiles(n);
   XArgs a{};
   a.A = P;
   a.B = P;
+  a.bad[0] = a.bad[1] = sc.bad;  // T's rows on both sides
+  a.when = kX6Dense;
   a.sa = sc.rinv;
   a.sb = sc.rinv;
-  a.sa_stride = 1;
   a.rsum = sc.rsum;
   a.C = rho;
   a.ldc = ldr;
@@ -1273,47 +1018,57 @@ hipError_t launch_x6_herk(const void* T, int64_t ldt, void* rho, int64_t ldr, in
   a.part = static_cast<float*>(partials);
   a.ntiles = (d / XT) * (d / XT + 1) / 2;
   a.kIters = d / 16;
+  a.sc = x6_herk_sched(n, x6_cus());
+  const int g = x0 ? x0->g : 0;
   if (x0) {
     a.x0 = x0->X;
     a.x0g = x0->g;
     a.x0up = n - x0->g;
-    return x0->g == 6 ? x6_run_herk<6>(a, n, s) : x0->g == 5 ? x6_run_herk<5>(a, n, s) : x6_run_herk<4>(a, n, s);
   }
-  return x6_run_herk<0>(a, n, s);
+  e = g == 6   ? x6_run_herk<6>(a, small, s)
+      : g == 5 ? x6_run_herk<5>(a, small, s)
+      : g == 4 ? x6_run_herk<4>(a, small, s)
+               : x6_run_herk<0>(a, small, s);
+  if (e != hipSuccess) return e;
+  if (prec == QST_F32) return small ? hipSuccess : x6_launch_fixup(a, g, s);
+  // QST_F32X6, T not dense: its partial tiles take the same fix-up
+  if ((e = x3_launch_herk(a, T, ldt, g, P, sc.rinv, s)) != hipSuccess) return e;
+  a.when = small ? kX6Sparse : kX6Always;
+  return x6_launch_fixup(a, g, s);
 }
 
-hipError_t launch_x6_hemm(const void* G, int64_t ldg, const void* T, int64_t ldt, void* out, int64_t ldo, int n,
-                          const double* tau_dev, const double* upstream_dev, void* planes, hipStream_t s,
-                          const X6Ready* ready) {
+hipError_t launch_x6_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T, int64_t ldt, void* out,
+                          int64_t ldo, int n, const double* tau_dev, const double* upstream_dev, void* planes,
+                          hipStream_t s, const X6Scales* t_ready, X6Gate* sparse) {
   const int d = 1 << n;
-  if (d < kX6Tile) return hipErrorInvalidValue;
-  u16x8* PG = static_cast<u16x8*>(planes);
+  if (d < kX6Tile || !planes) return hipErrorInvalidValue;
+  u16x8* PG = static_cast<u16x8*>(x6_hemm_planes(planes, n));
   u16x8* PT = PG + x6_plane_bytes(n) / sizeof(u16x8);
-  XArgs a{};
   hipError_t e;
-  if (ready) {
-    a.sa = ready->ginv;
-    a.sa_stride = 0;
-    a.sb = ready->tcinv;
-  } else {
+  const X6Pair p{{static_cast<const Cx<float>*>(G), static_cast<const Cx<float>*>(T)},
+                 {ldg, ldt},
+                 {x6_hemm_scales(planes, n, 0), t_ready ? *t_ready : x6_hemm_scales(planes, n, 1)},
+                 {PG, PT},
+                 {x6_dense_low(kX6DenseBits + (n >= 10 ? 2 : 0)), x6_dense_low(kX6DenseBits)}};
+  {
     ProfScope prof("x6_split_gt", s);
-    const X6Pair p{{static_cast<const Cx<float>*>(G), static_cast<const Cx<float>*>(T)},
-                   {ldg, ldt},
-                   {x6_scales_of(x6_hemm_scales(planes, n, 0), n), x6_scales_of(x6_hemm_scales(planes, n, 1), n)},
-                   {PG, PT}};
-    const unsigned mg = unsigned(std::min<int64_t>(kReduceBlocks, int64_t(d / 64) * (d / 64)));
-    x6_absmax_gt_kernel<<<dim3(mg, 2), 256, 0, s>>>(p, d);
+    const unsigned mg = unsigned(std::min<int64_t>(kReduceBlocks, int64_t(d / 64) * (d / 64))), ny = t_ready ? 1 : 2;
+    x6_absmax_gt_kernel<<<dim3(mg, ny), 256, 0, s>>>(p, d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    x6_split_gt_kernel<<<dim3(x6_split_grid(d), 2), 256, 0, s>>>(p, d);
+    x6_split_gt_kernel<<<dim3(x6_split_grid(d), ny), 256, 0, s>>>(p, d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    a.sa = p.sc[0].rinv;
-    a.sa_stride = 1;
-    a.sb = p.sc[1].cinv;
   }
   const bool small = x6_small_tiles(n);
-  if ((e = small ? x6_allow_lds<x6_hemm64_kernel>() : x6_allow_lds<x6_hemm_kernel>()) != hipSuccess) return e;
+  if ((e = small ? x6_allow_lds<x6_hemm64_kernel, XLDS>() : x6_allow_lds<x6_hemm_kernel, XLDS>()) != hipSuccess)
+    return e;
+  XArgs a{};
   a.A = PG;
   a.B = PT;
+  a.bad[0] = p.sc[0].bad;
+  a.bad[1] = p.sc[1].bad + 1;
+  a.when = kX6Dense;
+  a.sa = p.sc[0].rinv;
+  a.sb = p.sc[1].cinv;
   a.C = out;
   a.ldc = ldo;
   a.d = d;
@@ -1321,9 +1076,15 @@ hipError_t launch_x6_hemm(const void* G, int64_t ldg, const void* T, int64_t ldt
   a.up = upstream_dev;
   a.kIters = d / 16;
   const int ts = d / (small ? YT : XT);
-  ProfScope prof("hemm_x6", s, true);
-  hipExtLaunchKernelGGL(small ? x6_hemm64_kernel : x6_hemm_kernel, dim3(unsigned(ts * ts)), dim3(256), XLDS, s, prof.start(), prof.stop(), 0, a);
-  return hipGetLastError();
+  {
+    ProfScope prof("hemm_x6", s, true);
+    hipExtLaunchKernelGGL(small ? x6_hemm64_kernel : x6_hemm_kernel, dim3(unsigned(ts * ts)), dim3(256), XLDS, s,
+                          prof.start(), prof.stop(), 0, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (sparse) *sparse = X6Gate{{a.bad[0], a.bad[1]}};
+  if (prec == QST_F32) return hipSuccess;
+  return x3_launch_hemm(a, G, ldg, T, ldt, PG, p.sc[0].rinv, p.sc[1].cinv, s);
 }
 
 }  // namespace qst

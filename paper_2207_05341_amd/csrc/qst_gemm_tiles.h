@@ -32,6 +32,7 @@ struct GemmArgs {
   void* partial;  // stream-K partial accumulators [P][2][2 * TILE] (acc scalar)
   const double* tau_part;  // HERK: FP64 partial sums of tau (kReduceBlocks), or NULL to read *tau
   double* tau_out;         // HERK with tau_part: where workgroup 0 stores tau
+  const int* gate[2];      // run only where one of these flags is set (gate[0] NULL: always)
   // HERK with the first POVM pass in the epilogue (kernels instantiated with
   // X0; tetrahedral POVM): a finished tile of rho is not stored; the pass
   // over its x0g lowest qubits is applied to each of its 2^x0g x 2^x0g
@@ -65,7 +66,7 @@ struct CxPolicy {
   // waves per SIMD the register allocation must allow (fp64 3M: 2, which
   // caps a lane at 256 registers; it would take 260 unconstrained)
   static constexpr int kMinWaves = 2;
-  static constexpr bool kStreamK = sizeof(R) == 8;  // FP32 products of stream-K size run split (k_xgemm.hip)
+  static constexpr bool kStreamK = true;
   struct Smem {
     Cx<R> As[DB ? 2 : 1][KP][BM + PADC];
     Cx<R> Bs[DB ? 2 : 1][KP][BM + PADC];

@@ -126,16 +126,23 @@ struct Pass0Out {
 };
 // planes: the bf16 planes of T written by launch_tau (BF16 path, d >
 // kBf16SplitMaxDim), or NULL to round T inside the product.
+// gate: run only where one of its flags is set when the kernels start (the
+// split products have done the others), or NULL.
+struct X6Gate {
+  const int* bad[2];
+};
 hipError_t launch_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int64_t ldr, int n,
                        const double* tau_partials, double* tau_dev, void* sk_partial, hipStream_t s,
-                       const Pass0Out* x0 = nullptr, const void* planes = nullptr);
+                       const Pass0Out* x0 = nullptr, const void* planes = nullptr, const X6Gate* gate = nullptr);
 
 // out = (upstream ? *upstream : 1) * 2 / *tau_dev * G T.  planes (BF16 path,
 // used for d >= 1024; may be NULL): 16 d^2 bytes for the split-bf16 planes
-// of G and of T^T, which the 128 x 128-tile product reads.
+// of G and of T^T, which the 128 x 128-tile product reads.  Split products
+// (use_x6): planes of x6_hemm_bytes; t_ready as launch_x6_hemm.
 hipError_t launch_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T, int64_t ldt,
                        void* out, int64_t ldo, int n, const double* tau_dev,
-                       const double* upstream_dev, void* sk_partial, hipStream_t s, void* planes = nullptr);
+                       const double* upstream_dev, void* sk_partial, hipStream_t s, void* planes = nullptr,
+                       const X6Scales* t_ready = nullptr);
 
 // The whole of qst_likelihood for n <= kSmallMaxQubits in one launch (FP64,
 // FP32): tau, L and F, the counters (bad may be NULL) and, with G, G' in full;
@@ -145,28 +152,25 @@ hipError_t launch_small_likelihood(qst_prec prec, int n, bool tetra, const void*
                                    unsigned long long* bad_dev, void* G, int64_t ldG, const void* pt, double* fc_dev,
                                    hipStream_t s);
 
-// Split products (k_xgemm.hip), d >= kX6Tile.  T T^dagger: planes
-// x6_herk_bytes(n) and partials x6_partial_bytes(n) of workspace; the
-// kernel that finds T's scales also writes the kReduceBlocks partial sums of
-// tau at tau_partials and, with f (4^N FP32 values), those of F = sum f at
-// tau_partials + kReduceBlocks (launch_tau is not called); tau is stored at
-// tau_dev; rho and x0 as launch_herk.  With tt_planes (x6_plane_bytes(n))
-// the kernel that splits T also writes T^T's planes for G' T there, and what
-// takes their scales out again at cinv of T's X6Scales.
-// G' T: planes x6_hemm_bytes(n), G''s planes, then T^T's, then the scales;
-// ready: both planes are there already (G and T are not read), with one
-// scale for all of G' (ginv) and one per column of T (tcinv); as launch_hemm
-// otherwise.
-struct X6Ready {
-  const float* ginv;
-  const float* tcinv;
-};
-hipError_t launch_x6_herk(const void* T, int64_t ldt, void* rho, int64_t ldr, int n, double* tau_partials,
-                          const void* f, double* tau_dev, void* planes, void* partials, hipStream_t s,
-                          const Pass0Out* x0, void* tt_planes = nullptr);
-hipError_t launch_x6_hemm(const void* G, int64_t ldg, const void* T, int64_t ldt, void* out, int64_t ldo, int n,
-                          const double* tau_dev, const double* upstream_dev, void* planes, hipStream_t s,
-                          const X6Ready* ready = nullptr);
+// Split products (k_xgemm.hip), d >= kX6Tile, QST_F32 or QST_F32X6.
+// T T^dagger: planes x6_herk_bytes and partials x6_herk_partial_bytes of
+// workspace; the kernel that finds T's scales also writes the kReduceBlocks
+// partial sums of tau at tau_partials and, with f (4^N FP32 values), those of
+// F = sum f at tau_partials + kReduceBlocks (launch_tau is not called); tau is
+// stored at tau_dev; rho and x0 as launch_herk.  With tt_planes
+// (x6_plane_bytes) the kernel that splits T also writes T^T's fp16 planes for
+// G' T there, with the scales of T's columns in T's X6Scales.
+// G' T: planes x6_hemm_bytes; with t_ready (the X6Scales of that T) T^T's
+// planes are there already, after G''s; as launch_hemm otherwise.
+// QST_F32: where an operand is not dense nothing is stored, and the caller
+// launches the FP32 MFMA product with the X6Gate (launch_herk's gate is T's
+// X6Scales::bad[0]).
+hipError_t launch_x6_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int64_t ldr, int n,
+                          double* tau_partials, const void* f, double* tau_dev, void* planes, void* partials,
+                          hipStream_t s, const Pass0Out* x0, void* tt_planes = nullptr);
+hipError_t launch_x6_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T, int64_t ldt, void* out,
+                          int64_t ldo, int n, const double* tau_dev, const double* upstream_dev, void* planes,
+                          hipStream_t s, const X6Scales* t_ready, X6Gate* sparse);
 
 // Forward (adjoint=false): mat = rho (lower triangle read) -> pvec.
 // Adjoint (adjoint=true): g' = F - f/p from (pvec, fvec, F_dev) -> mat = G'
@@ -213,18 +217,12 @@ hipError_t launch_likelihood_finish(const double* part, int nb, const double* Fp
 // inter0), the fused last pass (+ NLL finish into nll_dev / bad_dev), and, if
 // G is not NULL, the adjoint passes P-2..0.  part: FP64 partials [4][blocks
 // of the last pass]; Fpart: the kReduceBlocks F partials.  With pt (4^N
-// reals), the last pass also forms F_c against pt into fc_dev.  With
-// gplanes (FP32 storage, tetrahedral, two passes, pass0_writes_planes(pl)),
-// adjoint pass 0 writes G' as the split planes of the QST_F32X6 gradient
-// product there instead of writing G (which may then be NULL), and what
-// takes their scale out again at ginv; ymax: one float per block of the last
-// pass.
+// reals), the last pass also forms F_c against pt into fc_dev.
 hipError_t launch_povm_fused(qst_prec prec, const PovmPlan& pl, const double* W, const double* V, bool tetra,
                              const void* rho, int64_t ld_rho, const void* fvec, const double* Fpart, void* G,
                              int64_t ldG, void* inter0, void* inter1, double* part, double* nll_dev,
                              unsigned long long* bad_dev, bool pass0_done, hipStream_t s, const void* pt = nullptr,
-                             double* fc_dev = nullptr, void* gplanes = nullptr, float* ymax = nullptr,
-                             float* ginv = nullptr);
+                             double* fc_dev = nullptr);
 
 hipError_t launch_fsum(qst_prec prec, const void* f, int n, double* partials, double* F_dev,
                        hipStream_t s);

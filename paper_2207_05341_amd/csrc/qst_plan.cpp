@@ -183,12 +183,12 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
   // stream-K partial tiles: the split T T^dagger always, the other
   // products from kStreamKMinQubits
   const bool sk = x6 || n >= kStreamKMinQubits;
-  const size_t sk_bytes = x6 ? x6_partial_bytes(n) : stream_k_partial_bytes(prec);
+  const size_t sk_bytes = x6 ? x6_herk_partial_bytes(prec, n) : stream_k_partial_bytes(prec);
   const bool planes = (prec == QST_BF16GEMM && d > size_t(kBf16SplitMaxDim)) || x6;
   const bool hemm_planes = (prec == QST_BF16GEMM && d >= 1024) || x6;
   // the BF16 path's bf16 planes (2 for T T^dagger, 8 for G' T), or the
   // split products' planes and scales
-  const size_t herk_planes = x6 ? x6_herk_bytes(n) : 2 * D * sizeof(uint16_t);
+  const size_t herk_planes = x6 ? x6_herk_bytes(prec, n) : 2 * D * sizeof(uint16_t);
   const size_t hemm_plane_bytes = x6 ? x6_hemm_bytes(prec, n) : 8 * D * sizeof(uint16_t);
   auto take_planes = [&](size_t bytes) {
     w.planes = take(bytes);
@@ -253,8 +253,7 @@ WsLayout workspace_layout(int n, qst_prec prec, int op, bool recompute) {
       off = absmap_layout(n).total;
       break;
     case QST_OP_LIKELIHOOD_GRAD: {
-      // the likelihood's layout (same offsets), then G' for the routes that
-      // form it, and the planes of the gradient product (split products: G''s
+      // the likelihood's layout (same offsets), then G', and the planes of the gradient product (split products: G''s
       // then T^T's; BF16 path from d = 1024: split planes of G' and T^T);
       // the likelihood's partial tiles serve the gradient product too
       w = workspace_layout(n, prec, QST_OP_LIKELIHOOD, false);
@@ -509,9 +508,9 @@ GeneralLayout general_layout(int n, qst_prec prec, int K, bool with_state) {
     w.h = take(D * rb);
     w.rho = take(D * cb);
     if (use_x6(prec, n)) {
-      w.planes = take(x6_herk_bytes(n));
+      w.planes = take(x6_herk_bytes(prec, n));
       w.has_planes = true;
-      w.sk = take(x6_partial_bytes(n));
+      w.sk = take(x6_herk_partial_bytes(prec, n));
       w.has_sk = true;
     } else {
       if (prec == QST_BF16GEMM && d > size_t(kBf16SplitMaxDim)) {

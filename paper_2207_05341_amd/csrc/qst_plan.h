@@ -19,24 +19,22 @@ inline bool prec_valid(int p) { return p == QST_F64 || p == QST_F32 || p == QST_
 // QST_F32 in its complex products only).
 inline qst_prec storage_prec(qst_prec p) { return p == QST_F32X6 ? QST_F32 : p; }
 
-// Split products (k_xgemm.hip): 128 x 128 output tiles; T T^dagger runs
-// stream-K on at most kX6MaxGrid workgroups, each leaving at most two
-// partial tiles (re, im FP32).  Operand planes: re and im in two fp16 parts
-// each (8 bytes per element) of T for T T^dagger and of G' and T^T for G' T,
-// followed by the scales they were split with (X6Scales).
+// Split products (k_xgemm.hip, k_xgemm3.hip): 128 x 128 output tiles;
+// T T^dagger runs stream-K on at most kX6MaxGrid workgroups, each leaving at
+// most two partial tiles (re, im FP32).
 constexpr int kX6Tile = 128;
 constexpr int kX6MaxGrid = 256;
-// Up to d = 1024 the products take 64 x 64 tiles, which need no split of K
-// to spread over the compute units (the 64-tile kernels of k_xgemm.hip).
+// Up to d = 1024 the fp16 products take 64 x 64 tiles, which need no split of
+// K to spread over the compute units (the 64-tile kernels of k_xgemm.hip).
 constexpr int kX6SmallTile = 64;
 inline bool x6_small_tiles(int n) { return n <= 10; }
-// QST_F32X6 from d = kX6Tile; QST_F32 from kX6F32MinQubits, where the
-// split products take over from the FP32 MFMA products: at N = 10 a
-// likelihood and gradient takes 124 us against 153 us, at N = 11 356 against
-// 673, at N = 12 2320 against 4932, with smaller errors at each.  Below,
-// QST_F32's gradient product takes no workspace, which its callers may rely
-// on, so there is no place for the planes (N = 9 with them, as QST_F32X6 in
-// one call: 66 us against 100; N = 8: 59 against 64; N = 7: 49 against 43).
+// QST_F32X6 from d = kX6Tile; QST_F32 from kX6F32MinQubits, where the fp16
+// products take over from the FP32 MFMA products for dense operands
+// (X6Scales): at N = 10 a likelihood and gradient takes 124 us against 153
+// us, at N = 11 356 against 673, at N = 12 2320 against 4932, with smaller
+// errors at each.  Below, a QST_F32 call would gain less (N = 9, as
+// QST_F32X6: 66 us against 100; N = 8: 59 against 64; N = 7: 49 against 43),
+// and its gradient product takes no workspace.
 constexpr int kX6F32MinQubits = 10;
 inline bool use_x6(qst_prec p, int n) {
   return (p == QST_F32X6 && (int64_t(1) << n) >= kX6Tile) || (p == QST_F32 && n >= kX6F32MinQubits);
@@ -99,7 +97,6 @@ inline X6HerkSched x6_herk_sched(int n, int cus) {
   return s;
 }
 inline size_t x6_partial_bytes(int n) {
-  if (x6_small_tiles(n)) return 0;
   // the largest schedule over devices with up to kX6MaxGrid compute units
   size_t most = 0;
   for (int cus = 1; cus <= kX6MaxGrid; ++cus) {
@@ -108,36 +105,56 @@ inline size_t x6_partial_bytes(int n) {
   }
   return most * 2 * kX6Tile * kX6Tile * sizeof(float);
 }
-inline size_t x6_plane_bytes(int n) { return (size_t(1) << (2 * n)) * 8; }
-// Scales of a split matrix: the largest component of every 64-entry piece of
-// a row and of a column ([d / 64][d] floats each), what takes the scale of
-// each row and of each column out again ([d] floats each), and the FP64 sum
-// of |x|^2 over every 128-entry piece of a row ([d / 128][d]).
-inline size_t x6_scale_bytes(int n) {
-  const size_t d = size_t(1) << n;
-  return (d / 128) * d * sizeof(double) + (2 * (d / 64) * d + 2 * d) * sizeof(float);
-}
+// What the split of a matrix leaves: the largest component of every 64-entry
+// piece of a row and of a column ([d / 64][d] floats each), what takes the
+// scale of each row and of each column out again ([d] floats each), the FP64
+// sum of |x|^2 over every 128-entry piece of a row ([d / 128][d]), and two
+// flags: rows (bad[0]) or columns (bad[1]) that are not dense (k_xgemm.hip),
+// whose products are left to the general kernels.
 struct X6Scales {
   double* rsum;
   float *rowp, *colp, *rinv, *cinv;
+  int* bad;
 };
+inline size_t x6_scale_bytes(int n) {
+  const size_t d = size_t(1) << n;
+  return (d / 128) * d * sizeof(double) + (2 * (d / 64) * d + 2 * d) * sizeof(float) + 256;
+}
 inline X6Scales x6_scales_of(void* base, int n) {
   const size_t d = size_t(1) << n, np = (d / 64) * d;
   double* r = static_cast<double*>(base);
   float* b = reinterpret_cast<float*>(r + (d / 128) * d);
-  return X6Scales{r, b, b + np, b + 2 * np, b + 2 * np + d};
+  return X6Scales{r, b, b + np, b + 2 * np, b + 2 * np + d, reinterpret_cast<int*>(b + 2 * np + 2 * d)};
 }
-// T T^dagger: T's planes, then its scales.  G' T: G''s planes, T^T's
-// planes, then G''s scales and T's; QST_F32X6 takes 36 bytes per element,
-// more than that from d = kX6Tile, the size its workspace has had.
-inline size_t x6_herk_bytes(int n) { return x6_plane_bytes(n) + x6_scale_bytes(n); }
+// Operand planes, after the scales: for the fp16 products re and im in two
+// parts each (8 bytes per element of T for T T^dagger; of G', then T^T, for
+// G' T); for the general products of QST_F32X6 (k_xgemm3.hip) four or three
+// groups in three bf16 parts, in the same place.  The FP32 MFMA products that
+// QST_F32 falls back to take no planes, but partial tiles, for G' T in the
+// place of the planes.
+constexpr int kX3HerkBytes = 24, kX3HemmBytes = 36;  // per element, all operands
+inline size_t stream_k_partial_bytes(qst_prec p);
+inline size_t x6_plane_bytes(int n) { return (size_t(1) << (2 * n)) * 8; }
+inline size_t x6_herk_bytes(qst_prec p, int n) {
+  const size_t D = size_t(1) << (2 * n);
+  return x6_scale_bytes(n) + (p == QST_F32X6 ? kX3HerkBytes * D : x6_plane_bytes(n));
+}
 inline size_t x6_hemm_bytes(qst_prec p, int n) {
-  return p == QST_F32X6 ? (size_t(1) << (2 * n)) * 36 : 2 * (x6_plane_bytes(n) + x6_scale_bytes(n));
+  const size_t D = size_t(1) << (2 * n), two = 2 * x6_plane_bytes(n), sk = stream_k_partial_bytes(QST_F32);
+  return 2 * x6_scale_bytes(n) + (p == QST_F32X6 ? kX3HemmBytes * D : two > sk ? two : sk);
 }
-inline void* x6_herk_scales(void* planes, int n) { return static_cast<char*>(planes) + x6_plane_bytes(n); }
-inline void* x6_hemm_scales(void* planes, int n, int which) {
-  return static_cast<char*>(planes) + 2 * x6_plane_bytes(n) + which * x6_scale_bytes(n);
+// partial tiles of T T^dagger
+inline size_t x6_herk_partial_bytes(qst_prec p, int n) {
+  const size_t x6 = p == QST_F32 && x6_small_tiles(n) ? 0 : x6_partial_bytes(n);
+  const size_t sk = p == QST_F32 ? stream_k_partial_bytes(QST_F32) : 0;
+  return x6 > sk ? x6 : sk;
 }
+inline X6Scales x6_herk_scales(void* planes, int n) { return x6_scales_of(planes, n); }
+inline void* x6_herk_planes(void* planes, int n) { return static_cast<char*>(planes) + x6_scale_bytes(n); }
+inline X6Scales x6_hemm_scales(void* planes, int n, int which) {
+  return x6_scales_of(static_cast<char*>(planes) + which * x6_scale_bytes(n), n);
+}
+inline void* x6_hemm_planes(void* planes, int n) { return static_cast<char*>(planes) + 2 * x6_scale_bytes(n); }
 
 // The product-POVM map is applied in passes.  Pass j contracts a group of
 // g_j consecutive qubits inside on-chip memory; groups run from the least
@@ -173,7 +190,6 @@ bool fused_likelihood(const PovmPlan& pl, qst_prec prec);
 
 // Whether adjoint pass 0 of a fused plan can write G' as split operand
 // planes (first group of 5 or 6 qubits: tiles of at least 32 rows).
-inline bool pass0_writes_planes(const PovmPlan& pl) { return pl.passes >= 2 && (pl.g[0] == 5 || pl.g[0] == 6); }
 
 // Absolute-map workspace (qst_abs_map, qst_abs_map_backward): three d x d
 // complex FP64 buffers, d FP64 values (Jacobi norm partials, then

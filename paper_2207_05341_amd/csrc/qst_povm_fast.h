@@ -8,7 +8,6 @@
 #include "qst_device.h"
 #include "qst_povm_ops.h"
 #include "qst_povm_rounds.h"
-#include "qst_split.h"
 
 namespace qst {
 namespace fast_pass {
@@ -20,21 +19,9 @@ namespace fast_pass {
 // call with index wb (thread tid of 256) covers tiles wb * TPW ..; tiles
 // past ntiles load nothing and store nothing.  lds holds TPW * 4^G values.
 // ---------------------------------------------------------------------------
-//
-// PLANES (adjoint, FP32, tetrahedral, G = 5 or 6): instead of G' itself, G'
-// as the split operand planes of the QST_F32X6 gradient product (row
-// operand; layout of qst_split.h) at a.gplanes: each tile, then its
-// conjugate transpose (off the diagonal), passes through LDS row-major
-// (16-byte chunks swizzled by row) and every thread writes four unit-block
-// slots.  All rows take one scale, from a bound that is known before any G'
-// is: with M_a the POVM, |G'_rc| <= sum_a |(M_a)_rc| |y_a| per qubit, and
-// sum_a |(M_a)_rc| is 1 on the diagonal and 0.82 off it, so no modulus grows
-// past the largest of the intermediate (a.ymax; a modulus is at most
-// sqrt 2 times its larger component, hence one binade of headroom).
-template <typename R, bool ADJ, bool TETRA, int G, bool PLANES = false>
+template <typename R, bool ADJ, bool TETRA, int G>
 __device__ __forceinline__ void mat_pass_body(const PassArgs& a, const ModeMatrix& A, int64_t ntiles, int64_t wb,
                                               unsigned tid, Cx<R> (&lds)[(256 >> (2 * (G - 2))) << (2 * G)]) {
-  static_assert(!PLANES || (ADJ && TETRA && G >= 5 && sizeof(R) == 4), "planes from FP32 adjoint tiles of 32 or 64 rows");
   constexpr int NT = 1 << (2 * (G - 2));
   constexpr int TPW = 256 / NT;
   constexpr int TILE = 1 << (2 * G);
@@ -63,19 +50,6 @@ __device__ __forceinline__ void mat_pass_body(const PassArgs& a, const ModeMatri
     }
   };
 
-  float gsc = 1.f;
-  if constexpr (PLANES) {
-    __shared__ float ym[4];
-    float m = 0.f;
-    for (int i = tid; i < a.nymax; i += 256) m = fmaxf(m, a.ymax[i]);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    if ((tid & 63) == 0) ym[tid >> 6] = m;
-    __syncthreads();
-    const int e = x6_scale_exp(fmaxf(fmaxf(ym[0], ym[1]), fmaxf(ym[2], ym[3])), kX6Top - 1);
-    gsc = x6_pow2(e);
-    if (wb == 0 && tid == 0) *a.ginv = x6_pow2(-e);
-  }
   Cx<R> x[16];
   if constexpr (!ADJ) {
     Cx<R> blk[4][4];
@@ -140,7 +114,7 @@ __device__ __forceinline__ void mat_pass_body(const PassArgs& a, const ModeMatri
           L[swz<G>(r, c)] = x[m];
         }
         __syncthreads();
-      } else if (active && !PLANES) {
+      } else if (active) {
         Cx<R> blk[4][4];
 #pragma unroll
         for (int m = 0; m < 16; ++m) blk[blk_ri(m)][blk_ci(m)] = x[m];
@@ -158,44 +132,6 @@ __device__ __forceinline__ void mat_pass_body(const PassArgs& a, const ModeMatri
 #pragma unroll
             for (int ri = 0; ri < 4; ++ri) row[ri] = Cx<R>{blk[ri][ci].re, -blk[ri][ci].im};
           }
-        }
-      }
-    }
-    if constexpr (PLANES) {
-      constexpr int S = 1 << G;  // tile side
-      // (r, c) of the tile in LDS: row-major, 16-byte chunks swizzled by row
-      auto at = [](int r, int c) { return r * S + 2 * (((c >> 1) ^ r) & (S / 2 - 1)) + (c & 1); };
-      __syncthreads();  // every thread is past its round-0 reads of L
-      if (active) {
-#pragma unroll
-        for (int m = 0; m < 16; ++m) L[at(4 * aq + blk_ri(m), 4 * bq + blk_ci(m))] = x[m];
-      }
-      __syncthreads();
-      if (active) {
-        // slots of the tile: 2 (tile, mirror) x (S / 32) row blocks x
-        // (S / 16) k blocks x 64 lanes, four per thread
-        constexpr int UB = (S / 32) * (S / 16);
-        const int64_t nkb = (int64_t(1) << a.n) / 16;
-        u16x8* PL = static_cast<u16x8*>(a.gplanes);
-#pragma unroll
-        for (int i = 0; i < (2 * UB * 64) / NT; ++i) {
-          const int it = t + NT * i;
-          const bool mir = it >= UB * 64;
-          if (mir && Rhi == Chi) continue;  // a diagonal tile is its own mirror
-          const int ub = (it / 64) % UB, ln = it % 64;
-          const int rbl = ub / (S / 16), kbl = ub % (S / 16);
-          const int rr = rbl * 32 + (ln & 31), k0 = kbl * 16 + 8 * (ln >> 5);
-          float re[8], im[8];
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            // G'[R0 + rr][C0 + k0 + e], or for the mirror G'[C0 + rr][R0 + k0 + e]
-            // = conj(G'[R0 + k0 + e][C0 + rr])
-            const Cx<R> v = mir ? L[at(k0 + e, rr)] : L[at(rr, k0 + e)];
-            re[e] = v.re;
-            im[e] = mir ? -v.im : v.im;
-          }
-          const int64_t rbg = (mir ? C0 : R0) / 32 + rbl, kbg = (mir ? R0 : C0) / 16 + kbl;
-          write_unit_block(PL + (rbg * nkb + kbg) * kX6BlockVecs + ln, re, im, gsc);
         }
       }
     }
@@ -316,8 +252,7 @@ __device__ __forceinline__ void kd_pass_body(const PassArgs& a, const ModeMatrix
 // Fused last pass (the kd_fused_pass kernel of k_povm_fast.hip): chunk lb
 // of J outcome positions, thread tid of 256, lds of 4^G * J values.  F is
 // the sum of f; the NLL terms and the bad-entry counts of the chunk are
-// added to L, bad0, bad1; with ymax (FP32) the largest |component| of the
-// thread's adjoint values goes there.  Reads X = a.out and writes the adjoint
+// added to L, bad0, bad1.  Reads X = a.out and writes the adjoint
 // intermediate in place.  Inactive (a padding call): the same loads,
 // rounds and barriers, nothing stored or counted.  FC: the classical
 // fidelity terms sqrt(max(p_k, 0) max(pt_k, 0)) against a.pt (loaded
@@ -326,8 +261,7 @@ __device__ __forceinline__ void kd_pass_body(const PassArgs& a, const ModeMatrix
 template <typename R, bool TETRA, int G, int J, bool FC = false>
 __device__ __forceinline__ void kd_fused_body(const PassArgs& a, const ModeMatrix& Af, const ModeMatrix& Aa, int64_t lb,
                                               unsigned tid, Cx<R> (&lds)[J << (2 * G)], bool active, double F,
-                                              double& L, double& bad0, double& bad1, double* fc = nullptr,
-                                              float* ymax = nullptr) {
+                                              double& L, double& bad0, double& bad1, double* fc = nullptr) {
   constexpr int TILE = 1 << (2 * G);
   constexpr int NB = TILE * J / 16;
   constexpr int BPT = NB / 256;
@@ -474,7 +408,6 @@ __device__ __forceinline__ void kd_fused_body(const PassArgs& a, const ModeMatri
           int r, c;
           rc_of(rf, cf, bA, bB, m >> 2, m & 3, r, c);
           if (r >= c) X[((uint32_t(r) << U) | uint32_t(c)) * kd + kd0 + j] = x[m];
-          if (sizeof(R) == 4 && ymax) *ymax = fmaxf(*ymax, fmaxf(fabsf(float(x[m].re)), fabsf(float(x[m].im))));
         }
       }
     }

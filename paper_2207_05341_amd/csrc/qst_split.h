@@ -1,16 +1,15 @@
-// Two-part fp16 split of FP32 values and the fragment-blocked operand
-// planes of the split products (written by the split kernel of k_xgemm.hip
-// and, in the combined likelihood-and-gradient call, by the last adjoint
-// POVM stage).
+// Two-part fp16 split and three-part bf16 split of FP32 values and the
+// fragment-blocked operand planes of the split products (k_xgemm.hip,
+// k_xgemm3.hip, and the batched kernel's in k_batch.hip).
 //
 // A row (or column) of an operand is first scaled by a power of two that
 // brings its largest component into [2^13, 2^14); the product's epilogue
 // takes the scales out again, so both steps are exact.  The scaled value x
 // is split as x = h + l + r, h = fp16(x), l = fp16(x - h), both rounded to
 // nearest even: h holds 11 significand bits, x - h is exact in FP32, and l
-// holds the next 11 with its sign, so |r| <= 2^-23 |x| (2^-25 at most
-// otherwise: entries below 2^-15 of the row's largest, where l is an fp16
-// subnormal of spacing 2^-24).
+// holds the next 11 with its sign, so |r| <= 2^-23 |x|; below 2^-15 of the
+// row's largest, where l is an fp16 subnormal of spacing 2^-24, |r| <= 2^-25
+// in the scaled range (2^-38 of the row's largest).
 //
 // Planes of a d x d complex matrix as the row operand of a product (row r,
 // k = column): unit (rb, kb, g, s) of 1 KB holds rows 32 rb .. 32 rb + 31,
@@ -38,9 +37,18 @@ __device__ __forceinline__ int x6_scale_exp(float m, int top) {
   const int e = top + 1 - __builtin_amdgcn_frexp_expf(m);
   return e > 126 ? 126 : (e < -126 ? -126 : e);
 }
+__device__ __forceinline__ bool x6_finite(float m) { return m <= 3.402823466e38f; }
 __device__ __forceinline__ float x6_pow2(int e) { return __builtin_amdgcn_ldexpf(1.0f, e); }
 // top of the scaled range: sums of two components of a row stay below 2^15
 constexpr int kX6Top = 13;
+// An operand is dense where at least three quarters of the components of
+// every piece of a row (column) are not below the row's (column's) largest by
+// more than 2^-bits: 8, but 10 for G' from d = 1024, whose entries fall off
+// with the Hamming distance of row and column (of Gaussian states, least
+// fraction of any 128-entry piece within 2^-8: 0.87 at N = 9, 0.52 at N = 13;
+// within 2^-10: 0.92 at N = 10, 0.85 at N = 13).
+constexpr int kX6DenseBits = 8;
+inline float x6_dense_low(int bits) { return float(1 << (kX6Top - bits)); }
 
 // H + L = the split of sc * x, eight values.
 __device__ __forceinline__ void split2(const float (&x)[8], float sc, u16x8& H, u16x8& L) {
@@ -57,9 +65,61 @@ __device__ __forceinline__ void split2(const float (&x)[8], float sc, u16x8& H, 
 
 // One lane's slot of a unit block: 8 values (re, im) scaled by sc, two
 // parts each.  out points at the unit block's first unit plus the lane.
-__device__ __forceinline__ void write_unit_block(u16x8* out, const float (&re)[8], const float (&im)[8], float sc) {
+// Returns how many of the 16 scaled components are not below low.
+__device__ __forceinline__ int write_unit_block(u16x8* out, const float (&re)[8], const float (&im)[8], float sc,
+                                                float low = 0.f) {
   split2(re, sc, out[0 * kX6UnitVecs], out[1 * kX6UnitVecs]);
   split2(im, sc, out[2 * kX6UnitVecs], out[3 * kX6UnitVecs]);
+  int n = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) n += int(fabsf(re[e] * sc) >= low) + int(fabsf(im[e] * sc) >= low);
+  return n;
+}
+
+// Three-part bf16 split: x = h + m + l exactly for every finite FP32 x above
+// 2^-110: h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), each rounded to
+// nearest even; x - h and x - h - m are exact in FP32, and the three parts
+// carry 3 x 8 significand bits and FP32's exponent range.  Planes as above,
+// three units (h, m, l) per group; groups re, im, re + im and, with NG = 4,
+// re - im.
+__device__ __forceinline__ uint32_t bf16x2_rne(float a, float b) {
+  typedef __bf16 bf2v_t __attribute__((ext_vector_type(2)));
+  const bf2v_t v = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+__device__ __forceinline__ void split3(const float (&x)[8], u16x8& H, u16x8& M, u16x8& L) {
+  u32x4 h, m, l;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    h[i] = bf16x2_rne(x[2 * i], x[2 * i + 1]);
+    float r0 = x[2 * i] - bf16_lo(h[i]), r1 = x[2 * i + 1] - bf16_hi(h[i]);
+    m[i] = bf16x2_rne(r0, r1);
+    r0 -= bf16_lo(m[i]);
+    r1 -= bf16_hi(m[i]);
+    l[i] = bf16x2_rne(r0, r1);
+  }
+  H = __builtin_bit_cast(u16x8, h);
+  M = __builtin_bit_cast(u16x8, m);
+  L = __builtin_bit_cast(u16x8, l);
+}
+
+// One lane's slot of a three-part unit block.
+template <int NG>
+__device__ __forceinline__ void write_unit_block3(u16x8* out, const float (&re)[8], const float (&im)[8]) {
+  float g2[8];
+  split3(re, out[0 * kX6UnitVecs], out[1 * kX6UnitVecs], out[2 * kX6UnitVecs]);
+  split3(im, out[3 * kX6UnitVecs], out[4 * kX6UnitVecs], out[5 * kX6UnitVecs]);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) g2[e] = re[e] + im[e];
+  split3(g2, out[6 * kX6UnitVecs], out[7 * kX6UnitVecs], out[8 * kX6UnitVecs]);
+  if constexpr (NG == 4) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g2[e] = re[e] - im[e];
+    split3(g2, out[9 * kX6UnitVecs], out[10 * kX6UnitVecs], out[11 * kX6UnitVecs]);
+  }
 }
 
 }  // namespace qst

@@ -9,6 +9,7 @@
 namespace qst {
 
 typedef float f16v __attribute__((ext_vector_type(16)));
+typedef float f4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // A wave-uniform pointer moved into scalar registers.  The builtin takes
@@ -45,6 +46,10 @@ __device__ __forceinline__ uint32_t lds_address(const char* p) {
 
 __device__ __forceinline__ f16v mfma32(h16x8 a, h16x8 b, f16v c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f16v mfma32b(u16x8 a, u16x8 b, f16v c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
 }
 
 // -x.  The empty statement hides the sign flip from the compiler, which
