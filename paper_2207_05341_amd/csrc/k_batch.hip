@@ -69,6 +69,7 @@ struct BatchArgs {
   void* grad_all;
   unsigned char* scratch;
   int64_t stride;  // bytes of scratch per workgroup
+  int64_t planes;  // offset of G''s planes in it (FP32 plans with d >= kBX6MinDim)
   int nmax;
   int fast_forms;  // 1: the register-round pass forms where a plan has one; 0: generic passes
   BatchPlanTable plan;
@@ -211,30 +212,36 @@ __device__ __forceinline__ void fast_fused_form(const BatchArgs& b, int n, int f
 // Split products of the FP32 instances with d >= 128 at 512 threads (the
 // arithmetic of k_xgemm.hip: rows scaled by powers of two, two fp16 parts,
 // ten MFMA products per complex product, T T^dagger's diagonal from FP64
-// sums).  Bound by what one workgroup gets from the matrix cores: an N = 8
+// sums), where the instance's operands are dense (qst_split.h), decided by the
+// workgroup as it splits them; the FP32 tiles elsewhere.  Bound by what one
+// workgroup gets from the matrix cores: an N = 8
 // FP32 instance spent 385 of its 550 us in FP32 MFMA products at 55% of one
 // CU's rate.  Measured with every CU at work: N = 8 550 -> 400 us, and 1024
 // instances of N = 3..8 583 -> 439 us; now half of an instance's time is its
 // 9 MB of traffic between stages (256 of them exceed the caches).  The line
 // lies at d = 128, the tile; 64 x 64 instances stay on the FP32 tiles (11 of
-// their 50 us).  No scratch beyond the passes' own: T's planes take the POVM
-// intermediate's place (free until the first pass), G''s planes their own
-// (each 32-row strip is as large as its planes), T^T's planes the
-// intermediate's again (free after the last adjoint pass), the scales p's.
+// their 50 us).  T's planes take the POVM intermediate's place (free until the
+// first pass), T^T's planes the same (free after the last adjoint pass), the
+// scales p's; G''s planes have 8 bytes per entry of their own (G' stays, for
+// the FP32 tiles).
 // ---------------------------------------------------------------------------
 constexpr int kBX6MinDim = 128;
 
 // Planes of X (d x d, d = 128 or 256) as a row operand, or with COLS of X^T:
 // strips of 32 rows (columns) through LDS, the next strip's loads in flight
 // while one is split.  inv: what takes the rows' scales out; with SUMS the
-// rows' FP64 sums of |x|^2.  P may be X itself without COLS.
+// rows' FP64 sums of |x|^2.  True in every thread if X's rows (columns) are
+// dense.
 template <bool COLS, bool SUMS>
-__device__ __forceinline__ void batch_split(const Cx<float>* X, int n, u16x8* P, float* inv, double* rsum,
+__device__ __forceinline__ bool batch_split(const Cx<float>* X, int n, u16x8* P, float* inv, double* rsum,
                                             unsigned char* pool) {
   constexpr int NT = 512, UMAX = 256 * 32 / NT;
+  constexpr float kLow = float(1 << (kX6Top - kX6DenseBits));
   const int d = 1 << n, ld = d + 1, t = fresh_thread(), per = d * 32 / NT;
   Cx<float>* L = reinterpret_cast<Cx<float>*>(pool);
   float* scl = reinterpret_cast<float*>(L + 32 * ld);
+  int* big = reinterpret_cast<int*>(scl + 32);  // a row's components that reach kLow
+  int* bad = big + 32;                          // rows that are not dense, or not finite
   Cx<float> v[UMAX];
   auto load = [&](int rb) {
 #pragma unroll
@@ -247,6 +254,11 @@ __device__ __forceinline__ void batch_split(const Cx<float>* X, int n, u16x8* P,
   load(0);
   for (int rb = 0; rb < d / 32; ++rb) {
     __syncthreads();  // the pool's previous user, or the previous strip, is done
+    if (t < 32) {
+      if (rb == 0) bad[t] = 0;
+      else if (2 * big[t] < 3 * d) bad[t] = 1;  // three quarters of 2 d
+      big[t] = 0;
+    }
 #pragma unroll
     for (int u = 0; u < UMAX; ++u)
       if (u < per) {
@@ -273,6 +285,7 @@ __device__ __forceinline__ void batch_split(const Cx<float>* X, int n, u16x8* P,
       scl[row] = x6_pow2(e);
       inv[32 * rb + row] = x6_pow2(-e);
       if constexpr (SUMS) rsum[32 * rb + row] = s2;
+      if (!x6_finite(m)) bad[row] = 1;
     }
     __syncthreads();
     const int slots = (d / 16) * 64;  // 512 or 1024
@@ -285,10 +298,13 @@ __device__ __forceinline__ void batch_split(const Cx<float>* X, int n, u16x8* P,
         re[e] = x.re;
         im[e] = x.im;
       }
-      write_unit_block(P + (rb * (d / 16) + kb) * kX6BlockVecs + ln, re, im, scl[r]);
+      atomicAdd(&big[r], write_unit_block(P + (rb * (d / 16) + kb) * kX6BlockVecs + ln, re, im, scl[r], kLow));
     }
   }
   __syncthreads();
+  const bool dense = __ballot(bad[t & 31] != 0 || 2 * big[t & 31] < 3 * d) == 0;
+  __syncthreads();
+  return dense;
 }
 
 // One 128 x 128 output tile by eight waves of 64 x 32 (row half w / 4, column
@@ -456,14 +472,15 @@ __device__ __forceinline__ void batch_herk_x6(int n, double tau, Cx<float>* rho,
   }
 }
 
-// grad = scale G' T; G' (in G) is overwritten by its planes.
-__device__ __forceinline__ void batch_hemm_x6(Cx<float>* G, const Cx<float>* T, int n, double scale, Cx<float>* grad,
-                                              u16x8* tplanes, float* scales, unsigned char* pool) {
+// grad = scale G' T, or false with nothing written to grad where an operand
+// is not dense.
+__device__ __forceinline__ bool batch_hemm_x6(const Cx<float>* G, const Cx<float>* T, int n, double scale,
+                                              Cx<float>* grad, u16x8* gplanes, u16x8* tplanes, float* scales,
+                                              unsigned char* pool) {
   const int d = 1 << n;
   float *ginv = scales, *tinv = scales + 256;
-  u16x8* gplanes = reinterpret_cast<u16x8*>(G);
-  batch_split<false, false>(G, n, gplanes, ginv, nullptr, pool);
-  batch_split<true, false>(T, n, tplanes, tinv, nullptr, pool);
+  if (!batch_split<false, false>(G, n, gplanes, ginv, nullptr, pool)) return false;
+  if (!batch_split<true, false>(T, n, tplanes, tinv, nullptr, pool)) return false;
   for (int tr = 0; tr < d / 128; ++tr)
     for (int tc = 0; tc < d / 128; ++tc) {
       f16v R[2], I[2];
@@ -480,6 +497,7 @@ __device__ __forceinline__ void batch_hemm_x6(Cx<float>* G, const Cx<float>* T, 
           grad[uint32_t(r * d + c)] = Cx<float>{R[i][v] * cs * rs, I[i][v] * cs * rs};
         }
     }
+  return true;
 }
 
 // A d x d operand, d <= 32, in LDS with rows of d + 1: the per-entry product
@@ -590,9 +608,10 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
     }
     R* const scales = pvec;  // p's place: free before the passes and after the adjoint's
     double* const rsum = reinterpret_cast<double*>(scales + 256);
+    bool dense = false;
     if constexpr (kX6) {
       if (x6) {
-        batch_split<false, true>(T, n, reinterpret_cast<u16x8*>(inter), scales, rsum, pool);
+        dense = batch_split<false, true>(T, n, reinterpret_cast<u16x8*>(inter), scales, rsum, pool);
         if (t < d) acc = rsum[t];
       }
     }
@@ -600,7 +619,7 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
     const double Fsum = block_sum_bcast<NW>(facc, red, slotp);
 
     // 2. rho = T T^dagger / tau
-    if (x6) {
+    if (dense) {
       if constexpr (kX6) batch_herk_x6(n, tau, rho, reinterpret_cast<u16x8*>(inter), scales, rsum, pool);
     } else if (BF16 && d >= 64 && d <= kBf16SplitMaxDim) {
       gemm::GemmArgs g{};
@@ -781,9 +800,13 @@ __global__ __launch_bounds__(THREADS) void batch_kernel(BatchArgs b) {
 
     // 6. grad = (2/tau) G' T
     const double scale = 2.0 / tau;
-    if (x6) {
-      if constexpr (kX6)
-        batch_hemm_x6(rho, T, n, scale, grad, reinterpret_cast<u16x8*>(inter), scales, pool);
+    bool split = false;
+    if constexpr (kX6) {
+      if (x6)
+        split = batch_hemm_x6(rho, T, n, scale, grad, reinterpret_cast<u16x8*>(scr + b.planes),
+                              reinterpret_cast<u16x8*>(inter), scales, pool);
+    }
+    if (split) {
     } else if (d >= 64) {
       gemm::GemmArgs g{};
       g.A = rho;
@@ -1057,7 +1080,8 @@ qst_status qst_batch_plan_create(const int* n_qubits, int count, qst_prec prec, 
   p->threads = p->thread_options[0];
   const int64_t dmax = int64_t(1) << p->nmax, Dmax = dmax * dmax;
   const size_t cb = qst::complex_bytes(p->prec), rb = qst::real_bytes(p->prec);
-  const int64_t stride = int64_t((2 * Dmax * cb + Dmax * rb + 64 + 255) / 256 * 256);
+  const int64_t planes = int64_t((2 * Dmax * cb + Dmax * rb + 64 + 255) / 256 * 256);
+  const int64_t stride = planes + (p->prec == QST_F32 && dmax >= qst::kBX6MinDim ? Dmax * int64_t(cb) : 0);
   const int max_grid = p->cus * occ_max;
   p->max_grid = max_grid;
   e = hipMalloc(&p->d_items, sizeof(qst::BatchItem) * count);
@@ -1078,6 +1102,7 @@ qst_status qst_batch_plan_create(const int* n_qubits, int count, qst_prec prec, 
   a.counter = p->d_counter;
   a.scratch = p->d_scratch;
   a.stride = stride;
+  a.planes = planes;
   a.nmax = p->nmax;
   for (int m = 1; m <= qst::kBatchMaxQubits; ++m) {
     const qst::PovmPlan pl = qst::make_povm_plan(m, p->prec);
