@@ -638,7 +638,10 @@ size_t qst_profile_report(char* buf, size_t len, int reset);
  * given buffers and keeps the fastest; with a cache
  * file (tune_cache, else the QST_TUNE_CACHE environment variable; NULL/unset
  * = no cache) the choice is appended there and reused by later plans with
- * the same precision, POVM kind, qubit-count histogram and device.
+ * the same precision, POVM kind, qubit-count histogram and device; lines of
+ * earlier kernels are passed over.  QST_F32 plans with instances of N = 7 or
+ * 8 are timed at 512 threads only, because the workgroup size selects their
+ * products (256, which a cache line can name: FP32 MFMA products for all).
  * A plan must not be run concurrently on two streams.
  */
 typedef struct qst_batch_plan qst_batch_plan;

@@ -226,6 +226,8 @@ __device__ __forceinline__ void fast_fused_form(const BatchArgs& b, int n, int f
 // the FP32 tiles).
 // ---------------------------------------------------------------------------
 constexpr int kBX6MinDim = 128;
+// Raised when a change of the kernels makes old tuning choices untrue.
+constexpr int kBatchKernelVersion = 2;
 
 // Planes of X (d x d, d = 128 or 256) as a row operand, or with COLS of X^T:
 // strips of 32 rows (columns) through LDS, the next strip's loads in flight
@@ -889,7 +891,10 @@ hipError_t launch_batch_kernel(qst_prec prec, bool tetra, const BatchArgs& a, in
   return launch_batch_t<HerkBf16Policy, HemmBf16x3Policy, float, true, 256>(tetra, a, grid, s);
 }
 
-// The workgroup sizes a precision offers (the first is the default).
+// The workgroup sizes a precision offers (the first is the default, and the
+// only one that the autotuner times for FP32 plans with d >= kBX6MinDim: there
+// the size selects the products, and their rounding is not to depend on a
+// timing).
 std::vector<int> batch_thread_options(qst_prec prec) {
   if (prec == QST_F32) return {512, 256};
   return {256};
@@ -1119,11 +1124,13 @@ qst_status qst_batch_plan_create(const int* n_qubits, int count, qst_prec prec, 
     a.W.a[i] = W[i];
     a.V.a[i] = V[i];
   }
-  // tuning key: precision, histogram of qubit counts, device
+  // tuning key: kernel version (of another one's lines the times, and what the
+  // fields select, are no longer true), precision, histogram of qubit
+  // counts, device
   int hist[qst::kBatchMaxQubits + 1] = {0};
   for (int i = 0; i < count; ++i) ++hist[p->n[i]];
   std::ostringstream key;
-  key << "prec" << int(p->prec) << (p->tetra ? "-tetra" : "-povm") << "-n";
+  key << "v" << qst::kBatchKernelVersion << "-prec" << int(p->prec) << (p->tetra ? "-tetra" : "-povm") << "-n";
   for (int m = 1; m <= qst::kBatchMaxQubits; ++m) key << (m > 1 ? "." : "") << hist[m];
   key << "-" << device_name(p->device);
   p->key = key.str();
@@ -1172,7 +1179,8 @@ qst_status qst_batch_run(qst_batch_plan* p, const void* T_all, const void* f_all
     int best_grid = p->grid, best_threads = p->threads;
     bool best_sorted = true, best_fast = true;
     const bool has_fast = p->tetra && p->prec != QST_BF16GEMM;
-    for (size_t v = 0; v < p->thread_options.size() && e == hipSuccess; ++v) {
+    const bool one_size = p->prec == QST_F32 && (1 << p->nmax) >= qst::kBX6MinDim;
+    for (size_t v = 0; v < (one_size ? 1 : p->thread_options.size()) && e == hipSuccess; ++v) {
       const int th = p->thread_options[v];
       for (int fast = 1; fast >= (has_fast ? 0 : 1) && e == hipSuccess; --fast) {
         for (int m = 1; m <= p->occ[v] && e == hipSuccess; ++m) {
