@@ -110,11 +110,14 @@ __device__ __forceinline__ Reflector reflector(C64 al, double nrm) {
   Reflector h{al.re, C64{0.0, 0.0}, C64{0.0, 0.0}};
   if (nrm == 0.0 && al.im == 0.0) return h;
   h.beta = -copysign(sqrt(al.re * al.re + al.im * al.im + nrm), al.re);
-  // two divisions, side by side: 1 / beta and 1 / |alpha - beta|^2
-  const C64 den{al.re - h.beta, al.im};
-  const double ib = 1.0 / h.beta, id = 1.0 / (den.re * den.re + den.im * den.im);
-  h.t = C64{-den.re * ib, -al.im * ib};
-  h.sc = C64{den.re * id, -den.im * id};
+  // two divisions, side by side: 1 / beta and 1 / |alpha - beta|^2, both
+  // scaled by beta's exponent so that neither reciprocal overflows (the second
+  // did below |beta| = 7e-155, where the squares still have bits)
+  const int ex = __builtin_amdgcn_frexp_exp(h.beta);
+  const C64 den{ldexp(al.re - h.beta, -ex), ldexp(al.im, -ex)};
+  const double ib = 1.0 / ldexp(h.beta, -ex), id = 1.0 / (den.re * den.re + den.im * den.im);
+  h.t = C64{-den.re * ib, -den.im * ib};
+  h.sc = C64{ldexp(den.re * id, -ex), ldexp(-den.im * id, -ex)};
   return h;
 }
 
