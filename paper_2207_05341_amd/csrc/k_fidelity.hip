@@ -11,12 +11,14 @@
 //      8 or 16 target columns;
 //   2. fid_mreduce_kernel: M from the row-block sums, in order;
 //   3. fid_gram_kernel: C_ab = sum_j M_aj conj(M_bj), one workgroup per pair;
-//   4. fid_jacobi_kernel: tau, tw, C / Tr C, parallel cyclic Jacobi
+//   4. fid_jacobi_kernel: tau, tw, C scaled by its trace, parallel cyclic Jacobi
 //      eigenvalues of the Hermitian C (FP64, one workgroup), F_q.
 // Classical fidelity (Eq. F_CF): F_c = (sum_k sqrt(p_hat_k p_k))^2 (negative
 // entries read as 0), a two-stage FP64 reduction.
 // Every sum has a fixed order: results are bitwise reproducible.
 #include <hip/hip_runtime.h>
+
+#include <cfloat>
 
 #include "qst_device.h"
 #include "qst_kernels.h"
@@ -161,8 +163,10 @@ __global__ __launch_bounds__(256) void fid_gram_kernel(const Zd* __restrict__ M,
 }
 
 // tau and tw (the workgroup partials, in order), then the eigenvalues of
-// C / Tr C by parallel cyclic Jacobi and F_q = Tr C / (tau tw) (sum_i
-// sqrt(lambda_i))^2.  A sweep takes the r(r-1)/2 pairs in r' - 1 steps of
+// C 2^-e, e the exponent of Tr C (a power of two: 1 / Tr C overflows for a
+// trace below 5.6e-309), by parallel cyclic Jacobi and F_q = 2^e / (tau tw)
+// (sum_i sqrt(lambda_i))^2; 0 where that sum is 0, for T or W of zeros too, or
+// not finite.  A sweep takes the r(r-1)/2 pairs in r' - 1 steps of
 // r'/2 disjoint pairs (round-robin order, r' = r rounded up to even; pairs
 // with the padding index are not rotated).  The rotation of a pair (p, q)
 // with c = C_pq, h = (C_qq - C_pp) / 2 and g = 1 / sqrt(h^2 + |c|^2):
@@ -207,10 +211,11 @@ __global__ __launch_bounds__(NT) void fid_jacobi_kernel(const double* __restrict
   }
   for (int k = 0; k < ntw; ++k) tw += twp[k];
   for (int k = 0; k < r; ++k) tr += Cin[k * r + k].re;
-  const double inv = tr > 0.0 ? 1.0 / tr : 0.0;
+  const bool finite = tr <= DBL_MAX;
+  const int ex = tr > 0.0 && finite ? __builtin_amdgcn_frexp_exp(tr) : 0;
   for (int e = t; e < r * r; e += NT) {
     const Zd v = Cin[e];
-    C[e / r][e % r] = Zd{v.re * inv, v.im * inv};
+    C[e / r][e % r] = Zd{ldexp(v.re, -ex), ldexp(v.im, -ex)};
   }
   __syncthreads();
   const int rp = r + (r & 1), np = rp / 2;
@@ -297,7 +302,7 @@ __global__ __launch_bounds__(NT) void fid_jacobi_kernel(const double* __restrict
   if (t == 0) {
     double sq = 0.0;
     for (int i = 0; i < r; ++i) sq += sqrt(fmax(C[i][i].re, 0.0));
-    *F = tr / (tau * tw) * (sq * sq);
+    *F = finite && sq > 0.0 ? ldexp(sq * sq, ex) / (tau * tw) : 0.0;
   }
 }
 
