@@ -323,15 +323,10 @@ qst_status qst_likelihood_fc(int n_qubits, qst_prec prec, const void* T, int64_t
  * counters as qst_likelihood, and
  *   gradT = dL/dRe T + i dL/dIm T = (2 / tau) G' T,
  * what qst_likelihood followed by qst_grad_product (upstream 1) gives;
- * G' itself is not returned.  With QST_F32X6 from d = 128 the kernel that
- * splits T for T T^dagger also writes T^T's planes for the gradient
- * product, and where the first POVM stage covers 5 or 6 qubits
- * (tetrahedral POVM, N = 9, 10, 11, 13) the adjoint's last stage writes G'
- * directly as that product's planes.  tau, L, F and the counters equal
- * qst_likelihood's bitwise; gradT equals the two calls' bitwise, except on
- * that last route, where it agrees to rounding (the adjoint stage that
- * writes planes is a kernel instance of its own, whose sums may contract
- * into FMAs differently).
+ * G' itself is not returned.  With QST_F32X6 from d = 128, and QST_F32 from
+ * N = 10, the kernel that splits T for T T^dagger also writes T^T's planes
+ * for the gradient product.  tau, L, F and the counters equal
+ * qst_likelihood's bitwise, and gradT the two calls'.
  *   gradT    [out] d x d complex, row stride ld_grad, device; must not
  *                  overlap T.
  * Workspace: qst_workspace_bytes(N, prec, QST_OP_LIKELIHOOD_GRAD).  Other
@@ -586,7 +581,11 @@ qst_status qst_rprop_step(int64_t count, qst_prec prec, void* param, const void*
                           double eta_minus, double eta_plus, double step_min, double step_max, void* stream);
 
 /* Workspace in bytes needed by op (a qst_op) at (n_qubits, prec); 0 for an
- * invalid request. */
+ * invalid request.  The operand planes of the split products are the largest
+ * part of it: 8 bytes per entry of T for T T^dagger and 16 for G' T (QST_F32
+ * from N = 10, where G' T takes 67 MB at least), or 24 and 36 (QST_F32X6 from
+ * d = 128).  QST_OP_GRAD_PRODUCT at N = 12: 275 MB for QST_F32, 610 MB for
+ * QST_F32X6. */
 size_t qst_workspace_bytes(int n_qubits, qst_prec prec, int op);
 
 /* Static string for a status code. */

@@ -30,11 +30,10 @@ constexpr int kX6SmallTile = 64;
 inline bool x6_small_tiles(int n) { return n <= 10; }
 // QST_F32X6 from d = kX6Tile; QST_F32 from kX6F32MinQubits, where the fp16
 // products take over from the FP32 MFMA products for dense operands
-// (X6Scales): at N = 10 a likelihood and gradient takes 124 us against 153
-// us, at N = 11 356 against 673, at N = 12 2320 against 4932, with smaller
-// errors at each.  Below, a QST_F32 call would gain less (N = 9, as
-// QST_F32X6: 66 us against 100; N = 8: 59 against 64; N = 7: 49 against 43),
-// and its gradient product takes no workspace.
+// (X6Scales): at N = 10 a likelihood and gradient takes 119 us against 159
+// us, at N = 11 382 against 678, at N = 12 2258 against 4960, with smaller
+// errors at each.  Below there is little or nothing to gain: N = 9 takes 90 us
+// as QST_F32X6 against 105, N = 8 74 against 69, N = 7 62 against 48.
 constexpr int kX6F32MinQubits = 10;
 inline bool use_x6(qst_prec p, int n) {
   return (p == QST_F32X6 && (int64_t(1) << n) >= kX6Tile) || (p == QST_F32 && n >= kX6F32MinQubits);
