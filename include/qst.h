@@ -91,10 +91,12 @@ typedef enum {
    * a sign for entries down to 2^-15 of the row's largest, an absolute error
    * of 2^-38 of it below), with three partial products (hh, hl, lh: what is
    * dropped is below 2^-22 of |a||b|).  Dense: at least three quarters of the
-   * components of every piece of a row (column) are within 2^-8 (G' from
-   * d = 1024: 2^-10) of the row's (column's) largest.  Then the accumulation
-   * of many comparable terms sets the error, and it is smaller than that of
-   * the general products and of FP32 MFMA products (measured against FP64).
+   * entries of every piece of a row (column) have a component within 2^-12
+   * (d <= 512: 2^-8) of the row's (column's) largest, and an eighth of the
+   * indices contracted over have an entry within 2^-4 of the largest of all.
+   * Then the accumulation
+   * of many terms sets the error, and it is smaller than that of the general
+   * products and of FP32 MFMA products (measured against FP64).
    * Below d = 128 the products are those of QST_F32.  The batched form runs
    * it as QST_F32, whose instances with d >= 128 take the fp16 split products
    * (at 512 threads). */

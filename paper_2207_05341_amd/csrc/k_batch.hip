@@ -238,11 +238,11 @@ template <bool COLS, bool SUMS>
 __device__ __forceinline__ bool batch_split(const Cx<float>* X, int n, u16x8* P, float* inv, double* rsum,
                                             unsigned char* pool) {
   constexpr int NT = 512, UMAX = 256 * 32 / NT;
-  constexpr float kLow = float(1 << (kX6Top - kX6DenseBits));
+  constexpr float kLow = x6_dense_low(8);
   const int d = 1 << n, ld = d + 1, t = fresh_thread(), per = d * 32 / NT;
   Cx<float>* L = reinterpret_cast<Cx<float>*>(pool);
   float* scl = reinterpret_cast<float*>(L + 32 * ld);
-  int* big = reinterpret_cast<int*>(scl + 32);  // a row's components that reach kLow
+  int* big = reinterpret_cast<int*>(scl + 32);  // a row's entries that reach kLow
   int* bad = big + 32;                          // rows that are not dense, or not finite
   Cx<float> v[UMAX];
   auto load = [&](int rb) {
@@ -258,7 +258,7 @@ __device__ __forceinline__ bool batch_split(const Cx<float>* X, int n, u16x8* P,
     __syncthreads();  // the pool's previous user, or the previous strip, is done
     if (t < 32) {
       if (rb == 0) bad[t] = 0;
-      else if (2 * big[t] < 3 * d) bad[t] = 1;  // three quarters of 2 d
+      else if (4 * big[t] < 3 * d) bad[t] = 1;
       big[t] = 0;
     }
 #pragma unroll
@@ -304,7 +304,7 @@ __device__ __forceinline__ bool batch_split(const Cx<float>* X, int n, u16x8* P,
     }
   }
   __syncthreads();
-  const bool dense = __ballot(bad[t & 31] != 0 || 2 * big[t & 31] < 3 * d) == 0;
+  const bool dense = __ballot(bad[t & 31] != 0 || 4 * big[t & 31] < 3 * d) == 0;
   __syncthreads();
   return dense;
 }

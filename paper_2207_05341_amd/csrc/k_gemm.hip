@@ -29,6 +29,7 @@
 #include "qst_gemm_tiles.h"
 #include "qst_kernels.h"
 #include "qst_plan.h"
+#include "qst_split.h"
 
 namespace qst {
 
@@ -52,7 +53,7 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& g, int tr, int tc, t
 }
 
 __device__ __forceinline__ bool gemm_off(const GemmArgs& g) {
-  return g.gate[0] && !(*g.gate[0] | *g.gate[1]);
+  return g.gate.bad[0] && !x6_sparse(g.gate);
 }
 
 // One tile per workgroup.
@@ -430,10 +431,7 @@ hipError_t launch_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int
   g.partial = sk_partial;
   g.tau_part = tau_partials;
   g.tau_out = tau_partials ? tau_dev : nullptr;
-  if (gate) {
-    g.gate[0] = gate->bad[0];
-    g.gate[1] = gate->bad[1];
-  }
+  if (gate) g.gate = *gate;
   const bool use_planes = prec == QST_BF16GEMM && d > kBf16SplitMaxDim && planes;
   if (use_planes) {  // operands: bf16 planes of T, row stride d
     g.A = planes;
@@ -670,8 +668,7 @@ hipError_t launch_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T,
   g.partial = sk_partial;
   g.tau_part = nullptr;
   g.tau_out = nullptr;
-  g.gate[0] = gate.bad[0];
-  g.gate[1] = gate.bad[1];
+  g.gate = gate;
   if (prec == QST_F64) return run_gemm<CxPolicy<double, false>>(g, s);
   if (prec == QST_F32) return run_gemm<CxPolicy<float, false>>(g, s);
   if (planes && d % (8 * kWideBM) == 0) {

@@ -16,19 +16,18 @@
 // are more accurate than FP32's where the accumulation of many comparable
 // terms sets the error, and less where a few terms carry an entry or large
 // entries of one operand meet small ones of the other.  So the split counts
-// the components near the largest of their row (column), and the fp16
-// products are stored only where both operands are dense by that count
-// (kX6DenseBits; three quarters of the components, so that in every sum at
-// least half of the terms have both factors near their largest).  Elsewhere
-// QST_F32 runs its FP32 MFMA products (k_gemm.hip) and QST_F32X6 the exact
-// three-part bf16 split (k_xgemm3.hip).  The choice is a pair of flags in
-// device memory that every kernel of either kind reads first: no host
+// the entries near the largest of their row (column), and the indices of the
+// contraction near the largest, and the fp16 products are stored only where
+// both operands are dense by those counts (qst_split.h, with the reasons).
+// Elsewhere QST_F32 runs its FP32 MFMA products (k_gemm.hip) and QST_F32X6 the
+// exact three-part bf16 split (k_xgemm3.hip).  The counts are in device
+// memory (X6Gate), and every kernel of either kind reads them first: no host
 // decision, and a captured call chooses again at each replay.  Relative errors
-// against FP64 at N = 10 or 11, old product of QST_F32 / of QST_F32X6 / fp16:
-// Gaussian T, G' T 1.1e-6 / 5.0e-7 / 2.5e-7; one nonzero column of T, rho
-// 7e-8 / 1.0e-7 / 1.3e-7; T = D^-1 X and G' = D A D with D within 2^+-12,
-// 8e-7 / 5.0e-7 / 1.5e-5.  The kernels that find themselves unused cost 2 to
-// 4 us each.
+// against FP64 at N = 10 or 11, FP32 MFMA / bf16 / fp16 products: Gaussian T,
+// G' T 1.1e-6 / 5.0e-7 / 2.2e-7; one nonzero column of T, rho 7e-8 / 1.0e-7 /
+// 1.3e-7; T = D^-1 X and G' = D A D with D within 2^+-12, 8e-7 / 5.0e-7 /
+// 1.5e-5.  A kernel that finds itself unused takes 4.6 us, a launch and a load
+// that misses: four of them in a QST_F32X6 step, three or four in a QST_F32 one.
 //
 // Complex products: ten MFMA products per 32 x 32 block and K panel.  The
 // leading part h h takes the four real products of the definition.  Each of
@@ -91,6 +90,7 @@ constexpr int XCOPY = 8;              // units copied per wave and slab
 constexpr int XLDS = XSLOT * XNSLOT;  // 131072 bytes of LDS
 
 static_assert((XDIST - 1) * XCOPY < 64, "vmcnt immediate");
+static_assert(kX6MaxBlocks >= kReduceBlocks, "one maximum per workgroup");
 
 // ---------------------------------------------------------------------------
 // Scales and split (helpers in qst_split.h)
@@ -111,13 +111,13 @@ static_assert((XDIST - 1) * XCOPY < 64, "vmcnt immediate");
 // steps finish it (nine shuffles in place of forty).
 template <bool TAU, bool WITH_F>
 __device__ __forceinline__ void x6_absmax(const Cx<float>* __restrict__ X, int64_t ld, int d, float* __restrict__ rowp,
-                                          float* __restrict__ colp, int* __restrict__ bad,
+                                          float* __restrict__ colp, float* __restrict__ wmax, int* __restrict__ flags,
                                           double* __restrict__ partials, const float* __restrict__ f) {
   constexpr int NT = 256, U = 16;
   __shared__ double red[4];
   __shared__ float cm[8][64];
   const int nb = gridDim.x, t = threadIdx.x;
-  if (blockIdx.x == 0 && t < 2) bad[t] = 0;  // the split that follows sets them
+  if (blockIdx.x == 0 && t < 4) flags[t] = 0;  // the split that follows sets them
   const int64_t D = int64_t(d) * d;
   const int64_t fbeg = D * blockIdx.x / nb, fend = D * (blockIdx.x + 1) / nb;
   float fv[U];
@@ -129,6 +129,7 @@ __device__ __forceinline__ void x6_absmax(const Cx<float>* __restrict__ X, int64
     }
   }
   double acc = 0.0, accf = 0.0;
+  float top = 0.f;
   const int tiles = d / 64, c2 = t & 31, rq = t >> 5;
   for (int tile = blockIdx.x; tile < tiles * tiles; tile += nb) {
     const int tr = tile / tiles, tc = tile % tiles;
@@ -172,8 +173,14 @@ __device__ __forceinline__ void x6_absmax(const Cx<float>* __restrict__ X, int64
 #pragma unroll
       for (int q = 1; q < 8; ++q) c = fmaxf(c, cm[q][t]);
       colp[int64_t(tr) * d + tc * 64 + t] = c;
+      top = fmaxf(top, c);
     }
     __syncthreads();
+  }
+  if (t < 64) {  // the wave that folded the columns
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) top = fmaxf(top, __shfl_xor(top, o, 64));
+    if (t == 0) wmax[blockIdx.x] = top;
   }
   if constexpr (WITH_F) {
 #pragma unroll
@@ -204,7 +211,7 @@ template <bool WITH_F>
 __global__ __launch_bounds__(256) void x6_absmax_t_kernel(const Cx<float>* __restrict__ T, int64_t ld, int d,
                                                           X6Scales sc, double* __restrict__ partials,
                                                           const float* __restrict__ f) {
-  x6_absmax<true, WITH_F>(T, ld, d, sc.rowp, sc.colp, sc.bad, partials, f);
+  x6_absmax<true, WITH_F>(T, ld, d, sc.rowp, sc.colp, sc.wmax, sc.bad, partials, f);
 }
 
 // G' (blockIdx.y 0) and T (1), for G' T: one launch for both.
@@ -213,11 +220,11 @@ struct X6Pair {
   int64_t ld[2];
   X6Scales sc[2];
   u16x8* P[2];
-  float low[2];
+  float low;
 };
 __global__ __launch_bounds__(256) void x6_absmax_gt_kernel(X6Pair p, int d) {
   const int y = blockIdx.y;
-  x6_absmax<false, false>(p.X[y], p.ld[y], d, p.sc[y].rowp, p.sc[y].colp, p.sc[y].bad, nullptr, nullptr);
+  x6_absmax<false, false>(p.X[y], p.ld[y], d, p.sc[y].rowp, p.sc[y].colp, p.sc[y].wmax, p.sc[y].bad, nullptr, nullptr);
 }
 
 // The planes of X as a row operand (ROWS; row r scaled by its largest
@@ -230,9 +237,9 @@ __global__ __launch_bounds__(256) void x6_absmax_gt_kernel(X6Pair p, int d) {
 // LDS (8 KB per wave, 16-byte chunks swizzled by row) and reads the two unit
 // blocks of X^T (lane u: column u % 32, rows 16 h + 8 (u / 32) .. + 7).
 // With SUMS also the FP64 sums of |x|^2 over the 128 columns of each row.
-// Where less than three quarters of the scaled components of a 128-entry
-// piece of a row (32-entry piece of a column) reach low, the flag bad[0]
-// (bad[1]) is set: the operand is not dense.
+// Where less than three quarters of the entries of a 128-entry piece of a row
+// (32-entry piece of a column) have a scaled component that reaches low, the
+// flag bad[0] (bad[1]) is set: the operand is not dense.
 // Bound by HBM: X read, 8 bytes per element and operand written.
 __device__ __forceinline__ int split_swz(int r, int c) {  // (r, c) of a 32 x 32 block, complex index
   return r * 32 + 2 * (((c >> 1) ^ r) & 15) + (c & 1);
@@ -240,12 +247,13 @@ __device__ __forceinline__ int split_swz(int r, int c) {  // (r, c) of a 32 x 32
 
 template <bool ROWS, bool COLS, bool SUMS>
 __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_t ld, int d, const X6Scales& sc6,
-                                         u16x8* __restrict__ P, u16x8* __restrict__ PT, float low) {
+                                         u16x8* __restrict__ P, u16x8* __restrict__ PT, float low, int nmax) {
   const float *rowp = sc6.rowp, *colp = sc6.colp;
   __shared__ Cx<float> blkL[COLS ? 4 : 1][COLS ? 32 * 32 : 1];
   __shared__ float rm[8][32], cmx[2][128], rsc[32], csc[128];
   __shared__ double rs[SUMS ? 4 : 1][32];
   __shared__ int big[ROWS ? 4 : 1][32];
+  __shared__ float tops[4];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int row = lane & 31, hq = lane >> 5;
   const int nkb = d / 16, nb32 = d / 32, np = d / 64;
@@ -255,17 +263,41 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[h][e] = X[(32 * br + row) * ld + 32 * bc + 16 * h + 8 * hq + e];
-  if constexpr (ROWS) {
+  // the first workgroups of either direction count the rows and columns near
+  // the largest, whichever operand this is
+  const bool rows = ROWS || bc0 == 0, cols = COLS || br == 0;
+  if (bc0 == 0 || br == 0) {
+    float m = 0.f;
+    for (int k = t; k < nmax; k += 256) m = fmaxf(m, sc6.wmax[k]);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if (lane == 0) tops[wv] = m;
+  }
+  if (rows) {
     float m = 0.f;
     for (int k = t >> 5; k < np; k += 8) m = fmaxf(m, rowp[int64_t(k) * d + 32 * br + (t & 31)]);
     rm[t >> 5][t & 31] = m;
   }
-  if constexpr (COLS) {
+  if (cols) {
     float m = 0.f;
     for (int k = t >> 7; k < np; k += 2) m = fmaxf(m, colp[int64_t(k) * d + 32 * bc0 + (t & 127)]);
     cmx[t >> 7][t & 127] = m;
   }
   __syncthreads();
+  if (bc0 == 0 && t < 64) {
+    float m = rm[0][t & 31];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) m = fmaxf(m, rm[q][t & 31]);
+    const float top = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
+    const int n = __popcll(__ballot(t < 32 && m >= kX6Near * top));
+    if (t == 0) atomicAdd(&sc6.near[0], n);
+  }
+  if (br == 0 && t >= 128) {
+    const float m = fmaxf(cmx[0][t - 128], cmx[1][t - 128]);
+    const float top = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
+    const int n = __popcll(__ballot(m >= kX6Near * top));
+    if (lane == 0) atomicAdd(&sc6.near[1], n);
+  }
   if constexpr (ROWS) {
     if (t < 32) {
       float m = rm[0][t];
@@ -321,7 +353,7 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
     n += __shfl_xor(n, 32, 64);
     if (lane < 32) big[wv][lane] = n;
     __syncthreads();
-    if (t < 32 && 4 * (big[0][t] + big[1][t] + big[2][t] + big[3][t]) < 3 * 256) sc6.bad[0] = 1;
+    if (t < 32 && 4 * (big[0][t] + big[1][t] + big[2][t] + big[3][t]) < 3 * 128) sc6.bad[0] = 1;
   }
   if constexpr (COLS) {
     const float sc = csc[32 * wv + row];
@@ -338,7 +370,7 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
       n += write_unit_block(PT + (bc * nkb + 2 * br + h) * kX6BlockVecs + lane, re, im, sc, low);
     }
     n += __shfl_xor(n, 32, 64);
-    if (4 * n < 3 * 64) sc6.bad[1] = 1;
+    if (4 * n < 3 * 32) sc6.bad[1] = 1;
   }
 }
 
@@ -346,13 +378,13 @@ __device__ __forceinline__ void x6_split(const Cx<float>* __restrict__ X, int64_
 template <bool TT>
 __global__ __launch_bounds__(256) void x6_split_t_kernel(const Cx<float>* __restrict__ T, int64_t ld, int d, X6Scales sc,
                                                          u16x8* __restrict__ P, u16x8* __restrict__ PT, float low) {
-  x6_split<true, TT, true>(T, ld, d, sc, P, PT, low);
+  x6_split<true, TT, true>(T, ld, d, sc, P, PT, low, kReduceBlocks);
 }
 
 // G' (blockIdx.y 0) and T^T (1) for G' T.
-__global__ __launch_bounds__(256) void x6_split_gt_kernel(X6Pair p, int d) {
-  if (blockIdx.y == 0) x6_split<true, false, false>(p.X[0], p.ld[0], d, p.sc[0], p.P[0], nullptr, p.low[0]);
-  else x6_split<false, true, false>(p.X[1], p.ld[1], d, p.sc[1], nullptr, p.P[1], p.low[1]);
+__global__ __launch_bounds__(256) void x6_split_gt_kernel(X6Pair p, int d, int nmax) {
+  if (blockIdx.y == 0) x6_split<true, false, false>(p.X[0], p.ld[0], d, p.sc[0], p.P[0], nullptr, p.low, nmax);
+  else x6_split<false, true, false>(p.X[1], p.ld[1], d, p.sc[1], nullptr, p.P[1], p.low, nmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -979,7 +1011,7 @@ hipError_t x6_launch_fixup(const XArgs& a, int x0g, hipStream_t s) {
 
 hipError_t launch_x6_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int64_t ldr, int n,
                           double* tau_partials, const void* f, double* tau_dev, void* planes, void* partials,
-                          hipStream_t s, const Pass0Out* x0, void* tt_planes) {
+                          hipStream_t s, const Pass0Out* x0, void* tt_planes, X6Gate* sparse) {
   const int d = 1 << n;
   if (d < kX6Tile || !tau_partials) return hipErrorInvalidValue;
   if (x0 && (x0->g < 4 || x0->g > 6 || !x0->tetra)) return hipErrorInvalidValue;
@@ -991,7 +1023,7 @@ hipError_t launch_x6_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, 
     const Cx<float>* Tf = static_cast<const Cx<float>*>(T);
     const float* ff = static_cast<const float*>(f);
     u16x8* PT = static_cast<u16x8*>(tt_planes);
-    const float low = x6_dense_low(kX6DenseBits);
+    const float low = x6_dense_low(n);
     if (f) x6_absmax_t_kernel<true><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc, tau_partials, ff);
     else x6_absmax_t_kernel<false><<<kReduceBlocks, 256, 0, s>>>(Tf, ldt, d, sc, tau_partials, ff);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1004,7 +1036,8 @@ hipError_t launch_x6_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, 
   XArgs a{};
   a.A = P;
   a.B = P;
-  a.bad[0] = a.bad[1] = sc.bad;  // T's rows on both sides
+  a.gate = X6Gate{{sc.bad, sc.bad}, {sc.near + 1, sc.near + 1}, d / 8};  // T's rows on both sides
+  if (sparse) *sparse = a.gate;
   a.when = kX6Dense;
   a.sa = sc.rinv;
   a.sb = sc.rinv;
@@ -1049,13 +1082,13 @@ hipError_t launch_x6_hemm(qst_prec prec, const void* G, int64_t ldg, const void*
                  {ldg, ldt},
                  {x6_hemm_scales(planes, n, 0), t_ready ? *t_ready : x6_hemm_scales(planes, n, 1)},
                  {PG, PT},
-                 {x6_dense_low(kX6DenseBits + (n >= 10 ? 2 : 0)), x6_dense_low(kX6DenseBits)}};
+                 x6_dense_low(n)};
   {
     ProfScope prof("x6_split_gt", s);
     const unsigned mg = unsigned(std::min<int64_t>(kReduceBlocks, int64_t(d / 64) * (d / 64))), ny = t_ready ? 1 : 2;
     x6_absmax_gt_kernel<<<dim3(mg, ny), 256, 0, s>>>(p, d);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    x6_split_gt_kernel<<<dim3(x6_split_grid(d), ny), 256, 0, s>>>(p, d);
+    x6_split_gt_kernel<<<dim3(x6_split_grid(d), ny), 256, 0, s>>>(p, d, int(mg));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const bool small = x6_small_tiles(n);
@@ -1064,8 +1097,8 @@ hipError_t launch_x6_hemm(qst_prec prec, const void* G, int64_t ldg, const void*
   XArgs a{};
   a.A = PG;
   a.B = PT;
-  a.bad[0] = p.sc[0].bad;
-  a.bad[1] = p.sc[1].bad + 1;
+  a.gate = X6Gate{{p.sc[0].bad, p.sc[1].bad + 1}, {p.sc[0].near + 1, p.sc[1].near}, d / 8};
+  if (sparse) *sparse = a.gate;
   a.when = kX6Dense;
   a.sa = p.sc[0].rinv;
   a.sb = p.sc[1].cinv;
@@ -1082,7 +1115,6 @@ hipError_t launch_x6_hemm(qst_prec prec, const void* G, int64_t ldg, const void*
                           prof.start(), prof.stop(), 0, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (sparse) *sparse = X6Gate{{a.bad[0], a.bad[1]}};
   if (prec == QST_F32) return hipSuccess;
   return x3_launch_hemm(a, G, ldg, T, ldt, PG, p.sc[0].rinv, p.sc[1].cinv, s);
 }

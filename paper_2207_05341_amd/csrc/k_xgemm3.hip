@@ -1,5 +1,5 @@
-// Split products of QST_F32X6 where an operand is not dense (X6Scales::bad;
-// k_xgemm.hip says why): every FP32 operand as three bf16 parts,
+// Split products of QST_F32X6 where an operand is not dense (qst_split.h says
+// what that is): every FP32 operand as three bf16 parts,
 // x = h + m + l exactly, with FP32's exponent range (qst_split.h).
 //
 // A real product a b keeps hh + hm + mh + hl + lh + mm, each exact in FP32;
@@ -39,11 +39,11 @@ struct X3Split {
   int64_t ld[2];
   u16x8* P[2];
   float* inv[2];
-  const int* bad[2];
+  X6Gate gate;
 };
 template <int NG>
 __global__ __launch_bounds__(256) void x3_split_kernel(X3Split p, int d) {
-  if (!(*p.bad[0] | *p.bad[1])) return;
+  if (!x6_sparse(p.gate)) return;
   const int y = blockIdx.y;
   const Cx<float>* X = p.X[y];
   const int64_t ld = p.ld[y];
@@ -257,8 +257,7 @@ hipError_t x3_launch_herk(XArgs a, const void* T, int64_t ldt, int x0g, void* pl
   p.ld[0] = ldt;
   p.P[0] = static_cast<u16x8*>(planes);
   p.inv[0] = rinv;
-  p.bad[0] = a.bad[0];
-  p.bad[1] = a.bad[1];
+  p.gate = a.gate;
   x3_split_kernel<4><<<x3_split_grid(a.d), 256, 0, s>>>(p, a.d);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -277,7 +276,7 @@ hipError_t x3_launch_hemm(XArgs a, const void* G, int64_t ldg, const void* T, in
             {ldg, ldt},
             {P, P + size_t(a.d) * a.d * (kX3HemmBytes / 2) / sizeof(u16x8)},
             {ginv, tinv},
-            {a.bad[0], a.bad[1]}};
+            a.gate};
   x3_split_kernel<3><<<dim3(x3_split_grid(a.d), 2), 256, 0, s>>>(p, a.d);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -39,11 +39,10 @@ hipError_t run_state_map(qst_prec prec, const void* T, int64_t ldT, void* rho, i
                          double* partials, double* tau_dev, void* sk, hipStream_t s, const void* f = nullptr,
                          const Pass0Out* x0 = nullptr, void* planes = nullptr, void* ttplanes = nullptr) {
   if (use_x6(prec, n)) {
+    X6Gate gate{};
     const hipError_t e =
-        launch_x6_herk(prec, T, ldT, rho, ldr, n, partials, f, tau_dev, planes, sk, s, x0, ttplanes);
+        launch_x6_herk(prec, T, ldT, rho, ldr, n, partials, f, tau_dev, planes, sk, s, x0, ttplanes, &gate);
     if (e != hipSuccess || prec == QST_F32X6) return e;
-    const int* bad = x6_herk_scales(planes, n).bad;  // T's rows on both sides
-    const X6Gate gate{{bad, bad}};
     return launch_herk(prec, T, ldT, rho, ldr, n, partials, tau_dev, sk, s, x0, nullptr, &gate);
   }
   const bool fold = n >= 6;

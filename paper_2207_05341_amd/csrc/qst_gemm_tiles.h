@@ -32,7 +32,7 @@ struct GemmArgs {
   void* partial;  // stream-K partial accumulators [P][2][2 * TILE] (acc scalar)
   const double* tau_part;  // HERK: FP64 partial sums of tau (kReduceBlocks), or NULL to read *tau
   double* tau_out;         // HERK with tau_part: where workgroup 0 stores tau
-  const int* gate[2];      // run only where one of these flags is set (gate[0] NULL: always)
+  X6Gate gate;             // run only where x6_sparse (gate.bad[0] NULL: always)
   // HERK with the first POVM pass in the epilogue (kernels instantiated with
   // X0; tetrahedral POVM): a finished tile of rho is not stored; the pass
   // over its x0g lowest qubits is applied to each of its 2^x0g x 2^x0g

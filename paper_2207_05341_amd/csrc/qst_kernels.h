@@ -126,11 +126,8 @@ struct Pass0Out {
 };
 // planes: the bf16 planes of T written by launch_tau (BF16 path, d >
 // kBf16SplitMaxDim), or NULL to round T inside the product.
-// gate: run only where one of its flags is set when the kernels start (the
-// split products have done the others), or NULL.
-struct X6Gate {
-  const int* bad[2];
-};
+// gate: run only where it is closed to the split products when the kernels
+// start, or NULL.
 hipError_t launch_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int64_t ldr, int n,
                        const double* tau_partials, double* tau_dev, void* sk_partial, hipStream_t s,
                        const Pass0Out* x0 = nullptr, const void* planes = nullptr, const X6Gate* gate = nullptr);
@@ -163,11 +160,10 @@ hipError_t launch_small_likelihood(qst_prec prec, int n, bool tetra, const void*
 // G' T: planes x6_hemm_bytes; with t_ready (the X6Scales of that T) T^T's
 // planes are there already, after G''s; as launch_hemm otherwise.
 // QST_F32: where an operand is not dense nothing is stored, and the caller
-// launches the FP32 MFMA product with the X6Gate (launch_herk's gate is T's
-// X6Scales::bad[0]).
+// launches the FP32 MFMA product with the X6Gate.
 hipError_t launch_x6_herk(qst_prec prec, const void* T, int64_t ldt, void* rho, int64_t ldr, int n,
                           double* tau_partials, const void* f, double* tau_dev, void* planes, void* partials,
-                          hipStream_t s, const Pass0Out* x0, void* tt_planes = nullptr);
+                          hipStream_t s, const Pass0Out* x0, void* tt_planes, X6Gate* sparse);
 hipError_t launch_x6_hemm(qst_prec prec, const void* G, int64_t ldg, const void* T, int64_t ldt, void* out,
                           int64_t ldo, int n, const double* tau_dev, const double* upstream_dev, void* planes,
                           hipStream_t s, const X6Scales* t_ready, X6Gate* sparse);

@@ -107,23 +107,35 @@ inline size_t x6_partial_bytes(int n) {
 // What the split of a matrix leaves: the largest component of every 64-entry
 // piece of a row and of a column ([d / 64][d] floats each), what takes the
 // scale of each row and of each column out again ([d] floats each), the FP64
-// sum of |x|^2 over every 128-entry piece of a row ([d / 128][d]), and two
-// flags: rows (bad[0]) or columns (bad[1]) that are not dense (k_xgemm.hip),
-// whose products are left to the general kernels.
+// sum of |x|^2 over every 128-entry piece of a row ([d / 128][d]), the largest
+// component by workgroup of the kernel that looks for them, and what decides
+// which products run (qst_split.h): flags for rows (bad[0]) or columns
+// (bad[1]) that are not dense, and how many rows (near[0]) and columns
+// (near[1]) come near the largest one.
 struct X6Scales {
   double* rsum;
-  float *rowp, *colp, *rinv, *cinv;
-  int* bad;
+  float *rowp, *colp, *rinv, *cinv, *wmax;
+  int *bad, *near;
+};
+constexpr int kX6MaxBlocks = 1024;  // entries of wmax
+// Read by a kernel when it starts: are the operands' rows (columns) not dense,
+// or fewer than `least` indices of the contraction near the largest?
+struct X6Gate {
+  const int* bad[2];
+  const int* near[2];
+  int least;
 };
 inline size_t x6_scale_bytes(int n) {
   const size_t d = size_t(1) << n;
-  return (d / 128) * d * sizeof(double) + (2 * (d / 64) * d + 2 * d) * sizeof(float) + 256;
+  return (d / 128) * d * sizeof(double) + (2 * (d / 64) * d + 2 * d + kX6MaxBlocks) * sizeof(float) + 256;
 }
 inline X6Scales x6_scales_of(void* base, int n) {
   const size_t d = size_t(1) << n, np = (d / 64) * d;
   double* r = static_cast<double*>(base);
   float* b = reinterpret_cast<float*>(r + (d / 128) * d);
-  return X6Scales{r, b, b + np, b + 2 * np, b + 2 * np + d, reinterpret_cast<int*>(b + 2 * np + 2 * d)};
+  float* w = b + 2 * np + 2 * d;
+  int* flags = reinterpret_cast<int*>(w + kX6MaxBlocks);
+  return X6Scales{r, b, b + np, b + 2 * np, b + 2 * np + d, w, flags, flags + 2};
 }
 // Operand planes, after the scales: for the fp16 products re and im in two
 // parts each (8 bytes per element of T for T T^dagger; of G', then T^T, for

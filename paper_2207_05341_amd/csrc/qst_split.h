@@ -20,6 +20,7 @@
 #pragma once
 
 #include "qst_device.h"
+#include "qst_plan.h"
 
 namespace qst {
 
@@ -41,14 +42,32 @@ __device__ __forceinline__ bool x6_finite(float m) { return m <= 3.402823466e38f
 __device__ __forceinline__ float x6_pow2(int e) { return __builtin_amdgcn_ldexpf(1.0f, e); }
 // top of the scaled range: sums of two components of a row stay below 2^15
 constexpr int kX6Top = 13;
-// An operand is dense where at least three quarters of the components of
-// every piece of a row (column) are not below the row's (column's) largest by
-// more than 2^-bits: 8, but 10 for G' from d = 1024, whose entries fall off
-// with the Hamming distance of row and column (of Gaussian states, least
-// fraction of any 128-entry piece within 2^-8: 0.87 at N = 9, 0.52 at N = 13;
-// within 2^-10: 0.92 at N = 10, 0.85 at N = 13).
-constexpr int kX6DenseBits = 8;
-inline float x6_dense_low(int bits) { return float(1 << (kX6Top - bits)); }
+// An operand is dense where at least three quarters of the entries of every
+// piece of a row (column) have a component not below 2^-bits of the row's
+// (column's) largest.  Two dense operands then have at least half of the
+// terms of every sum of their product with both factors that large, and
+// FP32 accumulation, which rounds at every one of them, loses more than the
+// split does per term: sqrt(d / 4) roundings of the partial sums against
+// about four of the terms.  12 bits are the most that leaves such terms above
+// 2^-24 of the largest product (and an entry all its 22 bits); at d = 128 to
+// 512, where d / 4 is not many, 8, which is what a heavy last column needs.  Least
+// fraction of any piece within 2^-12 at N = 10 and 11: Gaussian T 0.97, the
+// absolute map's T 0.91 (its diagonal is 2^5 above the rest), G' 0.94 for
+// three Pauli bases, 0.98 for Gaussian T; within 2^-8 those fall to 0.94,
+// 0.41, 0.32 and 0.91.
+// Besides, at least an eighth of the indices of the contraction (columns of T
+// for T T^dagger; columns of G' and rows of T for G' T) have their largest
+// component within 2^-4 of the largest of all: else a few terms carry every
+// sum, and FP32 rounds it little where they come last (the last column of T
+// 2^7 above the rest, N = 10: 7.6e-8 against 1.5e-7).
+constexpr float kX6Near = 1.f / 16.f;
+__device__ __forceinline__ bool x6_sparse(const X6Gate& g) {
+  // all four loads in flight together: they miss the caches in every kernel
+  const int b0 = *g.bad[0], b1 = *g.bad[1], n0 = *g.near[0], n1 = *g.near[1];
+  return (b0 | b1 | int(n0 < g.least) | int(n1 < g.least)) != 0;
+}
+constexpr int x6_dense_bits(int n) { return n >= 10 ? 12 : 8; }
+constexpr float x6_dense_low(int n) { return float(1 << (kX6Top - x6_dense_bits(n))); }
 
 // H + L = the split of sc * x, eight values.
 __device__ __forceinline__ void split2(const float (&x)[8], float sc, u16x8& H, u16x8& L) {
@@ -65,14 +84,14 @@ __device__ __forceinline__ void split2(const float (&x)[8], float sc, u16x8& H, 
 
 // One lane's slot of a unit block: 8 values (re, im) scaled by sc, two
 // parts each.  out points at the unit block's first unit plus the lane.
-// Returns how many of the 16 scaled components are not below low.
+// Returns how many of the 8 values have a scaled component not below low.
 __device__ __forceinline__ int write_unit_block(u16x8* out, const float (&re)[8], const float (&im)[8], float sc,
                                                 float low = 0.f) {
   split2(re, sc, out[0 * kX6UnitVecs], out[1 * kX6UnitVecs]);
   split2(im, sc, out[2 * kX6UnitVecs], out[3 * kX6UnitVecs]);
   int n = 0;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) n += int(fabsf(re[e] * sc) >= low) + int(fabsf(im[e] * sc) >= low);
+  for (int e = 0; e < 8; ++e) n += int(fmaxf(fabsf(re[e]), fabsf(im[e])) * sc >= low);
   return n;
 }
 

@@ -19,14 +19,13 @@ namespace qst {
 constexpr int XT = kX6Tile;  // output tile (complex)
 constexpr int XUNIT = kX6UnitVecs;
 
-// When a kernel of a launch sequence runs: the flags that the split of the
-// operands left (X6Scales::bad) are read by the kernel itself.
+// When a kernel of a launch sequence runs; it reads the gate itself.
 enum X6When { kX6Dense, kX6Sparse, kX6Always };
 
 struct XArgs {
   const u16x8* A;  // planes of the row operand
   const u16x8* B;  // planes of the column operand (rows of B^T)
-  const int* bad[2];  // flags of the two operands
+  X6Gate gate;
   X6When when;
   const float* sa;  // what takes A's row scales out again
   const float* sb;  // the same for B's rows (the output's columns)
@@ -46,7 +45,7 @@ struct XArgs {
 };
 
 __device__ __forceinline__ bool x6_off(const XArgs& a) {
-  return a.when != kX6Always && ((*a.bad[0] | *a.bad[1]) != 0) != (a.when == kX6Sparse);
+  return a.when != kX6Always && x6_sparse(a.gate) != (a.when == kX6Sparse);
 }
 
 constexpr int kXTileVals = XT * XT;  // complex values per tile

@@ -6,7 +6,8 @@ G' = D A D, D within 2^+-12).  Each precision against FP64.
 Tolerances.  One or four columns, QST_F32, entry by entry: each of re and im
 is a sum of 2 and 8 products; one rounding each, at most, for the product and
 its addition, the scale and the result, 2^-24 of the absolute sum: 4 and 10
-units of it, times sqrt 2 for the modulus.  Otherwise the relative Frobenius
+units of it, times sqrt 2 for the modulus.  A last column 2^7 above the rest: an
+entry is the last term added, so two roundings of 2^-24, 2^-23.  Otherwise the relative Frobenius
 error: K terms of random sign rounded (FP32) or truncated (bf16 MFMA, six
 products, three real products per complex one) at every step lose at most
 about 2^-24 sqrt(K) = 2^-18.5 at K = 2048; 2^-19 is between that bound and
@@ -38,6 +39,8 @@ def operands(n, pattern):
     elif pattern == "opposing":
         D = 2.0 ** g.integers(-12, 13, size=d)
         T, A = T / D[:, None], D[:, None] * A * D[None, :]
+    elif pattern == "last":  # one column far above the rest, in last place
+        T[:, -1] *= 2.0 ** 7
     elif pattern == "mixed":  # G' dense, T not
         T[d // 2:] *= 2.0 ** -12
     T, G = T.astype(np.complex64), (A + A.conj().T).astype(np.complex64)
@@ -55,7 +58,7 @@ def abs1(x):
 CASES = [(n, "f32x6") for n in (7, 8, 9, 10, 11)] + [(n, "f32") for n in (8, 10, 11)]
 
 
-@pytest.mark.parametrize("pattern", ["columns1", "columns4", "lower", "opposing", "mixed"])
+@pytest.mark.parametrize("pattern", ["columns1", "columns4", "lower", "opposing", "mixed", "last"])
 @pytest.mark.parametrize("n,prec", CASES)
 def test_products_of_operands_that_are_not_dense(n, prec, pattern):
     print(f"products n={n} {prec} {pattern}", flush=True)
@@ -70,6 +73,8 @@ def test_products_of_operands_that_are_not_dense(n, prec, pattern):
         units = 4 if pattern == "columns1" else 10
         bound = (abs1(T64) @ abs1(T64).T.contiguous()) / tau64
         assert bool(((rho.to(torch.complex128) - want).abs() <= units * 2.0 ** -23.5 * bound).all())
+    if prec == "f32" and pattern == "last":
+        assert fro(rho, want) <= 2.0 ** -23
     grad = qst.grad_product(G, T, tau, prec)
     assert fro(grad, (G64 @ T64) * (2 / tau64)) <= 2.0 ** -19
 
