@@ -8,8 +8,8 @@ in HBM before timing starts, as one call, qst_likelihood_grad:
     first adjoint pass fused, p never stored), then 2/tau G' T.
 The headline path is QST_F32X6 (FP32 storage and FP32-level accuracy; the
 two complex products on the 16-bit matrix cores from two-part fp16 splits,
-their operand planes formed inside the call); the FP64, FP32
-(the same products, G' written) and BF16 paths, the same step as two calls
+which this workload's dense operands take); the FP64, FP32
+(the same products) and BF16 paths, the same step as two calls
 (qst_likelihood returning G', then qst_grad_product) and as four separate
 calls with p stored (qst_state_map, qst_povm_probs, qst_nll,
 qst_nll_backward) are reported alongside, each with its error against the
@@ -50,13 +50,14 @@ METRIC = "likelihood fwd+bwd evals/sec at N=11 on 1 GPU; % HBM/MFMA peak; max|Δ
 
 PREC_NOTE = {
     "f64": "complex128 storage, FP64 MFMA products, FP64 POVM passes and NLL",
-    "f32": "complex64 storage, split fp16 products as f32x6 from N = 10 (FP32 MFMA products, 3M form, below), FP32 "
-           "POVM passes, tau and NLL sum in FP64",
+    "f32": "complex64 storage, FP32 MFMA products (3M form), from N = 10 split fp16 products as f32x6 where both "
+           "operands are dense, FP32 POVM passes, tau and NLL sum in FP64",
     "bf16": "complex64 storage, T T^dagger on bf16-rounded T (BF16 MFMA, FP32 accumulate), G' T with split "
             "bf16 operands, FP32 POVM passes, tau and NLL sum in FP64",
     "f32x6": "complex64 storage; both complex products with every FP32 operand (row-scaled) split into two fp16 "
-             "parts, ten MFMA products per complex product on the FP16 MFMA, FP32 accumulation "
-             "(FP32-accurate); FP32 POVM passes, tau and NLL sum in FP64",
+             "parts where both operands are dense (as here), ten MFMA products per complex product on the FP16 MFMA, "
+             "and exactly into three bf16 parts elsewhere, FP32 accumulation (FP32-accurate); FP32 POVM passes, tau "
+             "and NLL sum in FP64",
 }
 
 # MI355X published peaks
@@ -71,11 +72,12 @@ PEAK_HBM_GBS = 8000.0
 # them); otherwise the reported traffic is null.
 TRAFFIC_X6_SOURCES = ["paper_2207_05341_amd/csrc/k_xgemm.hip", "paper_2207_05341_amd/csrc/qst_device.h",
                       "paper_2207_05341_amd/csrc/qst_split.h", "paper_2207_05341_amd/csrc/qst_xtile.h",
+                      "paper_2207_05341_amd/csrc/qst_xgemm.h",
                       "paper_2207_05341_amd/csrc/qst_plan.h", "paper_2207_05341_amd/build.py"]
 TRAFFIC = {
-    # N = 11, d = 2048: 98457.0 KiB fetched x 1.9998 + 32768.0 KiB written x 1.0000
-    "hemm_x6": {"bytes": 235.17e6, "sources": TRAFFIC_X6_SOURCES,
-                "sources_sha256": "7741f5804552b9859d2f8581c883117d5b8ac1ceeb0754f5af2875fbff072dcf"},
+    # N = 11, d = 2048: 98469.0 KiB fetched x 1.9998 + 32768.0 KiB written x 1.0000
+    "hemm_x6": {"bytes": 235.20e6, "sources": TRAFFIC_X6_SOURCES,
+                "sources_sha256": "885bf9611cf945991648eae6739b5d36cc3efd853a3fa7edbe8a1d139376cf42"},
 }
 
 
@@ -925,7 +927,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": f"N={n} single state: T {d}x{d} complex Ginibre, {4 ** n} tetrahedral-POVM "
                                f"outcomes, f from 10^7 multinomial shots; forward+adjoint as one call, qst_likelihood_grad "
-                               f"(p and G' not stored)",
+                               f"(p not stored)",
                    "n_qubits": n, "precision": args.prec, "precision_note": PREC_NOTE[args.prec],
                    "parallelism": "none (1 GPU)"},
         "roofline": roofline,

@@ -38,15 +38,13 @@
 // FP32 rounding per term.  K2 and K3 go to the accumulators of im and re, K1
 // has its own, added once at the end of a segment.
 //
-// What bounds it: power.  At N = 11 under sustained load the eight XCDs run
-// G' T at 1.55 .. 1.72 GHz (2.4 nominal); a schedule that took 12% fewer
-// cycles ran at 11% lower clocks, in the same time.  G' T at N = 11 (172
-// GFLOP): 149 us, 1.15 PFLOP/s, what a large fp16 library product reaches on
-// this card (1.11).  Twelve products per block (four per correction):
-// 162 us; all in the three-product form (nine, with re + im planes as
-// operands) needs 1.5 times the LDS and plane bytes.  A split into three
-// bf16 parts with six products per real product, in the three-product form
-// (18): 224 us, and two times the plane bytes.
+// What bounds it: power.  At N = 11 under sustained load G' T runs at 1.65 GHz
+// (active cycles over its time; 2.4 nominal): 172 GFLOP in 150 us, 1.15
+// PFLOP/s, what a large fp16 library product reaches on this card (1.14).
+// Twelve products per block (four per correction): 162 us; all in the
+// three-product form (nine, with re + im planes as operands) needs 1.5 times
+// the LDS and plane bytes.  The three-part bf16 products (18): 224 us on the
+// same operands, and two times the plane bytes.
 //
 // Operand planes.  A split pass writes each operand once per call as fp16
 // planes in the order the v_mfma_f32_32x32x16_f16 fragments read them: a

@@ -9,7 +9,8 @@
 // S = T T^dagger, P1 = Tr Tr^T, P2 = Ti Ti^T, P3 = (Tr + Ti)(Tr - Ti)^T,
 // re = P1 + P2, im = P3 - P1 + P2.  The sums are formed in FP32 before the
 // split.  Eighteen MFMA products where the fp16 form takes ten, and 1.5 to
-// 2.25 times its plane bytes: G' T at N = 11 227 us against 147.
+// 2.25 times its plane bytes: G' T at N = 11, Gaussian operands, 224 us against
+// 150 (triangular T: 197 us).
 //
 // 128 x 128 tiles by four waves of 64 x 64, stream-K for T T^dagger
 // (qst_xgemm.h).  The K loop runs over slabs: one real product's three splits
